@@ -959,11 +959,6 @@ __global__ void k_scatter_rows(const R* __restrict__ src, const int32_t* __restr
   dst[(int64_t)perm[s] * width + k] = src[t];
 }
 
-__global__ void k_copy_rows(const double* __restrict__ src, double* __restrict__ dst, int64_t count) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < count) dst[t] = src[t];
-}
-
 // Charges from primitives (Sec. 4.3): Q = (rho, rho v, P/(gamma-1) + rho v^2/2) V.
 // prim and Q may be the same array (each thread reads its row before writing it).
 __global__ void k_init_charges(const SegDesc* __restrict__ segs, const int32_t* __restrict__ sseg, int64_t n,
@@ -1189,12 +1184,6 @@ void launch_init_charges(const SegDesc* segs, const int32_t* sseg, int64_t n, co
   if (n <= 0) return;
   hipLaunchKernelGGL(k_init_charges, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, segs, sseg, n, prim_slots,
                      perm, geo, Q_slots, only_fresh);
-}
-
-void launch_copy_rows(const double* src, double* dst, int64_t n, int width, hipStream_t st) {
-  const int64_t count = n * width;
-  if (count <= 0) return;
-  hipLaunchKernelGGL(k_copy_rows, dim3(blocks_for(count, kThreads)), dim3(kThreads), 0, st, src, dst, count);
 }
 
 #define MM_INSTANTIATE(R)                                                                                          \

@@ -23,18 +23,6 @@ constexpr int kGroup = 8;                        // lanes per cell in the assemb
 constexpr int kMeshThreads = 256;
 constexpr int kCellsPerBlock = kMeshThreads / kGroup;
 
-// 64 times the longest list of each slice of 64 cells (one wavefront per slice).
-__global__ __launch_bounds__(256) void k_slice_width(const unsigned long long* __restrict__ counts, int64_t n,
-                                                     unsigned long long* __restrict__ sw) {
-  const int64_t k = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  const int64_t s = 64 * k + __lane_id();
-  const int64_t nslices = (n + 63) / 64;
-  int w = s < n ? (int)(counts[s] >> 32) : 0;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) w = max(w, __shfl_xor(w, o, 64));
-  if (k < nslices && __lane_id() == 0) sw[k] = 64ull * (unsigned long long)w;
-}
-
 // Eight lanes per cell; lane l takes the cell's faces l, l + 8, ... (a lane
 // walks two or three faces: more cells per wavefront than with sixteen
 // lanes, whose last lanes idle while the first take a second face).
@@ -195,13 +183,6 @@ __global__ __launch_bounds__(kMeshThreads) void k_build_mesh(
   }
 }
 
-__global__ void k_copy_totals(const unsigned long long* off, int64_t n, DevStatus* st) {
-  if (threadIdx.x == 0) {
-    st->n_faces = off[n] & 0xffffffffull;
-    st->n_csr = off[n] >> 32;
-  }
-}
-
 __global__ void k_export_cells(int64_t n, const int32_t* __restrict__ perm, const double* __restrict__ spos,
                                const double* __restrict__ geo, double* V, double* centroid) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -232,23 +213,18 @@ __global__ void k_export_faces(int64_t nf, const int32_t* __restrict__ perm, con
 
 void launch_build_mesh(const double* spos, const double* geo, int64_t n, const SegDesc* segs, const int32_t* sseg,
                        const StageNbr* stage_nb, const StageGeo* stage_geo, const unsigned long long* counts,
-                       const unsigned long long* off, unsigned long long* sw, unsigned long long* soff,
-                       unsigned long long* scan_tmp, int64_t face_cap, int64_t sell_cap, Face* faces, int32_t* csr,
-                       void* nbr, int precision, double* minv, DevStatus* st_dev, SegStatus* segst, hipStream_t st) {
-  if (n > 0) {
-    const int64_t nslices = (n + 63) / 64;
-    hipLaunchKernelGGL(k_slice_width, dim3(blocks_for(nslices, 4)), dim3(256), 0, st, counts, n, sw);
-    scan_u64(sw, soff, nslices, scan_tmp, st);
-    if (precision == 1)   // MM_MIXED
-      hipLaunchKernelGGL(k_build_mesh<float>, dim3(blocks_for(n, kCellsPerBlock)), dim3(kMeshThreads), 0, st, spos,
-                         geo, n, segs, sseg, stage_nb, stage_geo, counts, off, soff, face_cap, sell_cap, faces, csr,
-                         (NbrEntry<float>*)nbr, minv, st_dev, segst);
-    else
-      hipLaunchKernelGGL(k_build_mesh<double>, dim3(blocks_for(n, kCellsPerBlock)), dim3(kMeshThreads), 0, st, spos,
-                         geo, n, segs, sseg, stage_nb, stage_geo, counts, off, soff, face_cap, sell_cap, faces, csr,
-                         (NbrEntry<double>*)nbr, minv, st_dev, segst);
-  }
-  hipLaunchKernelGGL(k_copy_totals, dim3(1), dim3(64), 0, st, off, n, st_dev);
+                       const unsigned long long* off, const unsigned long long* soff, int64_t face_cap,
+                       int64_t sell_cap, Face* faces, int32_t* csr, void* nbr, int precision, double* minv,
+                       DevStatus* st_dev, SegStatus* segst, hipStream_t st) {
+  if (n <= 0) return;
+  if (precision == 1)   // MM_MIXED
+    hipLaunchKernelGGL(k_build_mesh<float>, dim3(blocks_for(n, kCellsPerBlock)), dim3(kMeshThreads), 0, st, spos,
+                       geo, n, segs, sseg, stage_nb, stage_geo, counts, off, soff, face_cap, sell_cap, faces, csr,
+                       (NbrEntry<float>*)nbr, minv, st_dev, segst);
+  else
+    hipLaunchKernelGGL(k_build_mesh<double>, dim3(blocks_for(n, kCellsPerBlock)), dim3(kMeshThreads), 0, st, spos,
+                       geo, n, segs, sseg, stage_nb, stage_geo, counts, off, soff, face_cap, sell_cap, faces, csr,
+                       (NbrEntry<double>*)nbr, minv, st_dev, segst);
 }
 
 void launch_export_mesh(int64_t n, int64_t nf, const int32_t* perm, const double* spos, const double* geo,

@@ -263,7 +263,7 @@ mm_status mm_batch_step(mm_batch* b, mm_sim_info* info, int32_t info_cap, int32_
     n += s.n;
     any_fresh |= s.fresh != 0;
   }
-  if (mm_status r = E.upload(nseg)) return b->fail(r, E.err);
+  if (mm_status r = E.set_segments(nseg)) return b->fail(r, E.err);
   const int64_t hi = slot_high(b);
   if (b->layout_dirty) {
     launch_fill_i32(b->slot_seg, -1, hi, E.stream);

@@ -39,10 +39,11 @@ struct Engine {
   // Sort and tessellation.
   int32_t *key = nullptr, *perm = nullptr, *sseg = nullptr, *deferred = nullptr, *dcells = nullptr, *redo = nullptr;
   double *spos = nullptr, *geo = nullptr, *rmax2 = nullptr, *minv = nullptr;
-  unsigned long long *bcount = nullptr, *boff = nullptr, *scan_tmp = nullptr, *counts = nullptr, *off = nullptr;
+  uint32_t* bcount = nullptr;            // points of each bucket
+  unsigned long long *boff = nullptr, *scan_tmp = nullptr, *counts = nullptr, *off = nullptr;
   unsigned long long* sbase = nullptr;   // sub-table base of each bucket (dense buckets)
   uint32_t* soffs = nullptr;             // sub-bucket offsets of the dense buckets
-  unsigned long long *sw = nullptr, *soff = nullptr;   // slice widths and offsets of the per-cell lists
+  unsigned long long* soff = nullptr;    // slice offsets of the per-cell lists
   StageNbr* stage_nb = nullptr;
   StageGeo* stage_geo = nullptr;
   Face* faces = nullptr;
@@ -71,8 +72,8 @@ struct Engine {
   SegDesc* segs_host = nullptr;       // pinned staging of the table
   SegStatus* segst_host = nullptr;    // pinned mirror
   DevStatus* st_host = nullptr;       // pinned mirror
-  hipEvent_t upload_done = nullptr;
   int nseg = 0;
+  bool table_in_flight = false;       // work that reads the pinned table may still run
   // Mesh currently held.
   int64_t n = 0, n_faces = 0, nbt = 0;
   // List lengths of the last tessellation read back (none yet: -1); they
@@ -111,13 +112,18 @@ struct Engine {
   bool arena_mode = false;
 
   // Host staging of the segment table, safe to write once returned; then
-  // upload(nseg) copies the first nseg descriptors (stream-ordered).
+  // set_segments(k) makes its first k descriptors the segments of the next
+  // tessellation, which takes them to the device.  put_segment takes
+  // the first one there at once (new parameters for the mesh held).
   SegDesc* staging();
-  mm_status upload(int nseg);
+  mm_status set_segments(int nseg);
+  mm_status put_segment();
   void reset_status();
   // Sort, cell construction and mesh assembly of n cells living in n_slots
   // caller-order slots (slot_seg: segment per slot, NULL for one segment).
-  void enqueue_tessellation(const double* pos, int64_t n_slots, const int32_t* slot_seg, int64_t n, int64_t nbt);
+  // remesh: the second tessellation of a step.
+  void enqueue_tessellation(const double* pos, int64_t n_slots, const int32_t* slot_seg, int64_t n, int64_t nbt,
+                            bool remesh = false);
   // One whole step: tessellation, charges of fresh segments, states, two
   // gradients with the predictor, fluxes, update and drift.  Q, pos and w
   // are slot-order arrays, updated in place.

@@ -165,7 +165,6 @@ void reserve_buffers(Engine& E, Res& R, bool single) {
   R(&E.scan_tmp, scan_tmp_elems(std::max(N, nbcap)));
   R(&E.counts, N);
   R(&E.off, N + 1);
-  R(&E.sw, (N + 63) / 64 + 1);
   R(&E.soff, (N + 63) / 64 + 2);
   R(&E.stage_nb, (size_t)N * kMaxFaces);
   R(&E.stage_geo, (size_t)N * kMaxFaces);
@@ -247,7 +246,6 @@ mm_status Engine::init(int prec, int64_t n_cap, int64_t s_cap, int64_t f_cap, in
   ok &= hipHostMalloc((void**)&segs_host, sizeof(SegDesc) * segcap, hipHostMallocDefault) == hipSuccess;
   ok &= hipHostMalloc((void**)&segst_host, sizeof(SegStatus) * segcap, hipHostMallocDefault) == hipSuccess;
   ok &= hipHostMalloc((void**)&st_host, sizeof(DevStatus), hipHostMallocDefault) == hipSuccess;
-  ok &= hipEventCreateWithFlags(&upload_done, hipEventDisableTiming) == hipSuccess;
   for (hipEvent_t& e : ev) ok &= hipEventCreate(&e) == hipSuccess;
   if (!ok) {
     const hipError_t e = hipGetLastError();
@@ -265,7 +263,7 @@ void Engine::release() {
     *this = Engine();
     return;
   }
-  void* ptrs[] = {key, perm, sseg, deferred, dcells, redo, spos, geo, rmax2, minv, bcount, boff, sbase, soffs, scan_tmp, counts, off, sw, soff,
+  void* ptrs[] = {key, perm, sseg, deferred, dcells, redo, spos, geo, rmax2, minv, bcount, boff, sbase, soffs, scan_tmp, counts, off, soff,
                   stage_nb, stage_geo, faces, csr, nbr, U, G, Uh, rec, phi, w, Qs, pn, pos_half, Uh_slots,
                   Xe, Xh, recx, phiX, machF, machs, Ss, segs, segst, st};
   for (void* q : ptrs)
@@ -273,54 +271,54 @@ void Engine::release() {
   void* hptrs[] = {segs_host, segst_host, st_host};
   for (void* q : hptrs)
     if (q) (void)hipHostFree(q);
-  if (upload_done) (void)hipEventDestroy(upload_done);
   for (hipEvent_t& e : ev)
     if (e) (void)hipEventDestroy(e);
   *this = Engine();
 }
 
-mm_status Engine::upload(int k) {
+mm_status Engine::set_segments(int k) {
   if (k < 0 || k > segcap) return fail(MM_EINVAL, "segment count beyond capacity");
   nseg = k;
-  if (k == 0) return MM_OK;
-  if (arena_mode) {
-    // Each descriptor travels as a kernel argument (copied at the launch):
-    // no staging memory, and the host copy is free again at once.
-    for (int q = 0; q < k; ++q) hipLaunchKernelGGL(k_put_segment, dim3(1), dim3(64), 0, stream, segs_host[q], segs + q);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(MM_EHIP, std::string("segment upload: ") + hipGetErrorString(e));
-    return MM_OK;
-  }
-  const hipError_t e = hipMemcpyAsync(segs, segs_host, sizeof(SegDesc) * k, hipMemcpyHostToDevice, stream);
+  return MM_OK;
+}
+
+mm_status Engine::put_segment() {
+  // The descriptor travels as a kernel argument (copied at the launch).
+  hipLaunchKernelGGL(k_put_segment, dim3(1), dim3(64), 0, stream, segs_host[0], segs);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(MM_EHIP, std::string("segment upload: ") + hipGetErrorString(e));
-  (void)hipEventRecord(upload_done, stream);
   return MM_OK;
 }
 
 SegDesc* Engine::staging() {
-  // The staging buffer may be rewritten only once the last upload has run.
-  if (!arena_mode) (void)hipEventSynchronize(upload_done);
+  // The table may be rewritten only once the last tessellation has read it:
+  // every call that starts one waits for the stream, unless it failed first.
+  if (table_in_flight) (void)hipStreamSynchronize(stream);
+  table_in_flight = false;
   return segs_host;
 }
 
 void Engine::reset_status() { launch_status_reset(st, segst, nseg, stream); }
 
 void Engine::enqueue_tessellation(const double* pos, int64_t n_slots, const int32_t* slot_seg, int64_t n_cells,
-                                  int64_t n_buckets) {
+                                  int64_t n_buckets, bool remesh) {
   nbt = n_buckets;
   mark(0);
-  launch_sort(pos, n_slots, slot_seg, n_cells, segs, n_buckets, bcount, boff, scan_tmp, sbase, soffs, key, perm,
-              sseg, spos, dcells, st, segst, stream);
+  // The arrival ranks live in the shell pass's bounds, which are written
+  // only after the sort (8 bytes per cell: room for two slots per cell).
+  if (nseg > 1) table_in_flight = true;
+  launch_sort(pos, n_slots, slot_seg, segs_host, segs, nseg, remesh, n_buckets, bcount, boff, scan_tmp, sbase, soffs,
+              key, (int32_t*)rmax2, perm, sseg, spos, dcells, st, segst, stream);
   mark(1);
-  // One segment: its grid (the descriptor uploaded last) travels with the
+  // One segment: its grid (the descriptor set last) travels with the
   // pair passes' arguments.
   last_dense_cap = launch_tessellate(spos, n_cells, segs, sseg, boff, sbase, soffs, stage_nb, stage_geo, counts, geo,
                                      rmax2, deferred, dcells, redo, hints, nseg == 1 ? &segs_host[0].g : nullptr, st,
                                      segst, stream);
   mark(2);
-  scan_u64(counts, off, n_cells, scan_tmp, stream);
-  launch_build_mesh(spos, geo, n_cells, segs, sseg, stage_nb, stage_geo, counts, off, sw, soff, scan_tmp, fcap,
-                    sell_cap, faces, csr, nbr, precision, minv, st, segst, stream);
+  launch_mesh_scan(counts, n_cells, off, soff, scan_tmp, st, stream);
+  launch_build_mesh(spos, geo, n_cells, segs, sseg, stage_nb, stage_geo, counts, off, soff, fcap, sell_cap, faces, csr,
+                    nbr, precision, minv, st, segst, stream);
 }
 
 namespace {
@@ -351,8 +349,7 @@ void enqueue_hydro(Engine& E, double* pos, double* w_slots, double* Q, int64_t n
     if (E.timing) (void)hipEventRecord(E.ev[9], E.stream);
     launch_half_park<R>(E.segs, E.sseg, n, E.perm, Uh, E.w, E.segst, pos, E.pos_half, (R*)E.Uh_slots, w_slots,
                         E.stream);
-    launch_remesh_reset(E.st, E.stream);
-    E.enqueue_tessellation(E.pos_half, n, nullptr, n, nbt);
+    E.enqueue_tessellation(E.pos_half, n, nullptr, n, nbt, true);
     launch_half_unpark<R>(n, E.perm, (const R*)E.Uh_slots, w_slots, Q, Uh, E.w, E.Qs, E.stream);
     if (E.timing) (void)hipEventRecord(E.ev[10], E.stream);
   }
@@ -382,7 +379,6 @@ void Engine::enqueue_step(double* pos, double* w_slots, double* Q, int64_t n_slo
   const bool half = half_step && pos_half && Uh_slots && n_slots == n_cells && !slot_seg && !S;
   if (!(Ss && n_slots == n_cells && !slot_seg)) S = nullptr, mach = nullptr;
   remeshed = half;
-  reset_status();
   enqueue_tessellation(pos, n_slots, slot_seg, n_cells, n_buckets);
   mark(3);
   if (precision == MM_MIXED) enqueue_hydro<float>(*this, pos, w_slots, Q, n_cells, any_fresh, half, n_buckets, S, mach);
@@ -391,13 +387,19 @@ void Engine::enqueue_step(double* pos, double* w_slots, double* Q, int64_t n_slo
 }
 
 mm_status Engine::readback() {
+  // Pinned mirrors are written by a kernel (one launch instead of two copies);
+  // the arena's mirrors are ordinary host memory.
+  if (!arena_mode) launch_publish(st, segst, nseg, st_host, segst_host, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(MM_EHIP, std::string("launch: ") + hipGetErrorString(e));
-  e = hipMemcpyAsync(st_host, st, sizeof(DevStatus), hipMemcpyDeviceToHost, stream);
-  if (e == hipSuccess && nseg > 0)
-    e = hipMemcpyAsync(segst_host, segst, sizeof(SegStatus) * nseg, hipMemcpyDeviceToHost, stream);
+  if (arena_mode) {
+    e = hipMemcpyAsync(st_host, st, sizeof(DevStatus), hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess && nseg > 0)
+      e = hipMemcpyAsync(segst_host, segst, sizeof(SegStatus) * nseg, hipMemcpyDeviceToHost, stream);
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return fail(MM_EHIP, std::string("status readback: ") + hipGetErrorString(e));
+  table_in_flight = false;
   const DevStatus& s = *st_host;
   hints.dense_cells = s.n_dense_cells;
   hints.redo = s.n_redo;

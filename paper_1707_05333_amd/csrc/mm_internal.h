@@ -49,9 +49,10 @@ struct DevStatus {
   int bad_cell;                  // lowest internal cell index with a failure
   int n_overflow;                // of those, cells whose first-pass candidates overflowed
   int n_dense;                   // buckets with a sub-grid (length of the sort's dense-bucket list)
-  int n_dense_cells;             // cells for the dense first pass (follows n_dense: cleared together)
-  int n_redo;                    // cells the two-cell first pass hands to the one-cell one (cleared with n_dense)
-  int n_dredo;                   // cells the two-cell dense pass hands to the one-cell one (cleared with n_dense)
+  int n_dense_cells;             // cells for the dense first pass
+  int n_redo;                    // cells the two-cell first pass hands to the one-cell one
+  int n_dredo;                   // cells the two-cell dense pass hands to the one-cell one
+  int n_sub;                     // sub-bucket offsets handed out
   unsigned long long n_faces;    // unique faces (copy of the scan total)
   unsigned long long n_csr;      // directed faces (copy of the scan total)
   int asym_cell, asym_nbr;       // one face without a partner (internal cells), for diagnostics
@@ -285,28 +286,35 @@ inline __device__ void seg_fail(DevStatus* st, SegStatus* segst, int seg, int bi
 // Host-side launchers (each enqueues on `st`).
 // ---------------------------------------------------------------------------
 
-// Exclusive prefix sum of n uint64 values into out[0..n] (out[n] = total).
-// tmp must hold scan_tmp_elems(n) elements.
+// Elements of the scans' scratch for n items.
 size_t scan_tmp_elems(int64_t n);
-void scan_u64(const unsigned long long* in, unsigned long long* out, int64_t n, unsigned long long* tmp,
-              hipStream_t st);
 
-void launch_fill_u64(unsigned long long* p, unsigned long long v, int64_t n, hipStream_t st);
 void launch_status_reset(DevStatus* s, SegStatus* segst, int nseg, hipStream_t st);
-// Clears the per-mesh counters (deferred and overflowing cells, face and
-// list totals) before a second tessellation in one step; failure flags, the
-// timestep minimum and the floor counts are kept.
-void launch_remesh_reset(DevStatus* s, hipStream_t st);
+// Copies the status to pinned host memory.
+void launch_publish(const DevStatus* s, const SegStatus* segst, int nseg, DevStatus* host_s, SegStatus* host_segst,
+                    hipStream_t st);
 
-// Bucket sort of the generators of every segment (grid hash, counting sort,
-// caller order inside a bucket).  pos covers n_slots slots; slot_seg[q] is
-// the segment of slot q (-1: unused slot), or NULL for one segment covering
-// every slot.  Writes perm (internal -> slot), the segment of each internal
-// cell, the sorted positions and the bucket offsets of all nbt buckets.
-void launch_sort(const double* pos, int64_t n_slots, const int32_t* slot_seg, int64_t n, const SegDesc* segs,
-                 int64_t nbt, unsigned long long* bcount, unsigned long long* boff, unsigned long long* scan_tmp,
-                 unsigned long long* sbase, uint32_t* soffs, int32_t* key, int32_t* perm, int32_t* sseg,
-                 double* spos, int32_t* dcells, DevStatus* st_dev, SegStatus* segst, hipStream_t st);
+// Start of a tessellation and bucket sort of the generators of every segment
+// (grid hash, counting sort, caller order inside a bucket).  The segment
+// table is written to segs from segs_host (one segment: by value; more: from
+// pinned memory, which must stay as it is until the stream has been waited
+// for) and the status reset; with remesh (a second tessellation in one step)
+// the table, failure flags, timestep minimum and floor counts are kept and
+// only the counters of the mesh cleared.  pos covers n_slots slots;
+// slot_seg[q] is the segment of slot q (-1: unused slot), or NULL for one
+// segment covering every slot.  Writes perm (internal -> slot), the segment of
+// each internal cell, the sorted positions and the bucket offsets of all nbt
+// buckets.  key and rank are scratch of n_slots elements.
+void launch_sort(const double* pos, int64_t n_slots, const int32_t* slot_seg, const SegDesc* segs_host, SegDesc* segs,
+                 int nseg, bool remesh, int64_t nbt, uint32_t* bcount, unsigned long long* boff,
+                 unsigned long long* scan_tmp, unsigned long long* sbase, uint32_t* soffs, int32_t* key, int32_t* rank,
+                 int32_t* perm, int32_t* sseg, double* spos, int32_t* dcells, DevStatus* st_dev, SegStatus* segst,
+                 hipStream_t st);
+
+// Offsets of the unique faces (off, n + 1 entries) and of the list slices
+// (soff) from the cells' packed face counts, and their totals in the status.
+void launch_mesh_scan(const unsigned long long* counts, int64_t n, unsigned long long* off, unsigned long long* soff,
+                      unsigned long long* tmp, DevStatus* st_dev, hipStream_t st);
 
 // Lengths of an earlier tessellation's cell lists (-1: none yet).  They size
 // the grids of the passes that read the lists, never their results (those
@@ -334,13 +342,13 @@ inline __host__ __device__ int64_t sell_slot(const unsigned long long* soff, int
   return (int64_t)soff[s >> 6] + 64ll * e + (s & 63);
 }
 
-// Unique faces, per-cell lists (slice offsets soff, from the slice widths sw),
-// neighbour entries and inverse LSQ matrices from the staged lists.
+// Unique faces, per-cell lists (slice offsets soff), neighbour entries and
+// inverse LSQ matrices from the staged lists.
 void launch_build_mesh(const double* spos, const double* geo, int64_t n, const SegDesc* segs, const int32_t* sseg,
                        const StageNbr* stage_nb, const StageGeo* stage_geo, const unsigned long long* counts,
-                       const unsigned long long* off, unsigned long long* sw, unsigned long long* soff,
-                       unsigned long long* scan_tmp, int64_t face_cap, int64_t sell_cap, Face* faces, int32_t* csr,
-                       void* nbr, int precision, double* minv, DevStatus* st_dev, SegStatus* segst, hipStream_t st);
+                       const unsigned long long* off, const unsigned long long* soff, int64_t face_cap,
+                       int64_t sell_cap, Face* faces, int32_t* csr, void* nbr, int precision, double* minv,
+                       DevStatus* st_dev, SegStatus* segst, hipStream_t st);
 
 // Hydro kernels, instantiated for double (MM_FP64) and float (MM_MIXED).
 // Slot-space arrays (Q, pos, w, prim) are indexed through perm.  dt_src
@@ -442,8 +450,6 @@ void launch_init_charges(const SegDesc* segs, const int32_t* sseg, int64_t n, co
 void launch_export_mesh(int64_t n, int64_t nf, const int32_t* perm, const double* spos, const double* geo,
                         const Face* faces, double* V, double* centroid, int32_t* fi, int32_t* fj, int32_t* fc,
                         double* fA, double* ff, hipStream_t st);
-// Copies n rows of `width` doubles (device to device, may not overlap).
-void launch_copy_rows(const double* src, double* dst, int64_t n, int width, hipStream_t st);
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st);
 
 }  // namespace mm

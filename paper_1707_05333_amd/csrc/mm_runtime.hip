@@ -52,7 +52,7 @@ mm_status create_fail(mm_status code, const std::string& msg) {
   } while (0)
 
 // Writes the single segment descriptor (grid of the last sort, parameters,
-// dt cap) and uploads it.
+// dt cap); the next tessellation takes it to the device.
 mm_status put_segment(mm_ctx* c, double dt_max) {
   SegDesc* d = c->E.staging();
   d[0].g = c->grid;
@@ -60,7 +60,7 @@ mm_status put_segment(mm_ctx* c, double dt_max) {
   d[0].dt_max = dt_max;
   d[0].fresh = 0;
   d[0].pad = 0;
-  if (mm_status r = c->E.upload(1)) return fail(c, r, c->E.err);
+  if (mm_status r = c->E.set_segments(1)) return fail(c, r, c->E.err);
   return MM_OK;
 }
 
@@ -98,15 +98,6 @@ mm_status check_n(mm_ctx* c, int64_t n) {
 
 mm_status need_mesh(mm_ctx* c) {
   if (!c->have_mesh) return fail(c, MM_ESTATE, "no tessellation: call mm_tessellate first");
-  return MM_OK;
-}
-
-// Grid, segment upload, status reset and the tessellation of n positions.
-mm_status start_tessellation(mm_ctx* c, int64_t n, const double* pos, double dt_max) {
-  c->grid = make_grid(c->p, n, c->E.rfac, 0);
-  if (mm_status r = put_segment(c, dt_max)) return r;
-  c->E.n = n;
-  c->E.reset_status();
   return MM_OK;
 }
 
@@ -178,7 +169,9 @@ mm_status mm_set_params(mm_ctx* c, const mm_params* p) {
   const bool same_box = p->box[0] == c->p.box[0] && p->box[1] == c->p.box[1] && p->box[2] == c->p.box[2];
   c->p = *p;
   if (!same_box) c->have_mesh = false;
-  if (c->have_mesh) return put_segment(c, INFINITY);
+  if (!c->have_mesh) return MM_OK;
+  if (mm_status r = put_segment(c, INFINITY)) return r;
+  if (mm_status r = c->E.put_segment()) return fail(c, r, c->E.err);
   return MM_OK;
 }
 
@@ -187,7 +180,9 @@ mm_status mm_tessellate(mm_ctx* c, int64_t n, const double* pos, mm_step_info* i
   if (!pos) return fail(c, MM_EINVAL, "pos is NULL");
   if (mm_status r = check_n(c, n)) return r;
   c->have_mesh = false;
-  if (mm_status r = start_tessellation(c, n, pos, INFINITY)) return r;
+  c->grid = make_grid(c->p, n, c->E.rfac, 0);
+  if (mm_status r = put_segment(c, INFINITY)) return r;
+  c->E.n = n;
   c->E.enqueue_tessellation(pos, n, nullptr, n, c->grid.nbt);
   if (mm_status r = readback(c)) return r;
   fill_info(c, info, INFINITY);
