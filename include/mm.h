@@ -206,9 +206,9 @@ mm_status mm_fluxes(mm_ctx *ctx, const void *U_half, const void *grad_half, cons
  * Q: dev [n][5] in/out; info: host out (may be NULL).  Waits for the
  * stream once, at the end.  MM_EINVAL when p.mach_threshold > 0 (use
  * mm_step_entropy).
- * On any error pos and Q keep the values they had before the call (the
- * results are copied out only once the step is known to have succeeded),
- * so the caller can retry from them: after MM_ECAPACITY for the face
+ * On any error pos and Q hold the values they had before the call when it
+ * returns (a failed step is not written out, or put back), so the caller can
+ * retry from them: after MM_ECAPACITY for the face
  * capacity (mm_last_error names it), with a context created with a larger
  * face_capacity; after MM_ENONFINITE (a start-of-step state that is not
  * finite, or a step that produced one), with a smaller dt_max or repaired

@@ -363,10 +363,26 @@ __global__ __launch_bounds__(kThreads) void k_cell_state(const SegDesc* __restri
   seg_min_dt(dti, seg, active, segst);
 }
 
+// The list kernels take a cell's entries in rounds of CH: the round's entries
+// are loaded together, then the rows they point to, then they are summed in
+// order.  A round past the list's end goes on with terms that leave every sum
+// as it is (a branch around them would let the compiler move their loads
+// behind it, one round trip each).
+#define MM_MAX_WAVES(W) __attribute__((amdgpu_waves_per_eu(1, W)))
+
 // Least-squares gradient about the centroids with the S10 limiter (Sec. 4.1);
 // with U_half set, the half-step predictor is applied in the same pass.
+// Bound by its chain of loads on small meshes and by the list stream and the
+// row gathers on large ones.  With one or two entries in flight a lattice
+// cell's 17 entries were 9 to 17 round trips.  Rounds of six: 20 -> 12 us at
+// 1,000 cells, FP64 0.484 -> 0.451 ms at 1,331,000 cells (writing the records),
+// mixed 0.326 -> 0.280 ms; rounds of four, nine and twelve were slower (0.62,
+// 0.48 and 0.52 ms FP64).  In FP64 the displacements of a list's first 18
+// entries stay in LDS for the limiter's pass instead of being read again
+// (0.475 -> 0.451 ms; five wavefronts per CU keep enough loads in flight); the
+// half-sized mixed entries gain nothing from it.
 template <typename R>
-__global__ __launch_bounds__(kThreads) void k_gradient(const SegDesc* __restrict__ segs,
+__global__ __launch_bounds__(64) MM_MAX_WAVES(sizeof(R) == 8 ? 2 : 4) void k_gradient(const SegDesc* __restrict__ segs,
                                                        const int32_t* __restrict__ sseg, int64_t n,
                                                        const R* __restrict__ U,
                                                        const unsigned long long* __restrict__ counts,
@@ -377,6 +393,8 @@ __global__ __launch_bounds__(kThreads) void k_gradient(const SegDesc* __restrict
                                                        double dt_fixed, R* __restrict__ Uh,
                                                        FluxCell<R>* __restrict__ rec, const double* __restrict__ geo,
                                                        const double* __restrict__ spos, SegStatus* segst) {
+  constexpr int CH = 6, KEEP = sizeof(R) == 8 ? 18 : 0;
+  __shared__ R tile[KEEP ? 3 * KEEP : 1][64];
   const int64_t s = xcd_block() * blockDim.x + threadIdx.x;
   if (s >= n) return;
   const int nf = (int)(counts[s] >> 32);
@@ -390,25 +408,58 @@ __global__ __launch_bounds__(kThreads) void k_gradient(const SegDesc* __restrict
   }
 #pragma unroll
   for (int k = 0; k < 15; ++k) b[k] = R(0);
-  // Two entries' loads in flight at once pay in FP64 (10% faster) but not
-  // with the smaller FP32 entries (10% slower).
-  constexpr int kUnroll = sizeof(R) == 8 ? 2 : 1;
-#pragma unroll kUnroll
-  for (int e = 0; e < nf; ++e) {
-    const NbrW<R> E = *nbr_w(nbr, slot0 + 64 * e);
-    const R* dd = nbr_d(nbr, slot0 + 64 * e);
-    const R dx = dd[0], dy = dd[1], dz = dd[2], wg = E.wgt;
-    const R* uo = U + 5 * (int64_t)E.o;
+  auto round = [&](int e0, R (*d)[3]) {
+    R u[CH][5], wg[CH];
+    int o[CH];
 #pragma unroll
-    for (int q = 0; q < 5; ++q) {
-      const R v = uo[q];
-      const R t = wg * (v - ui[q]);
-      b[3 * q] += t * dx;
-      b[3 * q + 1] += t * dy;
-      b[3 * q + 2] += t * dz;
-      umax[q] = v > umax[q] ? v : umax[q];
-      umin[q] = v < umin[q] ? v : umin[q];
+    for (int c = 0; c < CH; ++c) {
+      const int64_t slot = slot0 + 64 * min(e0 + c, nf - 1);
+      const NbrW<R> E = *nbr_w(nbr, slot);
+      const R* dd = nbr_d(nbr, slot);
+      o[c] = e0 + c < nf ? E.o : (int)s;   // past the end: the cell itself, weight zero
+      wg[c] = e0 + c < nf ? E.wgt : R(0);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) d[c][a] = dd[a];
     }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const R* uo = U + 5 * (int64_t)o[c];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) u[c][q] = uo[q];
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        const R v = u[c][q];
+        const R t = wg[c] * (v - ui[q]);
+        b[3 * q] += t * d[c][0];
+        b[3 * q + 1] += t * d[c][1];
+        b[3 * q + 2] += t * d[c][2];
+        umax[q] = v > umax[q] ? v : umax[q];
+        umin[q] = v < umin[q] ? v : umin[q];
+      }
+    }
+  };
+#pragma unroll
+  for (int e0 = 0; e0 < KEEP; e0 += CH) {
+    R d[CH][3];
+    if (e0 < nf) {
+      round(e0, d);
+    } else {
+#pragma unroll
+      for (int c = 0; c < CH; ++c) d[c][0] = d[c][1] = d[c][2] = R(0);
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        tile[3 * (e0 + c) + a][threadIdx.x] = d[c][a];
+      }
+  }
+  for (int e0 = KEEP; e0 < nf; e0 += CH) {
+    R d[CH][3];
+    round(e0, d);
   }
   const double* mi = minv + 6 * s;
   const R m00 = (R)mi[0], m01 = (R)mi[1], m02 = (R)mi[2], m11 = (R)mi[3], m12 = (R)mi[4], m22 = (R)mi[5];
@@ -433,15 +484,27 @@ __global__ __launch_bounds__(kThreads) void k_gradient(const SegDesc* __restrict
     R dpos[5], dneg[5];
 #pragma unroll
     for (int q = 0; q < 5; ++q) dpos[q] = dneg[q] = R(0);
-    for (int e = 0; e < nf; ++e) {
-      const R* dd = nbr_d(nbr, slot0 + 64 * e);
-      const R dx = dd[0], dy = dd[1], dz = dd[2];
+    auto reach = [&](R dx, R dy, R dz) {
 #pragma unroll
       for (int q = 0; q < 5; ++q) {
         const R D = g[3 * q] * dx + g[3 * q + 1] * dy + g[3 * q + 2] * dz;
         dpos[q] = D > dpos[q] ? D : dpos[q];
         dneg[q] = D < dneg[q] ? D : dneg[q];
       }
+    };
+#pragma unroll
+    for (int e = 0; e < KEEP; ++e)   // (a displacement past the list's end is the last one, or zero)
+      reach(tile[3 * e][threadIdx.x], tile[3 * e + 1][threadIdx.x], tile[3 * e + 2][threadIdx.x]);
+    for (int e0 = KEEP; e0 < nf; e0 += CH) {
+      R d[CH][3];
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const R* dd = nbr_d(nbr, slot0 + 64 * min(e0 + c, nf - 1));
+#pragma unroll
+        for (int a = 0; a < 3; ++a) d[c][a] = dd[a];
+      }
+#pragma unroll
+      for (int c = 0; c < CH; ++c) reach(d[c][0], d[c][1], d[c][2]);
     }
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
@@ -691,7 +754,7 @@ __global__ __launch_bounds__(kThreads) void k_entropy_state(int64_t n, const int
 // limiter as k_gradient (one component); then either the half-step value
 // X + dt/2 (-div(X v) + w . grad X) or the face kernel's record.
 template <typename R>
-__global__ __launch_bounds__(kThreads) void k_entropy_gradient(
+__global__ __launch_bounds__(64) MM_MAX_WAVES(8) void k_entropy_gradient(
     const SegDesc* __restrict__ segs, const int32_t* __restrict__ sseg, int64_t n, const R* __restrict__ X,
     const unsigned long long* __restrict__ counts, const unsigned long long* __restrict__ soff,
     const NbrEntry<R>* __restrict__ nbr, const double* __restrict__ minv, int limit, const R* __restrict__ U,
@@ -703,16 +766,31 @@ __global__ __launch_bounds__(kThreads) void k_entropy_gradient(
   const int64_t slot0 = sell_slot(soff, s, 0);   // entry e at slot0 + 64 e
   const R xi = X[s];
   R xmax = xi, xmin = xi, b[3] = {R(0), R(0), R(0)};
-  for (int e = 0; e < nf; ++e) {
-    const NbrW<R> E = *nbr_w(nbr, slot0 + 64 * e);
-    const R* dd = nbr_d(nbr, slot0 + 64 * e);
-    const R v = X[E.o];
-    const R t = E.wgt * (v - xi);
-    b[0] += t * dd[0];
-    b[1] += t * dd[1];
-    b[2] += t * dd[2];
-    xmax = v > xmax ? v : xmax;
-    xmin = v < xmin ? v : xmin;
+  constexpr int CH = 6;
+  for (int e0 = 0; e0 < nf; e0 += CH) {
+    R v[CH], d[CH][3], wg[CH];
+    int o[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int64_t slot = slot0 + 64 * min(e0 + c, nf - 1);
+      const NbrW<R> E = *nbr_w(nbr, slot);
+      const R* dd = nbr_d(nbr, slot);
+      o[c] = e0 + c < nf ? E.o : (int)s;   // past the end: the cell itself, weight zero
+      wg[c] = e0 + c < nf ? E.wgt : R(0);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) d[c][a] = dd[a];
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) v[c] = X[o[c]];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const R t = wg[c] * (v[c] - xi);
+      b[0] += t * d[c][0];
+      b[1] += t * d[c][1];
+      b[2] += t * d[c][2];
+      xmax = v[c] > xmax ? v[c] : xmax;
+      xmin = v[c] < xmin ? v[c] : xmin;
+    }
   }
   const double* mi = minv + 6 * s;
   const R m00 = (R)mi[0], m01 = (R)mi[1], m02 = (R)mi[2], m11 = (R)mi[3], m12 = (R)mi[4], m22 = (R)mi[5];
@@ -724,11 +802,20 @@ __global__ __launch_bounds__(kThreads) void k_entropy_gradient(
                                           : ((hp.limit_mask >> (limit - kLimitMaskBit0)) & 1) != 0;
   if (lim) {
     R dpos = R(0), dneg = R(0);
-    for (int e = 0; e < nf; ++e) {
-      const R* dd = nbr_d(nbr, slot0 + 64 * e);
-      const R D = g[0] * dd[0] + g[1] * dd[1] + g[2] * dd[2];
-      dpos = D > dpos ? D : dpos;
-      dneg = D < dneg ? D : dneg;
+    for (int e0 = 0; e0 < nf; e0 += CH) {
+      R d[CH][3];
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const R* dd = nbr_d(nbr, slot0 + 64 * min(e0 + c, nf - 1));
+#pragma unroll
+        for (int a = 0; a < 3; ++a) d[c][a] = dd[a];
+      }
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const R D = g[0] * d[c][0] + g[1] * d[c][1] + g[2] * d[c][2];
+        dpos = D > dpos ? D : dpos;
+        dneg = D < dneg ? D : dneg;
+      }
     }
     R alpha = R(1);
     if (dpos > R(0)) {
@@ -789,42 +876,57 @@ __device__ inline void cell_flux_sum(int64_t s, const unsigned long long* counts
   const int32_t* list = csr + sell_slot(soff, s, 0);   // entry e at list[64 e]
 #pragma unroll
   for (int q = 0; q < 5; ++q) acc[q] = 0.0;
-  // Unrolled so the loads of four entries are in flight together (the sum
-  // keeps its order).
-#pragma unroll 4
-  for (int e = 0; e < nf; ++e) {
-    const int32_t cf = list[64 * e];
-    const int64_t fid = cf & 0x7fffffff;
-    const double sg = cf < 0 ? 1.0 : -1.0;
+  constexpr int CH = 6;
+  for (int e0 = 0; e0 < nf; e0 += CH) {
+    int32_t cf[CH];
+    R f[CH][5];
 #pragma unroll
-    for (int q = 0; q < 5; ++q) acc[q] += sg * (double)phi[5 * fid + q];
+    for (int c = 0; c < CH; ++c) cf[c] = list[64 * min(e0 + c, nf - 1)];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int64_t fid = cf[c] & 0x7fffffff;
+#pragma unroll
+      for (int q = 0; q < 5; ++q) f[c][q] = phi[5 * fid + q];
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const bool in = e0 + c < nf;   // past the end: minus zero is added
+      const double sg = in && cf[c] < 0 ? 1.0 : -1.0;
+#pragma unroll
+      for (int q = 0; q < 5; ++q) acc[q] += sg * (in ? (double)f[c][q] : 0.0);
+    }
   }
 }
 
-// The charges, positions and entropy charges after the step, in internal
-// order: Qn may be Qs (each thread reads its own row before writing it).
-// Nothing in the caller's arrays changes here; k_commit copies the results
-// out once every failure of the step is known.
+// The charges, positions, mesh velocities and (with the switch) entropy
+// charges after the step, into the caller's slot-order arrays.  Cells of a
+// segment that has failed already are left alone; should a charge come out
+// non-finite here, the host puts the failed segment's state back (k_restore)
+// before the call returns: the start-of-step charges, entropy charges and
+// positions stay in Qs, Ss and spos.  (Writing internal copies first and
+// committing them in a second kernel took 64 bytes per cell more each way:
+// 0.04 ms of the 1M-cell step and a launch of every small one.)
 template <typename R>
-__global__ __launch_bounds__(kThreads) void k_update(const SegDesc* __restrict__ segs,
+__global__ __launch_bounds__(64) MM_MAX_WAVES(4) void k_update(const SegDesc* __restrict__ segs,
                                                      const int32_t* __restrict__ sseg, int64_t n,
                                                      const unsigned long long* __restrict__ counts,
                                                      const unsigned long long* __restrict__ soff,
                                                      const int32_t* __restrict__ csr, const R* __restrict__ phi,
                                                      const double* __restrict__ geo, const int32_t* __restrict__ perm,
-                                                     const double* Qs, double* Qn,
+                                                     const double* __restrict__ Qs, double* __restrict__ Qc,
                                                      const double* __restrict__ spos, const double* __restrict__ w,
-                                                     const double* __restrict__ posc, double* __restrict__ pn,
+                                                     double* posc, double* __restrict__ wc,
                                                      const SegStatus* dt_src, DevStatus* st, SegStatus* segst,
-                                                     bool drift_from_slots, double* Ss,
+                                                     bool drift_from_slots, const double* __restrict__ Ss,
                                                      const R* __restrict__ phiX, const float* __restrict__ machF,
-                                                     float* __restrict__ machs) {
+                                                     double* __restrict__ Sc, float* __restrict__ machc) {
   const int64_t s = xcd_block() * blockDim.x + threadIdx.x;
   if (s >= n) return;
   const int seg = sseg[s];
   const HydroParams& hp = segs[seg].hp;
   double acc[5], Q[5];
-  cell_flux_sum(s, counts, soff, csr, phi, acc);
+  if (segst[seg].flags || (st->flags & F_FACECAP)) return;
+  cell_flux_sum<R>(s, counts, soff, csr, phi, acc);
 #pragma unroll
   for (int q = 0; q < 5; ++q) Q[q] = Qs[5 * s + q] + acc[q];
   const double V = geo[4 * s];
@@ -838,12 +940,24 @@ __global__ __launch_bounds__(kThreads) void k_update(const SegDesc* __restrict__
     const int nfc = (int)(counts[s] >> 32);
     const int32_t* list = csr + sell_slot(soff, s, 0);
     double accX = 0.0;
-#pragma unroll 4
-    for (int e = 0; e < nfc; ++e) {
-      const int32_t cf = list[64 * e];
-      const int64_t fid = cf & 0x7fffffff;
-      accX += (cf < 0 ? 1.0 : -1.0) * (double)phiX[fid];
-      mx = fmaxf(mx, machF[fid]);
+    constexpr int CH = 6;
+    for (int e0 = 0; e0 < nfc; e0 += CH) {
+      int32_t cf[CH];
+      double f[CH];
+      float m[CH];
+#pragma unroll
+      for (int c = 0; c < CH; ++c) cf[c] = list[64 * min(e0 + c, nfc - 1)];
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        f[c] = (double)phiX[cf[c] & 0x7fffffff];
+        m[c] = machF[cf[c] & 0x7fffffff];
+      }
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const bool in = e0 + c < nfc;   // past the end: minus zero is added
+        accX += (in && cf[c] < 0 ? 1.0 : -1.0) * (in ? f[c] : 0.0);
+        mx = fmaxf(mx, m[c]);
+      }
     }
     Snew = Ss[s] + accX;
     if ((double)mx < hp.mach_threshold) {
@@ -873,69 +987,62 @@ __global__ __launch_bounds__(kThreads) void k_update(const SegDesc* __restrict__
     }
   }
   int bad = 0;
+  const int64_t c = perm[s];
 #pragma unroll
   for (int q = 0; q < 5; ++q) {
-    Qn[5 * s + q] = Q[q];
+    Qc[5 * c + q] = Q[q];
     if (!isfinite(Q[q])) bad = 1;
   }
   // Drift by the full step with periodic wrap, from the start-of-step
   // position (the caller's slot when the mesh is a half-step one).
   const double dt = seg_dt(segs, dt_src, seg, 0.0);
-  const int64_t c = drift_from_slots ? perm[s] : 0;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    double x = (drift_from_slots ? posc[3 * c + a] : spos[3 * s + a]) + w[3 * s + a] * dt;
+    const double wa = w[3 * s + a];
+    double x = (drift_from_slots ? posc[3 * c + a] : spos[3 * s + a]) + wa * dt;
     if (x < 0.0) x += hp.L[a];
     if (x >= hp.L[a]) x -= hp.L[a];
-    pn[3 * s + a] = x;
+    posc[3 * c + a] = x;
+    wc[3 * c + a] = wa;
   }
   if (Ss) {
-    Ss[s] = Snew;
-    if (machs) machs[s] = mx;
+    Sc[c] = Snew;
+    if (machc) machc[c] = mx;
     if (!isfinite(Snew)) bad = 1;
   }
   if (bad) seg_fail(st, segst, seg, F_NONFINITE, (int)s);
 }
 
-// Copies the step's results of every segment whose step raised no failure
-// into the caller's slot-order arrays (charges, positions, mesh velocities,
-// and with the entropy column its charges and Mach numbers).  A segment
-// with a failure keeps its state as it was before the step, and so does
-// every segment when the shared face capacity overflowed.
-__global__ __launch_bounds__(kThreads) void k_commit(const int32_t* __restrict__ sseg, int64_t n,
-                                                     const int32_t* __restrict__ perm, const DevStatus* __restrict__ st,
-                                                     const SegStatus* __restrict__ segst,
-                                                     const double* __restrict__ Qn, const double* __restrict__ pn,
-                                                     const double* __restrict__ w, const double* __restrict__ Ss,
-                                                     const float* __restrict__ machs, double* __restrict__ Qc,
-                                                     double* __restrict__ posc, double* __restrict__ wc,
-                                                     double* __restrict__ Sc, float* __restrict__ machc) {
+// Puts the start-of-step charges, positions and entropy charges of every
+// failed segment back into the caller's arrays (of all of them after an
+// overflow of the shared face capacity).
+__global__ __launch_bounds__(kThreads) void k_restore(const int32_t* __restrict__ sseg, int64_t n,
+                                                      const int32_t* __restrict__ perm,
+                                                      const DevStatus* __restrict__ st,
+                                                      const SegStatus* __restrict__ segst,
+                                                      const double* __restrict__ Q0, const double* __restrict__ pos0,
+                                                      const double* __restrict__ S0, double* __restrict__ Qc,
+                                                      double* __restrict__ posc, double* __restrict__ Sc) {
   const int64_t s = xcd_block() * blockDim.x + threadIdx.x;
   if (s >= n) return;
-  if (segst[sseg[s]].flags || (st->flags & F_FACECAP)) return;
+  if (!segst[sseg[s]].flags && !(st->flags & F_FACECAP)) return;
   const int64_t c = perm[s];
 #pragma unroll
-  for (int q = 0; q < 5; ++q) Qc[5 * c + q] = Qn[5 * s + q];
+  for (int q = 0; q < 5; ++q) Qc[5 * c + q] = Q0[5 * s + q];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    posc[3 * c + a] = pn[3 * s + a];
-    wc[3 * c + a] = w[3 * s + a];
-  }
-  if (Sc) {
-    Sc[c] = Ss[s];
-    if (machc) machc[c] = machs[s];
-  }
+  for (int a = 0; a < 3; ++a) posc[3 * c + a] = pos0[3 * s + a];
+  if (Sc) Sc[c] = S0[s];
 }
 
 template <typename R>
-__global__ __launch_bounds__(kThreads) void k_accumulate(int64_t n, const unsigned long long* __restrict__ counts,
+__global__ __launch_bounds__(64) MM_MAX_WAVES(4) void k_accumulate(int64_t n, const unsigned long long* __restrict__ counts,
                                                          const unsigned long long* __restrict__ soff,
                                                          const int32_t* __restrict__ csr, const R* __restrict__ phi,
                                                          const int32_t* __restrict__ perm, double* __restrict__ dQc) {
   const int64_t s = xcd_block() * blockDim.x + threadIdx.x;
   if (s >= n) return;
   double acc[5];
-  cell_flux_sum(s, counts, soff, csr, phi, acc);
+  cell_flux_sum<R>(s, counts, soff, csr, phi, acc);
   const int64_t c = perm[s];
 #pragma unroll
   for (int q = 0; q < 5; ++q) dQc[5 * c + q] = acc[q];
@@ -1019,8 +1126,8 @@ void launch_gradient(const SegDesc* segs, const int32_t* sseg, int64_t n, const 
                      R* U_half, FluxCell<R>* rec, const double* geo, const double* spos, SegStatus* segst,
                      hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_gradient<R>, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, segs, sseg, n, U, counts,
-                     soff, nbr, minv, limit, G, w, dt_src, dt_fixed, U_half, rec, geo, spos, segst);
+  hipLaunchKernelGGL(k_gradient<R>, dim3(blocks_for(n, 64)), dim3(64), 0, st, segs, sseg, n, U, counts, soff, nbr,
+                     minv, limit, G, w, dt_src, dt_fixed, U_half, rec, geo, spos, segst);
 }
 
 template <typename R>
@@ -1072,29 +1179,29 @@ void launch_entropy_gradient(const SegDesc* segs, const int32_t* sseg, int64_t n
                              const double* minv, int limit, const R* U, const R* G, const double* w,
                              const SegStatus* dt_src, R* Xh, XCell<R>* recx, hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_entropy_gradient<R>, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, segs, sseg, n, X,
+  hipLaunchKernelGGL(k_entropy_gradient<R>, dim3(blocks_for(n, 64)), dim3(64), 0, st, segs, sseg, n, X,
                      counts, soff, nbr, minv, limit, U, G, w, dt_src, Xh, recx);
 }
 
 template <typename R>
 void launch_update(const SegDesc* segs, const int32_t* sseg, int64_t n, const unsigned long long* counts,
                    const unsigned long long* soff, const int32_t* csr, const R* phi, const double* geo,
-                   const int32_t* perm, double* Qs, const double* spos, const double* w, const double* pos_slots,
-                   double* pn, const SegStatus* dt_src, DevStatus* st_dev, SegStatus* segst, hipStream_t st,
-                   bool drift_from_slots, double* Ss, const R* phiX, const float* machF, float* machs) {
+                   const int32_t* perm, const double* Qs, double* Q_slots, const double* spos, const double* w,
+                   double* pos_slots, double* w_slots, const SegStatus* dt_src, DevStatus* st_dev, SegStatus* segst,
+                   hipStream_t st, bool drift_from_slots, const double* Ss, const R* phiX, const float* machF,
+                   double* S_slots, float* mach_slots) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_update<R>, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, segs, sseg, n, counts, soff,
-                     csr, phi, geo, perm, Qs, Qs, spos, w, pos_slots, pn, dt_src, st_dev, segst, drift_from_slots, Ss,
-                     phiX, machF, machs);
+  hipLaunchKernelGGL(k_update<R>, dim3(blocks_for(n, 64)), dim3(64), 0, st, segs, sseg, n, counts, soff, csr,
+                       phi, geo, perm, Qs, Q_slots, spos, w, pos_slots, w_slots, dt_src, st_dev, segst,
+                       drift_from_slots, Ss, phiX, machF, S_slots, mach_slots);
 }
 
-void launch_commit(const int32_t* sseg, int64_t n, const int32_t* perm, const DevStatus* st_dev,
-                   const SegStatus* segst, const double* Qn, const double* pn, const double* w, const double* Ss,
-                   const float* machs, double* Q_slots, double* pos_slots, double* w_slots, double* S_slots,
-                   float* mach_slots, hipStream_t st) {
+void launch_restore(const int32_t* sseg, int64_t n, const int32_t* perm, const DevStatus* st_dev,
+                    const SegStatus* segst, const double* Q0, const double* pos0, const double* S0, double* Q_slots,
+                    double* pos_slots, double* S_slots, hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_commit, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, sseg, n, perm, st_dev, segst, Qn, pn, w,
-                     Ss, machs, Q_slots, pos_slots, w_slots, S_slots, mach_slots);
+  hipLaunchKernelGGL(k_restore, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, sseg, n, perm, st_dev, segst,
+                     Q0, pos0, S0, Q_slots, pos_slots, S_slots);
 }
 
 template <typename R>
@@ -1126,8 +1233,10 @@ __global__ __launch_bounds__(kThreads) void k_half_park(const SegDesc* __restric
 template <typename R>
 __global__ __launch_bounds__(kThreads) void k_half_unpark(int64_t n, const int32_t* __restrict__ perm,
                                                           const R* __restrict__ Uhc, const double* __restrict__ wc,
-                                                          const double* __restrict__ Qc, R* __restrict__ Uh,
-                                                          double* __restrict__ w, double* __restrict__ Qs) {
+                                                          const double* __restrict__ Qc,
+                                                          const double* __restrict__ posc, R* __restrict__ Uh,
+                                                          double* __restrict__ w, double* __restrict__ Qs,
+                                                          double* __restrict__ pos0) {
   const int64_t s = xcd_block() * blockDim.x + threadIdx.x;
   if (s >= n) return;
   const int64_t c = perm[s];
@@ -1137,7 +1246,10 @@ __global__ __launch_bounds__(kThreads) void k_half_unpark(int64_t n, const int32
     Qs[5 * s + q] = Qc[5 * c + q];
   }
 #pragma unroll
-  for (int a = 0; a < 3; ++a) w[3 * s + a] = wc[3 * c + a];
+  for (int a = 0; a < 3; ++a) {
+    w[3 * s + a] = wc[3 * c + a];
+    pos0[3 * s + a] = posc[3 * c + a];
+  }
 }
 
 template <typename R>
@@ -1151,18 +1263,19 @@ void launch_half_park(const SegDesc* segs, const int32_t* sseg, int64_t n, const
 
 template <typename R>
 void launch_half_unpark(int64_t n, const int32_t* perm, const R* Uh_slots, const double* w_slots,
-                        const double* Q_slots, R* Uh, double* w, double* Qs, hipStream_t st) {
+                        const double* Q_slots, const double* pos_slots, R* Uh, double* w, double* Qs, double* pos0,
+                        hipStream_t st) {
   if (n <= 0) return;
   hipLaunchKernelGGL(k_half_unpark<R>, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, n, perm, Uh_slots,
-                     w_slots, Q_slots, Uh, w, Qs);
+                     w_slots, Q_slots, pos_slots, Uh, w, Qs, pos0);
 }
 
 template <typename R>
 void launch_accumulate(int64_t n, const unsigned long long* counts, const unsigned long long* soff, const int32_t* csr,
                        const R* phi, const int32_t* perm, double* dQ_slots, hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_accumulate<R>, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, n, counts, soff, csr,
-                     phi, perm, dQ_slots);
+  hipLaunchKernelGGL(k_accumulate<R>, dim3(blocks_for(n, 64)), dim3(64), 0, st, n, counts, soff, csr, phi, perm,
+                       dQ_slots);
 }
 
 template <typename R>
@@ -1208,14 +1321,14 @@ void launch_init_charges(const SegDesc* segs, const int32_t* sseg, int64_t n, co
                                            const double*, const SegStatus*, R*, XCell<R>*, hipStream_t);          \
   template void launch_update<R>(const SegDesc*, const int32_t*, int64_t, const unsigned long long*,              \
                                  const unsigned long long*, const int32_t*, const R*, const double*,              \
-                                 const int32_t*, double*, const double*, const double*, const double*, double*,   \
-                                 const SegStatus*, DevStatus*, SegStatus*, hipStream_t, bool, double*, const R*,  \
-                                 const float*, float*);                                                           \
+                                 const int32_t*, const double*, double*, const double*, const double*, double*,   \
+                                 double*, const SegStatus*, DevStatus*, SegStatus*, hipStream_t, bool,            \
+                                 const double*, const R*, const float*, double*, float*);                         \
   template void launch_half_park<R>(const SegDesc*, const int32_t*, int64_t, const int32_t*, const R*,            \
                                     const double*, const SegStatus*, const double*, double*, R*, double*,         \
                                     hipStream_t);                                                                 \
-  template void launch_half_unpark<R>(int64_t, const int32_t*, const R*, const double*, const double*, R*,         \
-                                      double*, double*, hipStream_t);                                             \
+  template void launch_half_unpark<R>(int64_t, const int32_t*, const R*, const double*, const double*,            \
+                                      const double*, R*, double*, double*, double*, hipStream_t);                 \
   template void launch_accumulate<R>(int64_t, const unsigned long long*, const unsigned long long*,               \
                                      const int32_t*, const R*, const int32_t*, double*, hipStream_t);             \
   template void launch_gather_rows<R>(const R*, const int32_t*, int64_t, int, R*, hipStream_t);                   \

@@ -52,7 +52,7 @@ struct Engine {
   // State in internal order.
   void *U = nullptr, *G = nullptr, *Uh = nullptr, *rec = nullptr, *phi = nullptr;   // rec: FluxCell<R>[n]
   double *w = nullptr, *Qs = nullptr;
-  double* pn = nullptr;   // positions after the drift, before they are committed
+  double* pos0 = nullptr;   // start-of-step positions in the cell order of a half-step mesh
   // Half-step mesh (single simulations): positions r + w dt/2 and the
   // half-step states and mesh velocities parked in slot order while the
   // mesh is rebuilt.  Reserved only when init is asked for them.
@@ -63,7 +63,6 @@ struct Engine {
   // the gathered entropy charges.
   void *Xe = nullptr, *Xh = nullptr, *recx = nullptr, *phiX = nullptr;
   float* machF = nullptr;
-  float* machs = nullptr;   // per cell, internal order
   double* Ss = nullptr;
   // Segment table and status.
   SegDesc* segs = nullptr;
@@ -138,6 +137,10 @@ struct Engine {
   // Waits for the stream and copies the status of the launch set and of
   // the first nseg segments to the host mirrors.
   mm_status readback();
+  // After the readback of a step: if a segment failed, puts the failed
+  // segments' start-of-step state back into the caller's arrays of the last
+  // enqueue_step and waits for it.
+  mm_status undo_failed(double* pos, double* Q, double* S);
   void finish_timing();
   // Status code and message for failure bits (of the whole set or a segment).
   mm_status check_flags(int flags, int bad_cell, std::string& msg) const;

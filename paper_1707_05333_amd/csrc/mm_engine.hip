@@ -52,7 +52,7 @@ int64_t engine_bytes_per_cell(int precision) {
                            + 16 + 8 + 4                                // bucket count, offset, sub-table base; sub-offsets
                            + (int64_t)kMaxFaces * (sizeof(StageNbr) + sizeof(StageGeo))
                            + kListPerCell * (4 + (r == 4 ? sizeof(NbrEntry<float>) : sizeof(NbrEntry<double>)))
-                           + r * (5 + 15 + 5) + 8 * (3 + 5 + 3)        // U, G, Uh, w, Qs, pn
+                           + r * (5 + 15 + 5) + 8 * (3 + 5 + 3)        // U, G, Uh, w, Qs, pos0
                            + (r == 4 ? sizeof(FluxCell<float>) : sizeof(FluxCell<double>));
   const int64_t per_face = sizeof(Face) + 5 * r;                       // face, phi
   return per_cell + kFacesPerCell * per_face;
@@ -180,7 +180,7 @@ void reserve_buffers(Engine& E, Res& R, bool single) {
   R.bytes(&E.phi, 5 * F * rs);
   R(&E.w, 3 * N);
   R(&E.Qs, 5 * N);
-  R(&E.pn, 3 * N);
+  R(&E.pos0, 3 * N);
   if (single) {
     R(&E.pos_half, 3 * slot_cap);
     R.bytes(&E.Uh_slots, 5 * slot_cap * rs);
@@ -189,7 +189,6 @@ void reserve_buffers(Engine& E, Res& R, bool single) {
     R.bytes(&E.recx, N * 4 * rs);
     R.bytes(&E.phiX, F * rs);
     R(&E.machF, F);
-    R(&E.machs, N);
     R(&E.Ss, N);
   }
   R(&E.segs, segcap);
@@ -264,8 +263,8 @@ void Engine::release() {
     return;
   }
   void* ptrs[] = {key, perm, sseg, deferred, dcells, redo, spos, geo, rmax2, minv, bcount, boff, sbase, soffs, scan_tmp, counts, off, soff,
-                  stage_nb, stage_geo, faces, csr, nbr, U, G, Uh, rec, phi, w, Qs, pn, pos_half, Uh_slots,
-                  Xe, Xh, recx, phiX, machF, machs, Ss, segs, segst, st};
+                  stage_nb, stage_geo, faces, csr, nbr, U, G, Uh, rec, phi, w, Qs, pos0, pos_half, Uh_slots,
+                  Xe, Xh, recx, phiX, machF, Ss, segs, segst, st};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   void* hptrs[] = {segs_host, segst_host, st_host};
@@ -350,7 +349,7 @@ void enqueue_hydro(Engine& E, double* pos, double* w_slots, double* Q, int64_t n
     launch_half_park<R>(E.segs, E.sseg, n, E.perm, Uh, E.w, E.segst, pos, E.pos_half, (R*)E.Uh_slots, w_slots,
                         E.stream);
     E.enqueue_tessellation(E.pos_half, n, nullptr, n, nbt, true);
-    launch_half_unpark<R>(n, E.perm, (const R*)E.Uh_slots, w_slots, Q, Uh, E.w, E.Qs, E.stream);
+    launch_half_unpark<R>(n, E.perm, (const R*)E.Uh_slots, w_slots, Q, pos, Uh, E.w, E.Qs, E.pos0, E.stream);
     if (E.timing) (void)hipEventRecord(E.ev[10], E.stream);
   }
   E.mark(5);
@@ -363,12 +362,9 @@ void enqueue_hydro(Engine& E, double* pos, double* w_slots, double* Q, int64_t n
   launch_flux<R>(E.segs, E.fcap, nf_dev, E.faces, rec, E.segst, 0.0, phi, E.segst, E.stream, ent ? recx : nullptr,
                  (R*)E.phiX, E.machF);
   E.mark(7);
-  launch_update<R>(E.segs, E.sseg, n, E.counts, E.soff, E.csr, phi, E.geo, E.perm, E.Qs, E.spos, E.w, pos, E.pn,
-                   E.segst, E.st, E.segst, E.stream, half, ent ? E.Ss : nullptr, (const R*)E.phiX, E.machF, E.machs);
-  // Results reach the caller's arrays only for segments without a failure,
-  // so a failed step leaves the state it started from.
-  launch_commit(E.sseg, n, E.perm, E.st, E.segst, E.Qs, E.pn, E.w, ent ? E.Ss : nullptr, E.machs, Q, pos, w_slots,
-                ent ? S_slots : nullptr, mach_slots, E.stream);
+  launch_update<R>(E.segs, E.sseg, n, E.counts, E.soff, E.csr, phi, E.geo, E.perm, E.Qs, Q, E.spos, E.w, pos, w_slots,
+                   E.segst, E.st, E.segst, E.stream, half, ent ? E.Ss : nullptr, (const R*)E.phiX, E.machF, S_slots,
+                   mach_slots);
 }
 
 }  // namespace
@@ -406,6 +402,14 @@ mm_status Engine::readback() {
   hints.dense_redo = s.n_dredo + std::max<int64_t>(0, (int64_t)s.n_dense_cells - last_dense_cap);
   hints.deferred = s.n_deferred;
   return MM_OK;
+}
+
+mm_status Engine::undo_failed(double* pos, double* Q, double* S) {
+  if (!st_host->flags) return MM_OK;
+  launch_restore(sseg, n, perm, st, segst, Qs, remeshed ? pos0 : spos, Ss, Q, pos, S, stream);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  return e == hipSuccess ? MM_OK : fail(MM_EHIP, std::string("restoring the state: ") + hipGetErrorString(e));
 }
 
 void Engine::finish_timing() {
