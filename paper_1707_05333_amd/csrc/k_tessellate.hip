@@ -1002,18 +1002,9 @@ __device__ inline unsigned own_count(const TessArgs& A, const GridParams& g, con
   return (unsigned)(A.boff[key + 1] - A.boff[key]);
 }
 
-__device__ void defer_cell(const TessArgs& A, int s, double rmax2) {
-  if (__lane_id() == 0) {
-    const int idx = atomicAdd(&A.st->n_deferred, 1);
-    A.deferred[idx] = s;
-    A.rmax2[s] = rmax2;
-  }
-}
-
-// Hands a cell with a dense bucket in its stencil to the dense first pass.
-__device__ void defer_dense(const TessArgs& A, int s) {
-  if (__lane_id() == 0) A.dcells[atomicAdd(&A.st->n_dense_cells, 1)] = s;
-}
+// What a first pass makes of a cell: built (or failed), for the dense first
+// pass (a dense bucket in its stencil), or for the shell pass.
+enum : int { kBuilt = 0, kToDense = 1, kToShells = 2 };
 
 // Squared outer radius of the next shell after [sqrt(lo2), sqrt(hi2)), which
 // held nc candidates: twice the farthest vertex (the shell the cell needs),
@@ -1044,8 +1035,10 @@ __device__ inline double next_shell(double rmax2, double lo2, double hi2, int nc
 //   the candidate slots, until twice the farthest vertex lies inside the
 //   shells done.  The first shell ends at twice the farthest vertex found
 //   before, which bounds the true one (that cell contains the true cell).
+// rm2: for the shell pass, its bound of the farthest vertex (-1: none),
+// set by the first passes.
 template <int MODE>
-__device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* vl = nullptr) {
+__device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2, double4* vl = nullptr) {
   const int seg = A.sseg[s];
   const GridParams& g = A.segs[seg].g;   // read in place (wave-uniform loads), never copied
   const double r[3] = {A.spos[3 * (int64_t)s], A.spos[3 * (int64_t)s + 1], A.spos[3 * (int64_t)s + 2]};
@@ -1069,7 +1062,7 @@ __device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* v
     // beyond what the sort orders: then the call fails (the sort has
     // flagged it) and the cell gets empty outputs here.
     if (cnt > (unsigned)kDenseMax) fail_cell(A, s, seg, F_DENSE);
-    return;
+    return kBuilt;
   }
   if (MODE < 2) {
     const int ring = dense ? min(g.ring, ring_for(g, edge, rloc * rloc)) : g.ring;
@@ -1079,8 +1072,7 @@ __device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* v
     double hi2 = fmin(reach * reach, rloc * rloc);
     int nc = gather<MODE != 0>(S, A, g, s, r, b, ring, 0.0, hi2);
     if (nc < 0) {
-      defer_dense(A, s);
-      return;
+      return kToDense;
     }
     if (MODE == 0 && nc < kFewCands) {
       // A thin region: the first radius, sized for the mean spacing, holds
@@ -1097,21 +1089,20 @@ __device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* v
       if (nhi2 > hi2 && nring <= kThinRing && nring <= g.nb[0] && nring <= g.nb[1] && nring <= g.nb[2]) {
         nc = gather<false>(S, A, g, s, r, b, nring, 0.0, nhi2);
         if (nc < 0) {
-          defer_dense(A, s);
-          return;
+          return kToDense;
         }
         hi2 = nhi2;
       }
     }
     if (nc > kCands) {
       if (__lane_id() == 0) atomicAdd(&A.st->n_overflow, 1);
-      defer_cell(A, s, -1.0);
-      return;
+      rm2 = -1.0;
+      return kToShells;
     }
     sort_candidates(S, nc);
     if (int bad = clip_candidates(S, nc, C)) {
       fail_cell(A, s, seg, bad);
-      return;
+      return kBuilt;
     }
     // A cell whose candidates fell short of twice its farthest vertex goes
     // on with a few more shells here (irregular inputs need them often);
@@ -1126,15 +1117,14 @@ __device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* v
       // that only the shell pass's pruning keeps cheap.)
       if (shell == kShells1 || (MODE == 0 && nc < kFewCands) || nring > g.nb[0] || nring > g.nb[1] ||
           nring > g.nb[2]) {
-        defer_cell(A, s, C.rmax2);
-        return;
+        rm2 = C.rmax2;
+        return kToShells;
       }
       lo2 = hi2;
       hi2 = nhi2;
       int nc2 = gather<MODE != 0>(S, A, g, s, r, b, nring, lo2, hi2);
       if (nc2 < 0) {
-        defer_dense(A, s);
-        return;
+        return kToDense;
       }
       // A shell that overflows (its radius may double) is narrowed, as in
       // the shell pass; the next shell goes on from there.
@@ -1143,14 +1133,14 @@ __device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* v
         nc2 = gather<MODE != 0>(S, A, g, s, r, b, nring, lo2, hi2);
       }
       if (nc2 > kCands) {
-        defer_cell(A, s, C.rmax2);
-        return;
+        rm2 = C.rmax2;
+        return kToShells;
       }
       last = nc2;
       sort_candidates(S, nc2);
       if (int bad = clip_candidates(S, nc2, C)) {
         fail_cell(A, s, seg, bad);
-        return;
+        return kBuilt;
       }
     }
   } else {
@@ -1158,7 +1148,6 @@ __device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* v
     // the current farthest vertex but at most twice the previous radius, so
     // a cell that still touched the starting box after the first pass does
     // not ask for a stencil as wide as the box at once.
-    const double rm2 = A.rmax2[s];
     const double rf2 = rloc * rloc;
     double lo2 = 0.0;
     // The first shell holds about twice the first pass's expected
@@ -1169,7 +1158,7 @@ __device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* v
       const int ring = ring_for(g, edge, hi2);
       if (ring > g.nb[0] || ring > g.nb[1] || ring > g.nb[2]) {
         fail_cell(A, s, seg, F_BOX);
-        return;
+        return kBuilt;
       }
       // Buckets, sub-bucket rows and points that cannot cut the cell are
       // left out (a cell next to a much denser region sees only the few
@@ -1184,12 +1173,12 @@ __device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* v
       }
       if (nc > kCands) {
         fail_cell(A, s, seg, F_CANDS);
-        return;
+        return kBuilt;
       }
       sort_candidates(S, nc);
       if (int bad = clip_candidates(S, nc, C)) {
         fail_cell(A, s, seg, bad);
-        return;
+        return kBuilt;
       }
       if (4.0 * C.rmax2 <= hi2 * (1.0 - 1e-12)) {
         done = true;
@@ -1201,10 +1190,24 @@ __device__ void tess_cell(TessLds& S, const TessArgs& A, const int s, double4* v
     }
     if (!done) {
       fail_cell(A, s, seg, F_INCOMPLETE);
-      return;
+      return kBuilt;
     }
   }
   if (int bad = finish_cell(S, A, s, C)) fail_cell(A, s, seg, bad);
+  return kBuilt;
+}
+
+// A cell of a first pass, listed for the pass it needs next.
+template <int MODE>
+__device__ void first_pass_cell(TessLds& S, const TessArgs& A, const int s) {
+  double rm2;
+  const int r = tess_cell<MODE>(S, A, s, rm2);
+  if (__lane_id() != 0) return;
+  if (r == kToDense) A.dcells[atomicAdd(&A.st->n_dense_cells, 1)] = s;
+  if (r == kToShells) {
+    A.deferred[atomicAdd(&A.st->n_deferred, 1)] = s;
+    A.rmax2[s] = rm2;
+  }
 }
 
 // Four waves per SIMD, with some values of the two-level gather and the
@@ -1218,7 +1221,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
   const int64_t nr = A.st->n_dredo;
   const int64_t nx = max((int64_t)0, (int64_t)A.st->n_dense_cells - A.dense_cap);
   for (int64_t it = (int64_t)blockIdx.x * kWaves + w; it < nr + nx; it += (int64_t)gridDim.x * kWaves)
-    tess_cell<1>(lds[w], A, it < nr ? A.redo[it] : A.dcells[A.dense_cap + (it - nr)]);
+    first_pass_cell<1>(lds[w], A, it < nr ? A.redo[it] : A.dcells[A.dense_cap + (it - nr)]);
 }
 
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3))) void k_tess_pass2(TessArgs A) {
@@ -1226,8 +1229,33 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3))
   __shared__ double4 verts[kWaves][kPruneVerts];   // the cell's live vertices, for pruning candidates
   const int w = threadIdx.x >> 6;
   const int nd = A.st->n_deferred;
-  for (int64_t it = (int64_t)blockIdx.x * kWaves + w; it < nd; it += (int64_t)gridDim.x * kWaves)
-    tess_cell<2>(lds[w], A, A.deferred[it], verts[w]);
+  for (int64_t it = (int64_t)blockIdx.x * kWaves + w; it < nd; it += (int64_t)gridDim.x * kWaves) {
+    const int s = A.deferred[it];
+    double rm2 = A.rmax2[s];
+    tess_cell<2>(lds[w], A, s, rm2, verts[w]);
+  }
+}
+
+// The four list passes in one launch, for short lists: a wavefront takes a
+// cell the lean pass handed on (or listed as dense) through all the one-cell
+// passes it needs, so no list waits for another.  Four launches of about
+// 4.6 us each become one where the lists are empty or short; the cells are
+// those of the separate passes.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_tess_rest(TessArgs A) {
+  __shared__ TessLds lds;
+  __shared__ double4 verts[kPruneVerts];
+  const int nr = A.st->n_redo;
+  const int n = nr + A.st->n_dense_cells;
+  for (int it = blockIdx.x; it < n; it += gridDim.x) {
+    const int s = it < nr ? A.redo[it] : A.dcells[it - nr];
+    double rm2 = 0.0;
+    int r = it < nr ? tess_cell<0>(lds, A, s, rm2) : kToDense;
+    if (r == kToDense) r = tess_cell<1>(lds, A, s, rm2);
+    if (r == kToShells) {
+      if (__lane_id() == 0) atomicAdd(&A.st->n_deferred, 1);
+      tess_cell<2>(lds, A, s, rm2, verts);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2164,8 +2192,12 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
   const int w = threadIdx.x >> 6;
   const int nr = A.st->n_redo;
   for (int64_t it = (int64_t)blockIdx.x * kWaves + w; it < nr; it += (int64_t)gridDim.x * kWaves)
-    tess_cell<0>(lds[w], A, A.redo[it]);
+    first_pass_cell<0>(lds[w], A, A.redo[it]);
 }
+
+// Cells the one-launch list pass is meant for: about one round of its
+// wavefronts (12 per CU by registers).
+constexpr int64_t kRestCells = 4096;
 
 }  // namespace
 
@@ -2187,6 +2219,13 @@ int64_t launch_tessellate(const double* spos, int64_t n, const SegDesc* segs, co
     hipLaunchKernelGGL(k_tess_pair<true>, dim3((unsigned)((n + 1) / 2)), dim3(64), 0, st, A);
   else
     hipLaunchKernelGGL(k_tess_pair<false>, dim3((unsigned)((n + 1) / 2)), dim3(64), 0, st, A);
+  // Short lists (the last tessellation's, or those of a mesh of at most
+  // kRestCells cells whatever they hold): one launch for all of them.  Dense
+  // lists of larger meshes keep the two-cell dense pass.
+  if (n <= kRestCells || (hints.dense_cells == 0 && hints.redo >= 0 && hints.redo <= kRestCells / 2)) {
+    hipLaunchKernelGGL(k_tess_rest, dim3((unsigned)std::min<int64_t>(n, kRestCells / 2)), dim3(64), 0, st, A);
+    return 0;
+  }
   // The handed-on and deferred counts are known on the device only.  Each
   // list pass gets blocks for the length the last tessellation's list had
   // and a quarter more (a wavefront per cell; at least 256 blocks), at most
