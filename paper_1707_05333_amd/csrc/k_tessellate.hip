@@ -1609,7 +1609,9 @@ __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams&
 }
 
 // Candidates of each half ordered by distance, ties by neighbour and image
-// (as sort_candidates).
+// (as sort_candidates, but moved into that order: the cut loop then reads
+// candidate k at a known place instead of through an index, one LDS round
+// trip less per candidate).
 __device__ void sort_pair(PairLds& S, const int nc) {
   const int hl = hlane();
   const int c0 = hl, c1 = hl + 32;
@@ -1617,7 +1619,16 @@ __device__ void sort_pair(PairLds& S, const int nc) {
   // Keys past the half's count read as +inf while ranking: no bound test
   // in the loop.
   constexpr double kInf = __builtin_huge_val();
-  const double k0 = c0 < nc ? S.cd[c0].w : kInf, k1 = c1 < nc ? S.cd[c1].w : kInf;
+  double4 q0 = make_double4(0.0, 0.0, 0.0, kInf), q1 = q0;
+  int j0 = 0, j1 = 0;
+  if (c0 < nc) {
+    q0 = S.cd[c0];
+    j0 = S.cjk[c0];
+  }
+  if (c1 < nc) {
+    q1 = S.cd[c1];
+    j1 = S.cjk[c1];
+  }
   const int ncmax = (int)wave_umax32((unsigned)nc);
   if (c0 >= nc && c0 < ncmax) S.cd[c0].w = kInf;
   if (c1 >= nc && c1 < ncmax) S.cd[c1].w = kInf;
@@ -1625,35 +1636,46 @@ __device__ void sort_pair(PairLds& S, const int nc) {
 #pragma unroll 4
   for (int m = 0; m < ncmax; ++m) {
     const double km = S.cd[m].w;
-    lt0 += km < k0;
-    lt1 += km < k1;
+    lt0 += km < q0.w;
+    lt1 += km < q1.w;
   }
+  // A repeated distance gives two candidates the same rank, which the
+  // read-back of the rank's owner shows.
   if (c0 < nc) S.order[lt0] = (uint8_t)c0;
-  else if (c0 < kCandsP) S.order[c0] = 0;
   if (c1 < nc) S.order[lt1] = (uint8_t)c1;
-  else if (c1 < kCandsP) S.order[c1] = 0;
   wave_sync();
   const bool tie = (c0 < nc && S.order[lt0] != c0) || (c1 < nc && S.order[lt1] != c1);
   const bool htie = hbits(__ballot(tie)) != 0u;
-  if (__ballot(htie) == 0ull) return;
-  wave_sync();
-  for (int rnd = 0; rnd < 2; ++rnd) {
-    const int c = hl + 32 * rnd;
-    if (htie && c < nc) {
-      const double key = S.cd[c].w;
-      const int id = S.cjk[c];
-      int rank = 0;
+  if (__ballot(htie)) {
+    auto rank = [&](int c, double key, int id) {
+      int r = 0;
       for (int m = 0; m < nc; ++m) {
         const double km = S.cd[m].w;
-        rank += (km < key) || (km == key && (S.cjk[m] < id || (S.cjk[m] == id && m < c)));
+        r += (km < key) || (km == key && (S.cjk[m] < id || (S.cjk[m] == id && m < c)));
       }
-      S.order[rank] = (uint8_t)c;
-    }
+      return r;
+    };
+    if (htie && c0 < nc) lt0 = rank(c0, q0.w, j0);
+    if (htie && c1 < nc) lt1 = rank(c1, q1.w, j1);
+  }
+  wave_sync();   // every key has been read
+  if (c0 < nc) {
+    S.cd[lt0] = q0;
+    S.cjk[lt0] = j0;
+  }
+  if (c1 < nc) {
+    S.cd[lt1] = q1;
+    S.cjk[lt1] = j1;
   }
   wave_sync();
 }
 
 // Cuts each half's cell by its ordered candidates (as clip_candidates).
+// Each half first steps on its own to its next candidate that cuts, and
+// then both cut: about a third of the candidates cut nothing, different ones
+// in the two halves, and a step past one is a fraction of a cut (with one
+// candidate index for both halves, 22 of a lattice cell's 26 candidates
+// went through the cut for a half or the other; now its own 17).
 // Returns 0 or a failure bit for this half's cell.
 __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C) {
   const int hl = hlane();
@@ -1667,36 +1689,48 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C) {
   unsigned long long failp = 0ull, failv = 0ull;  // halves out of plane or vertex slots
   int since0 = 0, since1 = 0;                      // cuts since each half's last bound
   double lim = 2.0 * C.rmax2;
-  const int ncmax = (int)wave_umax32((unsigned)max(nc, 0));
-  for (int k = 0; k < ncmax; ++k) {
-    // A half that stopped, or ran out of candidates, stays idle: the loop
-    // ends when both are.  (Slots past a half's count hold candidate 0.)
-    unsigned long long actw = __ballot(k < nc) & ~donew;
-    if (actw == 0ull) break;
-    const int c = S.order[k];
-    const double4 q = S.cd[c];
-    const double h = q.w;
-    // Stop test of each half: farther images cannot cut its cell.  A bound
-    // older than the last cut is refreshed and the test taken again.
-    const unsigned long long farw = __ballot(h >= lim) & actw;
-    if (farw) {
-      const double nb = farthest_bound_pair(C);
-      const unsigned long long refw = farw & stalew;
-      if (lane_on(refw)) {
-        C.rmax2 = nb;
-        lim = 2.0 * nb;
+  int k = 0;   // the half's next candidate
+  double4 q = make_double4(0.0, 0.0, 0.0, 0.0);
+  for (;;) {
+    // To the next candidate that cuts.  A half that found its own waits with
+    // it; one that is stopped by the bound or out of candidates is done.
+    unsigned long long M0w = 0ull, M1w = 0ull;       // vertices cut off
+    unsigned long long cutw = 0ull;                  // halves with a candidate that cuts
+    for (unsigned long long seekw = ~donew; seekw;) {
+      if (lane_on(seekw)) {
+        q = S.cd[k];
+        ++k;
       }
-      stalew &= ~refw;
-      if (refw & LO) since0 = 0;
-      if (refw & HI) since1 = 0;
-      const unsigned long long stopw = (farw & ~refw) | (refw & __ballot(h >= lim));
-      donew |= stopw;
-      actw &= ~stopw;
+      // Stop test of each half: farther images cannot cut its cell.  A bound
+      // older than the last cut is refreshed and the test taken again.
+      const unsigned long long farw = __ballot(q.w >= lim) & seekw;
+      if (farw) {
+        const double nb = farthest_bound_pair(C);
+        const unsigned long long refw = farw & stalew;
+        if (lane_on(refw)) {
+          C.rmax2 = nb;
+          lim = 2.0 * nb;
+        }
+        stalew &= ~refw;
+        if (refw & LO) since0 = 0;
+        if (refw & HI) since1 = 0;
+        const unsigned long long stopw = (farw & ~refw) | (refw & __ballot(q.w >= lim));
+        donew |= stopw;
+        seekw &= ~stopw;
+      }
+      const unsigned long long n0 = __ballot(q.x * C.v0x + q.y * C.v0y + q.z * C.v0z > q.w) & seekw & C.L0w;
+      const unsigned long long n1 = __ballot(q.x * C.v1x + q.y * C.v1y + q.z * C.v1z > q.w) & seekw & C.L1w;
+      const unsigned long long hitw = halves_of(n0 | n1);
+      M0w |= n0;
+      M1w |= n1;
+      cutw |= hitw;
+      seekw &= ~hitw;
+      const unsigned long long endw = __ballot(k >= nc) & seekw;
+      donew |= endw;
+      seekw &= ~endw;
     }
-    const unsigned long long M0w = __ballot(q.x * C.v0x + q.y * C.v0y + q.z * C.v0z > h) & actw & C.L0w;
-    const unsigned long long M1w = __ballot(q.x * C.v1x + q.y * C.v1y + q.z * C.v1z > h) & actw & C.L1w;
-    const unsigned long long cutw = halves_of(M0w | M1w);   // the halves whose cell this cuts
-    if (cutw == 0ull) continue;
+    if (cutw == 0ull) break;
+    const double h = q.w;
 
     // Plane slot: the next unused one (a cell that needs more goes to the
     // one-cell pass, which reuses the slots of faces cut away).
@@ -1705,7 +1739,6 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C) {
     failp |= fullw;
     donew |= fullw;
     const unsigned long long gow = cutw & ~fullw;
-    if (gow == 0ull) continue;
     if (lane_on(gow)) C.np = (int)p + 1;
     // The half's kept vertices as a set over its 64 slots (bit v: slot v,
     // the first register's 32 slots, then the second's).
@@ -1733,14 +1766,13 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C) {
     failv |= gow & ~roomw;
     donew |= gow & ~roomw;
     const unsigned long long doitw = gow & roomw;
-    if (doitw == 0ull) continue;
     if (lane_on(doitw) && hl == 0) {
       S.pl[p] = make_double4(q.x, q.y, q.z, h);
       // (the slot's byte offset is taken opaque: derived from the plane
       // row's address the compiler forms it with a 64-bit multiply-add)
       unsigned p4 = p << 2;
       asm volatile("" : "+v"(p4));
-      *(int32_t*)((char*)S.pcand + p4) = S.cjk[c];
+      *(int32_t*)((char*)S.pcand + p4) = S.cjk[k - 1];
     }
     // Each removed vertex lists its boundary edges from position pre, the
     // first register's, then the second's (only when a removed vertex
@@ -1801,6 +1833,7 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C) {
     wave_sync();
     C.L0w = (C.L0w & ~(M0w & doitw)) | new0w;
     C.L1w = (C.L1w & ~(M1w & doitw)) | new1w;
+    donew |= __ballot(k >= nc);
     // The bound is refreshed every fourth cut of a half.
     stalew |= doitw;
     if (doitw & LO) ++since0;
