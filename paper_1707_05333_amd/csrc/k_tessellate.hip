@@ -586,6 +586,134 @@ __device__ int gather_runs(TessLds& S, const TessArgs& A, const GridParams& g, c
   return nc;
 }
 
+// The lean passes' gather: images with lo2 <= |d|^2 < hi2 from the stencil of
+// half-width `ring`, by rows of buckets along x, for G lanes per cell (a
+// wavefront, or a half of one: G = 64 or 32).  Along a row the buckets of one
+// tile are consecutive in the cell order, so a row of the window is one run
+// of points, or two where the window crosses the end of a tile or of the box
+// (more for a very narrow last tile: they are taken two at a time).  A lane
+// takes one row: its runs cost two bucket offsets each, where the buckets one
+// by one cost a key and two offsets per bucket (125 or 343 of them), a third
+// to a half of the gather's instructions.  The points of a lane's row are
+// read kRowPoints at a time.  Returns the number of images found (more than
+// CAP: an overflow, of which only the first CAP are stored), or -1 when a run
+// holds more than kRunMax points (a dense region: the cell goes to the dense
+// passes).  Called by the whole wavefront (act: the lane's group has a cell).
+constexpr int kRowPoints = 3;
+constexpr int kRunMax = 24;
+
+// The part of the row at x = t (unwrapped, at most `left` buckets) that lies
+// in one tile: its length, wrapped start and image.
+struct RowRun {
+  int len, x, k;
+};
+__device__ inline RowRun row_run(int t, int left, int nb) {
+  RowRun R;
+  R.k = t < 0 ? -1 : (t >= nb ? 1 : 0);
+  R.x = t - R.k * nb;
+  R.len = min(left, min(nb, (R.x & ~(kTile - 1)) + kTile) - R.x);
+  return R;
+}
+
+template <int G, int CAP, typename LDS>
+__device__ int gather_rows(LDS& S, const TessArgs& A, const GridParams& g, bool act, const int s, const double r[3],
+                           const int b[3], const int ring, const double lo2, const double hi2) {
+  const int gl = __lane_id() & (G - 1);
+  // This group's bits of a wavefront mask, as a count and a count below.
+  auto count = [&](unsigned long long m) {
+    if constexpr (G == 64) return __popcll(m);
+    else return __popc((unsigned)(m >> (__lane_id() & 32)));
+  };
+  auto below = [&](unsigned long long m) {
+    if constexpr (G == 64) return __popcll(m & lanes_below());
+    else return __popc((unsigned)(m >> (__lane_id() & 32)) & ((1u << gl) - 1u));
+  };
+  const int W = 2 * ring + 1, rows = act ? W * W : 0;
+  const WidthDiv D = width_div((unsigned)W);
+  const int rows_max = (int)wave_umax32((unsigned)rows);
+  int nc = 0;
+  bool dense = false;
+  for (int r0 = 0; r0 < rows_max; r0 += G) {
+    const int o = r0 + gl;
+    const bool have = o < rows;
+    const int q = have ? (int)div_width((unsigned)o, D) : 0;
+    const int ty = b[1] + (have ? o - q * W - ring : 0), tz = b[2] + (have ? q - ring : 0);
+    const int ky = ty < 0 ? -1 : (ty >= g.nb[1] ? 1 : 0), kz = tz < 0 ? -1 : (tz >= g.nb[2] ? 1 : 0);
+    const int y = ty - ky * g.nb[1], z = tz - kz * g.nb[2];
+    // The row's part of bucket_key, which stays the same along x.
+    const int y0 = y & ~(kTile - 1), z0 = z & ~(kTile - 1);
+    const int ey = min(kTile, g.nb[1] - y0), ez = min(kTile, g.nb[2] - z0);
+    const int64_t row = g.base + g.nb[0] * g.nb[1] * z0 + g.nb[0] * y0 * ez;
+    const int slab = ey * ez, line = (y - y0) + ey * (z - z0);
+    const double sy = ky * g.L[1], sz = kz * g.L[2];
+    const int code_yz = 3 * (ky + 1) + 9 * (kz + 1);
+    int t = b[0] - ring;
+    const int t_end = act ? b[0] + ring + 1 : t;
+    while (__ballot(t < t_end)) {
+      const int left = t_end - t;
+      const RowRun R0 = row_run(t, left, g.nb[0]);
+      const RowRun R1 = row_run(t + R0.len, left - R0.len, g.nb[0]);
+      int s0 = 0, c0 = 0, s1 = 0, c1 = 0;
+      if (have && R0.len > 0) {
+        const int x0 = R0.x & ~(kTile - 1);
+        const int64_t key = row + x0 * slab + (R0.x - x0) + min(kTile, g.nb[0] - x0) * line;
+        const unsigned long long a = A.boff[key];
+        s0 = (int)a;
+        c0 = (int)(A.boff[key + R0.len] - a);
+      }
+      if (have && R1.len > 0) {
+        const int x0 = R1.x & ~(kTile - 1);
+        const int64_t key = row + x0 * slab + (R1.x - x0) + min(kTile, g.nb[0] - x0) * line;
+        const unsigned long long a = A.boff[key];
+        s1 = (int)a;
+        c1 = (int)(A.boff[key + R1.len] - a);
+      }
+      t += max(R0.len, 0) + max(R1.len, 0);
+      dense |= count(__ballot(c0 > kRunMax || c1 > kRunMax)) != 0;
+      const int cnt = dense ? 0 : c0 + c1;
+      const int maxc = (int)wave_umax32((unsigned)cnt);
+      const double sx0 = R0.k * g.L[0], sx1 = R1.k * g.L[0];
+      const int code0 = code_yz + R0.k + 1, code1 = code_yz + R1.k + 1;
+      for (int k0 = 0; k0 < maxc; k0 += kRowPoints) {
+        double dx[kRowPoints], dy[kRowPoints], dz[kRowPoints], d2[kRowPoints];
+        bool keep[kRowPoints];
+#pragma unroll
+        for (int u = 0; u < kRowPoints; ++u) {
+          const int k = k0 + u;
+          const int j = (k < c0 ? s0 : s1 - c0) + k;
+          const bool v = k < cnt && j != s;
+          double x = 0, yy = 0, zz = 0;
+          if (v) {
+            x = A.spos[3 * (int64_t)j];
+            yy = A.spos[3 * (int64_t)j + 1];
+            zz = A.spos[3 * (int64_t)j + 2];
+          }
+          dx[u] = (x + (k < c0 ? sx0 : sx1)) - r[0];
+          dy[u] = (yy + sy) - r[1];
+          dz[u] = (zz + sz) - r[2];
+          d2[u] = dx[u] * dx[u] + dy[u] * dy[u] + dz[u] * dz[u];
+          keep[u] = v && d2[u] >= lo2 && d2[u] < hi2;
+        }
+#pragma unroll
+        for (int u = 0; u < kRowPoints; ++u) {
+          const unsigned long long mk = __ballot(keep[u]);
+          if (keep[u]) {
+            const int k = k0 + u;
+            const int idx = nc + below(mk);
+            if (idx < CAP) {
+              S.cd[idx] = make_double4(dx[u], dy[u], dz[u], 0.5 * d2[u]);
+              S.cjk[idx] = (((k < c0 ? s0 : s1 - c0) + k) << 5) | (k < c0 ? code0 : code1);
+            }
+          }
+          nc += count(mk);
+        }
+      }
+    }
+  }
+  wave_sync();
+  return dense ? -1 : nc;
+}
+
 // Gathers the neighbour images with lo2 <= |d|^2 < hi2 from the stencil of
 // half-width `ring` into LDS (at most kCands of them); returns their number.
 // Each lane takes two buckets of the stencil at a time and the wave steps
@@ -595,10 +723,6 @@ __device__ int gather_runs(TessLds& S, const TessArgs& A, const GridParams& g, c
 // With a vertex list (vl, nv) of the current cell, images that cannot cut it
 // are left out (a cell next to a much denser region then sees only the few
 // points that face it).
-// Without RUNS (the first pass over all cells) a stencil chunk that holds a
-// dense bucket ends the gather with -1: the cell goes to the first pass for
-// cells near dense regions.
-template <bool RUNS>
 __device__ int gather(TessLds& S, const TessArgs& A, const GridParams& g, const int s, const double r[3],
                       const int b[3], const int ring, const double lo2, const double hi2,
                       const double4* vl = nullptr, int nv = 0) {
@@ -611,8 +735,7 @@ __device__ int gather(TessLds& S, const TessArgs& A, const GridParams& g, const 
     const StencilBucket B1 = stencil_bucket(A, g, b, ring, chunk + 64 + lane, W3, D);
     // With a vertex list every chunk takes the run path, whose boxes prune
     // whole buckets and rows.
-    if (__ballot(B0.cnt > kDense || B1.cnt > kDense) || (RUNS && vl)) {
-      if constexpr (!RUNS) return -1;
+    if (__ballot(B0.cnt > kDense || B1.cnt > kDense) || vl) {
       nc = gather_runs(S, A, g, s, r, b, ring, chunk, W3, D, lo2, hi2, vl, nv, nc);
       continue;
     }
@@ -1064,13 +1187,18 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
     if (cnt > (unsigned)kDenseMax) fail_cell(A, s, seg, F_DENSE);
     return kBuilt;
   }
+  // The first passes' gather: by rows, or two-level near dense regions.
+  auto gather_first = [&](int ring, double lo2, double hi2) {
+    if constexpr (MODE == 0) return gather_rows<64, kCands>(S, A, g, true, s, r, b, ring, lo2, hi2);
+    else return gather(S, A, g, s, r, b, ring, lo2, hi2);
+  };
   if (MODE < 2) {
     const int ring = dense ? min(g.ring, ring_for(g, edge, rloc * rloc)) : g.ring;
     double reach = 1e300;
 #pragma unroll
     for (int a = 0; a < 3; ++a) reach = fmin(reach, ring * g.hb[a] + edge[a]);
     double hi2 = fmin(reach * reach, rloc * rloc);
-    int nc = gather<MODE != 0>(S, A, g, s, r, b, ring, 0.0, hi2);
+    int nc = gather_first( ring, 0.0, hi2);
     if (nc < 0) {
       return kToDense;
     }
@@ -1087,7 +1215,7 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
       const double nhi2 = rt * rt;
       const int nring = ring_for(g, edge, nhi2);
       if (nhi2 > hi2 && nring <= kThinRing && nring <= g.nb[0] && nring <= g.nb[1] && nring <= g.nb[2]) {
-        nc = gather<false>(S, A, g, s, r, b, nring, 0.0, nhi2);
+        nc = gather_first( nring, 0.0, nhi2);
         if (nc < 0) {
           return kToDense;
         }
@@ -1122,7 +1250,7 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
       }
       lo2 = hi2;
       hi2 = nhi2;
-      int nc2 = gather<MODE != 0>(S, A, g, s, r, b, nring, lo2, hi2);
+      int nc2 = gather_first( nring, lo2, hi2);
       if (nc2 < 0) {
         return kToDense;
       }
@@ -1130,7 +1258,7 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
       // the shell pass; the next shell goes on from there.
       for (int t = 0; nc2 > kCands && t < 2; ++t) {
         hi2 = lo2 + 0.5 * (hi2 - lo2);
-        nc2 = gather<MODE != 0>(S, A, g, s, r, b, nring, lo2, hi2);
+        nc2 = gather_first( nring, lo2, hi2);
       }
       if (nc2 > kCands) {
         rm2 = C.rmax2;
@@ -1166,10 +1294,10 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
       // prunes nothing: it takes the plain gather.
       const int nv = shell > 0 ? vertex_list(C, vl) : 0;
       const double4* vlp = nv ? vl : nullptr;
-      int nc = gather<true>(S, A, g, s, r, b, ring, lo2, hi2, vlp, nv);
+      int nc = gather(S, A, g, s, r, b, ring, lo2, hi2, vlp, nv);
       for (int tries = 0; nc > kCands && tries < 40; ++tries) {
         hi2 = lo2 + 0.5 * (hi2 - lo2);
-        nc = gather<true>(S, A, g, s, r, b, ring, lo2, hi2, vlp, nv);
+        nc = gather(S, A, g, s, r, b, ring, lo2, hi2, vlp, nv);
       }
       if (nc > kCands) {
         fail_cell(A, s, seg, F_CANDS);
@@ -1413,25 +1541,18 @@ __device__ inline double farthest_bound_pair(const PairRegs& C) {
   return half_max_bound(m2);
 }
 
-// The gather of both halves: images with lo2 <= |d|^2 < hi2 from each
-// half's stencil of half-width `ring`.  The lean pass takes four stencil
-// buckets per lane at a time (the usual 125-bucket stencil in one memory
-// round trip, as in the one-cell gather); the dense pass one (its stencils
-// are small, and the registers spared shrink its spill: the polytropes'
-// dense cells 6% faster than with two, 10% than with four).  Returns the
-// number of images this half found (more than kCandsP: an overflow, of
-// which only the first kCandsP are stored).
-// Without RUNS (the lean pass) a stencil that holds a dense bucket gives -1;
-// with RUNS a chunk of the stencil that holds one, in either half, is taken
-// by the two-level gather of both halves.  Called by the whole wavefront
+// The dense pass's gather of both halves: images with lo2 <= |d|^2 < hi2 from
+// each half's stencil of half-width `ring`, one stencil bucket per lane at a
+// time (the stencils are small, and more buckets per lane spill registers:
+// 10% slower with four).  A chunk of the stencil that holds a dense bucket,
+// in either half, is taken by the two-level gather of both halves.  Returns
+// the number of images this half found (more than kCandsP: an overflow, of
+// which only the first kCandsP are stored).  Called by the whole wavefront
 // (act: the half has a cell).
-constexpr int kPairBuckets = 4;
-
 __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams& g, const int s, const double r[3],
-                                const int b[3], const int ring, const int chunk, const int nb, const int W3,
-                                const WidthDiv& D, const double lo2, const double hi2, int nc);
+                                const int b[3], const int ring, const int chunk, const int W3, const WidthDiv& D,
+                                const double lo2, const double hi2, int nc);
 
-template <bool RUNS>
 __device__ int gather_pair(PairLds& S, const TessArgs& A, const GridParams& g, bool act, const int s,
                            const double r[3], const int b[3], const int ring, const double lo2, const double hi2) {
   const int hl = hlane();
@@ -1439,70 +1560,41 @@ __device__ int gather_pair(PairLds& S, const TessArgs& A, const GridParams& g, b
   const WidthDiv D = width_div((unsigned)W);
   const int W3max = (int)wave_umax32((unsigned)W3);
   int nc = 0;
-  bool dense = false;
-  constexpr int NB = RUNS ? 1 : kPairBuckets;   // stencil buckets per lane and chunk
-  for (int chunk = 0; chunk < W3max; chunk += 32 * NB) {
-    StencilBucket B[NB];
-    bool dn = false;
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      B[u] = stencil_bucket(A, g, b, ring, chunk + 32 * u + hl, W3, D);
-      dn |= B[u].cnt > kDense;
+  for (int chunk = 0; chunk < W3max; chunk += 32) {
+    const StencilBucket B = stencil_bucket(A, g, b, ring, chunk + hl, W3, D);
+    if (__ballot(B.cnt > kDense)) {
+      nc = gather_runs_pair(S, A, g, s, r, b, ring, chunk, W3, D, lo2, hi2, nc);
+      continue;
     }
-    if constexpr (RUNS) {
-      if (__ballot(dn)) {
-        nc = gather_runs_pair(S, A, g, s, r, b, ring, chunk, NB, W3, D, lo2, hi2, nc);
-        continue;
-      }
-    } else {
-      dense |= hbits(__ballot(dn)) != 0u;
-    }
-    int cmax = 0;
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      if (dense) B[u].cnt = 0;
-      cmax = max(cmax, B[u].cnt);
-    }
-    const int maxc = (int)wave_umax32((unsigned)cmax);
+    const int maxc = (int)wave_umax32((unsigned)B.cnt);
     for (int k = 0; k < maxc; ++k) {
-      double dx[NB], dy[NB], dz[NB], d2[NB];
-      bool keep[NB];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int j = B[u].bst + k;
-        const bool v = k < B[u].cnt && j != s;
-        double x = 0, y = 0, z = 0;
-        if (v) {
-          x = A.spos[3 * (int64_t)j];
-          y = A.spos[3 * (int64_t)j + 1];
-          z = A.spos[3 * (int64_t)j + 2];
-        }
-        dx[u] = (x + B[u].sx) - r[0];
-        dy[u] = (y + B[u].sy) - r[1];
-        dz[u] = (z + B[u].sz) - r[2];
-        d2[u] = dx[u] * dx[u] + dy[u] * dy[u] + dz[u] * dz[u];
-        keep[u] = v && d2[u] >= lo2 && d2[u] < hi2;
+      const int j = B.bst + k;
+      const bool v = k < B.cnt && j != s;
+      double x = 0, y = 0, z = 0;
+      if (v) {
+        x = A.spos[3 * (int64_t)j];
+        y = A.spos[3 * (int64_t)j + 1];
+        z = A.spos[3 * (int64_t)j + 2];
       }
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const unsigned mk = hbits(__ballot(keep[u]));
-        if (keep[u]) {
-          const int idx = nc + __popc(mk & hbelow());
-          if (idx < kCandsP) {
-            S.cd[idx] = make_double4(dx[u], dy[u], dz[u], 0.5 * d2[u]);
-            S.cjk[idx] = ((B[u].bst + k) << 5) | B[u].code;
-          }
+      const double dx = (x + B.sx) - r[0], dy = (y + B.sy) - r[1], dz = (z + B.sz) - r[2];
+      const double d2 = dx * dx + dy * dy + dz * dz;
+      const bool keep = v && d2 >= lo2 && d2 < hi2;
+      const unsigned mk = hbits(__ballot(keep));
+      if (keep) {
+        const int idx = nc + __popc(mk & hbelow());
+        if (idx < kCandsP) {
+          S.cd[idx] = make_double4(dx, dy, dz, 0.5 * d2);
+          S.cjk[idx] = (j << 5) | B.code;
         }
-        nc += __popc(mk);
       }
+      nc += __popc(mk);
     }
   }
   wave_sync();
-  if (dense) return -1;
   return nc;   // all it found: above kCandsP only the first kCandsP are stored
 }
 
-// The two-level gather of one chunk of 32 nb stencil buckets per half (as
+// The two-level gather of one chunk of 32 stencil buckets per half (as
 // gather_runs, with 32 lanes per cell): each bucket that meets the box
 // around the query sphere contributes runs of consecutive points, a sparse
 // bucket its whole range and a dense one the part of each sub-bucket row
@@ -1510,15 +1602,15 @@ __device__ int gather_pair(PairLds& S, const TessArgs& A, const GridParams& g, b
 // bucket of its run by a binary search over the half's run prefix sums.
 // The per-point test is the plain path's, so the candidates are the same.
 __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams& g, const int s, const double r[3],
-                                const int b[3], const int ring, const int chunk, const int nb, const int W3,
-                                const WidthDiv& D, const double lo2, const double hi2, int nc) {
+                                const int b[3], const int ring, const int chunk, const int W3, const WidthDiv& D,
+                                const double lo2, const double hi2, int nc) {
   const int hl = hlane();
   const int h0 = __lane_id() & 32;   // first lane of this half
   const double rq = sqrt(hi2) * (1.0 + 1e-9) + 1e-9 * fmin(g.hb[0], fmin(g.hb[1], g.hb[2]));
-  for (int u = 0; u < nb; ++u) {
+  {
     int bb[3] = {0, 0, 0};
     int64_t key = 0;
-    const StencilBucket B = stencil_bucket(A, g, b, ring, chunk + 32 * u + hl, W3, D, bb, &key);
+    const StencilBucket B = stencil_bucket(A, g, b, ring, chunk + hl, W3, D, bb, &key);
     int nr = 0, pack = 0, base = 0;
     if (B.cnt > 0) {
       const double sh[3] = {B.sx, B.sy, B.sz};
@@ -2020,6 +2112,14 @@ __device__ inline void redo_cell(const TessArgs& A, int s) {
   A.redo[atomicAdd(DENSE ? &A.st->n_dredo : &A.st->n_redo, 1)] = s;
 }
 
+template <bool DENSE>
+__device__ __forceinline__ int gather_half(PairLds& S, const TessArgs& A, const GridParams& g, bool act, const int s,
+                                           const double r[3], const int b[3], const int ring, const double lo2,
+                                           const double hi2) {
+  if constexpr (DENSE) return gather_pair(S, A, g, act, s, r, b, ring, lo2, hi2);
+  else return gather_rows<32, kCandsP>(S, A, g, act, s, r, b, ring, lo2, hi2);
+}
+
 // One cell per half of the wavefront (act: the half has a cell, s).
 // DENSE = false: the lean first pass over every cell; cells of dense
 // buckets are left to the dense passes (listed by the sort), and a cell
@@ -2068,7 +2168,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
   // already has can split, by rounding, the vertices that lie on them).
   bool work = act;
   for (int shell = 0;; ++shell) {
-    int nc = gather_pair<DENSE>(S, A, g, work, s, r, b, ring, lo2, hi2);
+    int nc = gather_half<DENSE>(S, A, g, work, s, r, b, ring, lo2, hi2);
     if (!DENSE && work && nc < 0) {
       if (hl == 0) A.dcells[atomicAdd(&A.st->n_dense_cells, 1)] = s;
       act = work = false;
@@ -2082,7 +2182,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
     const bool over = work && nc > kCandsP && (!DENSE || shell == 0);
     if (__ballot(over)) {
       if (over) hi2 = shell_for(lo2, hi2, nc, 38.0);
-      const int nc2 = gather_pair<DENSE>(S, A, g, over, s, r, b, ring, lo2, hi2);
+      const int nc2 = gather_half<DENSE>(S, A, g, over, s, r, b, ring, lo2, hi2);
       if (over) nc = nc2;
     }
     // Too many candidates, or (lean pass, first radius) few: a thin region,
@@ -2128,13 +2228,13 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
             hi2 = nhi2;
           }
         }
-        int nc2 = gather_pair<DENSE>(S2, A, g2, go, s2, G2.r, G2.b, ring2, lo2, hi2);
+        int nc2 = gather_half<DENSE>(S2, A, g2, go, s2, G2.r, G2.b, ring2, lo2, hi2);
         // A shell that overflows is narrowed once (the one-cell pass takes
         // the cell on if it still falls short).
         const bool over2 = go && nc2 > kCandsP;
         if (__ballot(over2)) {
           if (over2) hi2 = shell_for(lo2, hi2, nc2, 38.0);
-          const int nc3 = gather_pair<DENSE>(S2, A, g2, over2, s2, G2.r, G2.b, ring2, lo2, hi2);
+          const int nc3 = gather_half<DENSE>(S2, A, g2, over2, s2, G2.r, G2.b, ring2, lo2, hi2);
           if (over2) nc2 = nc3;
         }
         if (go && (nc2 < 0 || nc2 > kCandsP)) {
