@@ -372,7 +372,10 @@ mm_status mm_serve(mm_batch* b, const mm_request* req, int32_t n_req, mm_request
   const auto t0 = std::chrono::steady_clock::now();
   double last_finish = 0.0;
 
-  auto finish = [&](int32_t sim, int status) {
+  std::vector<int32_t> leaving;   // simulations read out, to be evicted
+
+  // The results of a completed (or failed) simulation, read out.
+  auto complete = [&](int32_t sim, int status) {
     const int32_t r = req_of[sim];
     const Sim& s = b->sims[sim];
     if (status == MM_OK && !s.fresh && (req[r].pos_out || req[r].Q_out))
@@ -383,14 +386,19 @@ mm_status mm_serve(mm_batch* b, const mm_request* req, int32_t n_req, mm_request
     res[r].finished = now_s(t0);
     last_finish = res[r].finished;
     turnaround.push_back(res[r].finished - req[r].arrival);
-    mm_batch_evict(b, sim);
-    req_of[sim] = -1;
-    --resident;
-    ++done;
+    leaving.push_back(sim);
   };
-
-  while (done < n_req) {
-    // Admission: arrived requests in order, while they fit.
+  auto evict_leaving = [&]() {
+    for (int32_t sim : leaving) {
+      mm_batch_evict(b, sim);
+      req_of[sim] = -1;
+      --resident;
+      ++done;
+    }
+    leaving.clear();
+  };
+  // Admission: arrived requests in order, while they fit.
+  auto admit_arrived = [&]() {
     while (next < n_req && req[next].arrival <= now_s(t0)) {
       const mm_request& q = req[next];
       int32_t sim = -1;
@@ -410,8 +418,13 @@ mm_status mm_serve(mm_batch* b, const mm_request* req, int32_t n_req, mm_request
       ++resident;
       ++next;
       stats->max_resident = std::max(stats->max_resident, resident);
-      if (q.steps <= 0) finish(sim, MM_OK);
+      if (q.steps <= 0) complete(sim, MM_OK);
     }
+  };
+
+  while (done < n_req) {
+    admit_arrived();
+    evict_leaving();   // (requests of no steps)
     if (resident == 0) {
       if (next < n_req) {
         const double wait = req[next].arrival - now_s(t0);
@@ -432,11 +445,15 @@ mm_status mm_serve(mm_batch* b, const mm_request* req, int32_t n_req, mm_request
         step_ms.push_back(ms);
         stats->sim_steps += 1;
         stats->cell_updates += I.n;
-        if (I.steps >= req[rq].steps) finish(I.sim, MM_OK);
+        if (I.steps >= req[rq].steps) complete(I.sim, MM_OK);
       } else {
-        finish(I.sim, I.status);
+        complete(I.sim, I.status);
       }
     }
+    // What arrived during the step joins before the completed leave, where
+    // there is room for both.
+    if (!leaving.empty()) admit_arrived();
+    evict_leaving();
   }
   stats->wall = last_finish;
   stats->cell_updates_per_s = stats->wall > 0 ? (double)stats->cell_updates / stats->wall : 0.0;
