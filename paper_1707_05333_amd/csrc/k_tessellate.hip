@@ -1762,26 +1762,141 @@ __device__ void sort_pair(PairLds& S, const int nc) {
   wave_sync();
 }
 
+// Start of each half's cell from the six nearest candidates of the six axis
+// sectors (the axis of the largest |d| component, and its sign), in place of
+// the box: near a lattice their bisectors bound a slightly deformed cube, and
+// six cuts of some 115 instructions each become one lane-parallel pass of
+// about that length (Sod tube, 1M cells: 6.57 -> 5.84 ms a step).  A half takes
+// it when every one of the eight corners (one plane of each axis, the triple
+// oriented as in the box) lies strictly inside the three opposite planes and
+// inside the box: eight vertices are all that six planes can have, so the
+// corners are the polytope's, and the box planes cannot cut it any more.  A
+// corner is solved in the order the cuts would have used (the farthest plane
+// last).
+// Six candidates that are the nearest of all take the plane slots and vertex
+// slots that cutting the box by them would have given (each cut replaces the
+// four corners of its side in place), so the cell is bitwise that of the box
+// start, provided that each of those cuts removes just those corners (in a box
+// many spacings wide tilted planes may meet, and the slots then come out in
+// another order, which moves sums by a rounding).
+// Otherwise every plane of the cell takes the slot of its candidate's rank,
+// which keeps the order of distance.  With KEEP only the bitwise form is
+// taken: float arithmetic on the mesh turns a last-bit change of a sliver
+// face into differences of 1e-8 within some twenty steps.
+// The used candidates' entries are emptied (a zero normal cuts nothing).
+// Returns the wavefront mask of the halves whose planes take their rank's
+// slot; k0 is the first candidate left to try (0: the box start stands).
+template <bool KEEP>
+__device__ unsigned long long cube_start(PairLds& S, const GridParams& g, const bool act, const int nc, PairRegs& C,
+                                         int& k0) {
+  const int hl = hlane();
+  double4 q = make_double4(0.0, 0.0, 0.0, 0.0);
+  if (hl < nc) q = S.cd[hl];
+  const unsigned long long have = __ballot(act && hl < nc);
+  const unsigned long long xy = __ballot(fabs(q.x) >= fabs(q.y)), xz = __ballot(fabs(q.x) >= fabs(q.z)),
+                           yz = __ballot(fabs(q.y) >= fabs(q.z));
+  const unsigned long long X = xy & xz & have, Y = ~(xy & xz) & yz & have, Z = ~(xy & xz) & ~yz & have;
+  unsigned long long tryw = ~0ull;
+  if constexpr (KEEP) {
+    // Each of the six stays on its side of the generator all over the box and
+    // cuts off all four corners there: whatever their order, each cut then
+    // removes just the corners of its side.  (Tested before all else: points
+    // far from a lattice fail here.)
+    const bool ix = lane_on(X), iy = lane_on(Y);
+    const double ex = 0.5 * g.L[0] * fabs(q.x), ey = 0.5 * g.L[1] * fabs(q.y), ez = 0.5 * g.L[2] * fabs(q.z);
+    const double own = ix ? ex : (iy ? ey : ez), rest = ix ? ey + ez : (iy ? ex + ez : ex + ey);
+    tryw = ~halves_of(~__ballot(rest < q.w && own - rest > q.w) & 0x0000003f0000003full);
+    if (tryw == 0ull) return 0ull;
+  }
+  const unsigned long long nx = __ballot(q.x < 0.0), ny = __ballot(q.y < 0.0), nz = __ballot(q.z < 0.0);
+  const unsigned long long m[6] = {X & ~nx, X & nx, Y & ~ny, Y & ny, Z & ~nz, Z & nz};
+  unsigned long long okw = ~0ull, usedw = 0ull;
+  int kp[6];   // rank of each sector's nearest candidate
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const unsigned lo = (unsigned)m[k], hi = (unsigned)(m[k] >> 32);
+    okw &= halves_of(m[k]);
+    const unsigned l0 = lo & (0u - lo), h0 = hi & (0u - hi);   // lowest bits
+    usedw |= ((unsigned long long)h0 << 32) | l0;
+    const int a = 31 - __builtin_clz(l0 | 1u), b = 31 - __builtin_clz(h0 | 1u);
+    kp[k] = (__lane_id() & 32) ? b : a;
+  }
+  // Halves whose six are the nearest candidates.
+  const unsigned long long firstw = ~halves_of(usedw ^ 0x0000003f0000003full);
+  if constexpr (KEEP) okw &= firstw & tryw;
+  if (okw == 0ull) return 0ull;
+  // Corner hl (< 8) of its half; the other lanes repeat them.
+  const int sx = hl & 1, sy = (hl >> 1) & 1, sz = (hl >> 2) & 1;
+  const int px = kp[sx], py = kp[2 + sy], pz = kp[4 + sz];
+  const bool odd = (sx ^ sy ^ sz) != 0;
+  const int pb = odd ? pz : py, pc = odd ? py : pz;
+  // (px, pb, pc) turned so that the largest rank comes last.
+  const int pm = max(px, max(pb, pc));
+  const int ia = pm == px ? pb : (pm == pb ? pc : px), ib = pm == px ? pc : (pm == pb ? px : pb);
+  const double4 A = S.cd[ia], B = S.cd[ib], P = S.cd[pm];
+  double vx, vy, vz;
+  intersect3(A, B, P, vx, vy, vz);
+  const double det = P.x * (A.y * B.z - A.z * B.y) + P.y * (A.z * B.x - A.x * B.z) + P.z * (A.x * B.y - A.y * B.x);
+  bool in = det > 0.0 && fabs(vx) < 0.5 * g.L[0] && fabs(vy) < 0.5 * g.L[1] && fabs(vz) < 0.5 * g.L[2];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const double4 o = S.cd[k == 0 ? kp[1 - sx] : (k == 1 ? kp[3 - sy] : kp[5 - sz])];
+    in = in && o.x * vx + o.y * vy + o.z * vz < o.w;
+  }
+  okw &= ~halves_of(__ballot(!in));
+  if (okw == 0ull) return 0ull;
+  const int at = KEEP || lane_on(firstw) ? 6 : 0;   // plane slot of rank 0
+  const unsigned long long corner = okw & 0x000000ff000000ffull;
+  if (lane_on(corner)) {
+    const unsigned x = (unsigned)(ia + at), y = (unsigned)(ib + at), p = (unsigned)(pm + at);
+    C.t0 = x | (y << 8) | (p << 16);
+    C.v0x = vx;
+    C.v0y = vy;
+    C.v0z = vz;
+    S.E[__umul24(x, kPlanesP) + y] = (uint8_t)hl;
+    S.E[__umul24(y, kPlanesP) + p] = (uint8_t)hl;
+    S.E[__umul24(p, kPlanesP) + x] = (uint8_t)hl;
+  }
+  usedw &= okw;
+  if (lane_on(usedw)) {
+    S.pl[hl + at] = q;
+    S.pcand[hl + at] = S.cjk[hl];
+    S.cd[hl] = make_double4(0.0, 0.0, 0.0, q.w);
+  }
+  wave_sync();
+  C.L0w = (C.L0w & ~okw) | corner;
+  const double nb = half_max_bound(vx * vx + vy * vy + vz * vz);   // (finite in the halves that take it)
+  if (lane_on(okw)) {
+    const unsigned used = hbits(usedw);
+    C.rmax2 = nb;
+    C.np = 32 - __builtin_clz(used) + at;
+    k0 = __builtin_ctz(~used);
+  }
+  return KEEP ? 0ull : okw & ~firstw;
+}
+
 // Cuts each half's cell by its ordered candidates (as clip_candidates).
 // Each half first steps on its own to its next candidate that cuts, and
 // then both cut: about a third of the candidates cut nothing, different ones
 // in the two halves, and a step past one is a fraction of a cut (with one
 // candidate index for both halves, 22 of a lattice cell's 26 candidates
 // went through the cut for a half or the other; now its own 17).
-// Returns 0 or a failure bit for this half's cell.
-__device__ int clip_pair(PairLds& S, const int nc, PairRegs& C) {
+// cubew: the halves whose planes take the slot of their candidate's rank
+// (cube_start, only with RANKS); k: the half's first candidate.  Returns 0 or a failure
+// bit for this half's cell.
+template <bool RANKS>
+__device__ int clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned long long cubew, int k) {
   const int hl = hlane();
   constexpr unsigned long long LO = 0xffffffffull, HI = ~LO;
   // The per-half state is held as wavefront masks (a half's 32 bits all set
   // or all clear) and per-half counters, which the compiler keeps in scalar
   // registers: a lane's own flag is a select on the mask, and the loop's
   // control is scalar work apart from the compares behind its ballots.
-  unsigned long long donew = __ballot(nc <= 0);   // halves that stopped
+  unsigned long long donew = __ballot(k >= nc);   // halves that stopped
   unsigned long long stalew = 0ull;                // rmax2 older than the last cut
   unsigned long long failp = 0ull, failv = 0ull;  // halves out of plane or vertex slots
   int since0 = 0, since1 = 0;                      // cuts since each half's last bound
   double lim = 2.0 * C.rmax2;
-  int k = 0;   // the half's next candidate
   double4 q = make_double4(0.0, 0.0, 0.0, 0.0);
   for (;;) {
     // To the next candidate that cuts.  A half that found its own waits with
@@ -1826,12 +1941,12 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C) {
 
     // Plane slot: the next unused one (a cell that needs more goes to the
     // one-cell pass, which reuses the slots of faces cut away).
-    const unsigned p = (unsigned)C.np;
+    const unsigned p = RANKS && lane_on(cubew) ? (unsigned)(k - 1) : (unsigned)C.np;
     const unsigned long long fullw = __ballot(p >= (unsigned)kPlanesP) & cutw;
     failp |= fullw;
     donew |= fullw;
     const unsigned long long gow = cutw & ~fullw;
-    if (lane_on(gow)) C.np = (int)p + 1;
+    if (lane_on(gow)) C.np = RANKS ? max(C.np, (int)p + 1) : (int)p + 1;
     // The half's kept vertices as a set over its 64 slots (bit v: slot v,
     // the first register's 32 slots, then the second's).
     const unsigned long long K =
@@ -2128,7 +2243,8 @@ __device__ __forceinline__ int gather_half(PairLds& S, const TessArgs& A, const 
 // half cannot finish is handed to the one-cell pass of its kind.
 // ONE: one segment, whose grid comes with the kernel's arguments (scalar
 // loads at the start, instead of a load that waits for the cell's segment).
-template <bool DENSE, bool ONE>
+// KEEP: see cube_start (lean pass).
+template <bool DENSE, bool ONE, bool KEEP>
 __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) {
   const int hl = hlane();
   const int seg = ONE ? 0 : A.sseg[s];
@@ -2193,9 +2309,12 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
     }
     if (!work) nc = 0;
     sort_pair(S, nc);
+    int k0 = 0;
+    unsigned long long cubew = 0ull;
+    if constexpr (!DENSE) cubew = cube_start<KEEP>(S, g, work, nc, C, k0);
     // A failure (plane or vertex slots): the one-cell pass builds the cell
     // again.
-    if (clip_pair(S, nc, C) && work) {
+    if (clip_pair<!DENSE && !KEEP>(S, nc, C, cubew, k0) && work) {
       if (hl == 0) redo_cell<DENSE>(A, s);
       act = work = false;
     }
@@ -2246,7 +2365,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
         }
         if (!go) nc2 = 0;
         sort_pair(S2, nc2);
-        if (clip_pair(S2, nc2, C) && go) {
+        if (clip_pair<false>(S2, nc2, C, 0ull, 0) && go) {
           if (hl == 0) redo_cell<DENSE>(A, s);
           act = go = false;
         }
@@ -2280,12 +2399,12 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
 }
 
 // Two cells per wavefront: cells 2w and 2w + 1 of the launch.
-template <bool ONE>
+template <bool ONE, bool KEEP>
 __global__ __launch_bounds__(64) void k_tess_pair(TessArgs A) {
   __shared__ PairLds lds[2];
   const int64_t s64 = 2 * xcd_block() + (__lane_id() >> 5);
   const bool act = s64 < A.n;
-  pair_cell<false, ONE>(lds[__lane_id() >> 5], A, act, act ? (int)s64 : 0);
+  pair_cell<false, ONE, KEEP>(lds[__lane_id() >> 5], A, act, act ? (int)s64 : 0);
 }
 
 // The listed cells of dense regions, two per wavefront: those of the dense
@@ -2314,7 +2433,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   if (it >= npair) return;
   const int64_t q = 2 * it + (__lane_id() >> 5);
   const bool act = q < nd;
-  pair_cell<true, ONE>(lds[__lane_id() >> 5], A, act, A.dcells[act ? q : 2 * it]);
+  pair_cell<true, ONE, true>(lds[__lane_id() >> 5], A, act, A.dcells[act ? q : 2 * it]);
 }
 
 // The one-cell first pass over the cells the pair pass handed on.  Four
@@ -2338,7 +2457,7 @@ int64_t launch_tessellate(const double* spos, int64_t n, const SegDesc* segs, co
                           const unsigned long long* boff, const unsigned long long* sbase, const uint32_t* soffs,
                           StageNbr* stage_nb, StageGeo* stage_geo, unsigned long long* counts, double* geo,
                           double* rmax2, int32_t* deferred, int32_t* dcells, int32_t* redo, const TessHints& hints,
-                          const GridParams* g_one, DevStatus* st_dev, SegStatus* segst, hipStream_t st) {
+                          const GridParams* g_one, bool keep_bits, DevStatus* st_dev, SegStatus* segst, hipStream_t st) {
   if (n <= 0) return 0;
   // Grid of the two-cell dense pass: the last tessellation's dense-list
   // length and a quarter more (all cells when there is none yet).
@@ -2348,10 +2467,11 @@ int64_t launch_tessellate(const double* spos, int64_t n, const SegDesc* segs, co
   TessArgs A{spos,   n,     segs,     sseg,   boff,      sbase,  soffs, stage_nb, stage_geo, counts,
              geo,    rmax2, deferred, dcells, redo,      dense_cap, st_dev, segst, GridParams{}};
   if (g_one) A.g1 = *g_one;
-  if (g_one)
-    hipLaunchKernelGGL(k_tess_pair<true>, dim3((unsigned)((n + 1) / 2)), dim3(64), 0, st, A);
-  else
-    hipLaunchKernelGGL(k_tess_pair<false>, dim3((unsigned)((n + 1) / 2)), dim3(64), 0, st, A);
+  const dim3 pairs((unsigned)((n + 1) / 2));
+  if (g_one && keep_bits) hipLaunchKernelGGL((k_tess_pair<true, true>), pairs, dim3(64), 0, st, A);
+  else if (g_one) hipLaunchKernelGGL((k_tess_pair<true, false>), pairs, dim3(64), 0, st, A);
+  else if (keep_bits) hipLaunchKernelGGL((k_tess_pair<false, true>), pairs, dim3(64), 0, st, A);
+  else hipLaunchKernelGGL((k_tess_pair<false, false>), pairs, dim3(64), 0, st, A);
   // Short lists (the last tessellation's, or those of a mesh of at most
   // kRestCells cells whatever they hold): one launch for all of them.  Dense
   // lists of larger meshes keep the two-cell dense pass.

@@ -312,7 +312,8 @@ void Engine::enqueue_tessellation(const double* pos, int64_t n_slots, const int3
   // One segment: its grid (the descriptor set last) travels with the
   // pair passes' arguments.
   last_dense_cap = launch_tessellate(spos, n_cells, segs, sseg, boff, sbase, soffs, stage_nb, stage_geo, counts, geo,
-                                     rmax2, deferred, dcells, redo, hints, nseg == 1 ? &segs_host[0].g : nullptr, st,
+                                     rmax2, deferred, dcells, redo, hints, nseg == 1 ? &segs_host[0].g : nullptr,
+                                     precision == MM_MIXED, st,
                                      segst, stream);
   mark(2);
   launch_mesh_scan(counts, n_cells, off, soff, scan_tmp, st, stream);

@@ -329,11 +329,14 @@ struct TessHints {
 
 // Tessellation: pass 1 over every cell, then the listed and deferred cells.
 // Returns the number of listed dense cells the two-cell dense pass takes.
+// keep_bits: only the starts of a cell that leave its every bit as the box
+// start gives it (mixed precision).
 int64_t launch_tessellate(const double* spos, int64_t n, const SegDesc* segs, const int32_t* sseg,
                           const unsigned long long* boff, const unsigned long long* sbase, const uint32_t* soffs,
                           StageNbr* stage_nb, StageGeo* stage_geo, unsigned long long* counts, double* geo,
                           double* rmax2, int32_t* deferred, int32_t* dcells, int32_t* redo, const TessHints& hints,
-                          const GridParams* g_one, DevStatus* st_dev, SegStatus* segst, hipStream_t st);
+                          const GridParams* g_one, bool keep_bits, DevStatus* st_dev, SegStatus* segst,
+                          hipStream_t st);
 
 // Per-cell lists (face ids with sign, neighbour entries) use a sliced ELL
 // layout: slices of 64 consecutive internal cells, each as wide as its

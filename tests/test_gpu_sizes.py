@@ -22,3 +22,18 @@ def test_tessellation_at_path_edges(orc, n):
     # amplified by nearly co-spherical generators (1e-9 of the cell scale, as
     # in the full-size samples).
     compare_mesh(mm, om, ftol=1e-9)
+
+
+# Cells started from their six nearest sector neighbours: nearly exact
+# lattices (all of them, bitwise as from the box), jittered ones (some, in
+# rank order), a long box (tilted planes meet inside it), and points so
+# irregular that most start from the box.
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape,jitter", [((12, 11, 10), 1e-3), ((11, 12, 13), 0.1), ((13, 10, 11), 0.3),
+                                          ((48, 6, 6), 0.05), ((48, 6, 7), 0.25), ((9, 9, 9), 0.5)])
+def test_lattice_starts(orc, shape, jitter, precision):
+    box = tuple(s / shape[1] for s in shape)
+    pos = W.jittered_lattice(shape, box, jitter=jitter, seed=31)
+    mm, info, om = mesh_pair(orc, pos, box, precision=precision)
+    assert om.status == 0 and om.delta_min > 1e-12
+    compare_mesh(mm, om, ftol=1e-9)
