@@ -599,7 +599,7 @@ __device__ int gather_runs(TessLds& S, const TessArgs& A, const GridParams& g, c
 // CAP: an overflow, of which only the first CAP are stored), or -1 when a run
 // holds more than kRunMax points (a dense region: the cell goes to the dense
 // passes).  Called by the whole wavefront (act: the lane's group has a cell).
-constexpr int kRowPoints = 3;
+constexpr int kRowPoints = 2;
 constexpr int kRunMax = 24;
 
 // The part of the row at x = t (unwrapped, at most `left` buckets) that lies
@@ -2275,16 +2275,32 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
   for (int a = 0; a < 3; ++a) reach = fmin(reach, ring * g.hb[a] + edge[a]);
   double lo2 = 0.0, hi2 = fmin(reach * reach, rloc * rloc);
   // The first radius, then, for a cell whose candidates do not reach twice
-  // its farthest vertex, more distance shells as in the one-cell passes
-  // (irregular inputs need one often): up to kShells1 in the dense pass,
-  // one in the lean pass (below).  A cell still short, or whose shell needs
-  // a wider stencil than the grid has, is handed on.
+  // its farthest vertex, up to kShells1 more distance shells, as in the
+  // one-cell passes (irregular inputs need one or two often).  A cell still
+  // short, or whose shell needs a wider stencil than the grid has, is handed
+  // on.
   // work: the half gathers and cuts in this round (a half whose cell is
   // complete takes no further candidates: cutting a cell again by planes it
   // already has can split, by rounding, the vertices that lie on them).
+  // In the lean pass the generator's geometry is taken afresh in each round,
+  // opaque to the compiler, so that little derived from it stays live across the cuts: the
+  // loop then keeps 4 waves per SIMD with a spill of a few registers, where
+  // the lean pass had one extra shell written out after the first (random
+  // points: 9% of the cells fell short of it and were built again by the
+  // one-cell pass: 0.43 of 2.64 ms at 300,001 points, now 0.11 of 2.30).  One
+  // gather call in a loop for the first try and the narrower one spilled
+  // more (lattices 5% slower), and so did a thin region's wider first radius
+  // in this pass (the polytropes' background 1.5 times the one-cell pass's
+  // time).
   bool work = act;
   for (int shell = 0;; ++shell) {
-    int nc = gather_half<DENSE>(S, A, g, work, s, r, b, ring, lo2, hi2);
+    int s1 = s;
+    if constexpr (!DENSE) asm volatile("" : "+v"(s1));
+    const GridParams& g1 = DENSE ? g : (ONE ? A.g1 : A.segs[A.sseg[s1]].g);
+    CellGeom fresh;
+    if constexpr (!DENSE) cell_geom(A, g1, s1, fresh);
+    const CellGeom& G1 = DENSE ? G : fresh;
+    int nc = gather_half<DENSE>(S, A, g1, work, s1, G1.r, G1.b, ring, lo2, hi2);
     if (!DENSE && work && nc < 0) {
       if (hl == 0) A.dcells[atomicAdd(&A.st->n_dense_cells, 1)] = s;
       act = work = false;
@@ -2298,7 +2314,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
     const bool over = work && nc > kCandsP && (!DENSE || shell == 0);
     if (__ballot(over)) {
       if (over) hi2 = shell_for(lo2, hi2, nc, 38.0);
-      const int nc2 = gather_half<DENSE>(S, A, g, over, s, r, b, ring, lo2, hi2);
+      const int nc2 = gather_half<DENSE>(S, A, g1, over, s1, G1.r, G1.b, ring, lo2, hi2);
       if (over) nc = nc2;
     }
     // Too many candidates, or (lean pass, first radius) few: a thin region,
@@ -2311,7 +2327,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
     sort_pair(S, nc);
     int k0 = 0;
     unsigned long long cubew = 0ull;
-    if constexpr (!DENSE) cubew = cube_start<KEEP>(S, g, work, nc, C, k0);
+    if (!DENSE && shell == 0) cubew = cube_start<KEEP>(S, g, work, nc, C, k0);
     // A failure (plane or vertex slots): the one-cell pass builds the cell
     // again.
     if (clip_pair<!DENSE && !KEEP>(S, nc, C, cubew, k0) && work) {
@@ -2319,67 +2335,16 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
       act = work = false;
     }
     bool go = work && !(4.0 * C.rmax2 <= hi2 * (1.0 - 1e-12));
-    if constexpr (!DENSE) {
-      // One more shell here (the one-cell passes take up to kShells1); a
-      // cell still short is handed on.  The generator's geometry and the
-      // LDS address are taken afresh, opaque to the compiler, so that
-      // nothing derived from them stays live across the first cuts: the
-      // pass keeps 128 VGPRs and 4 waves per SIMD (146 otherwise), and a
-      // loop over shells would hold more.
-      if (__ballot(go)) {
-        int s2 = s;
-        asm volatile("" : "+v"(s2));
-        PairLds* Sp = &S;
-        asm volatile("" : "+v"(Sp));
-        PairLds& S2 = *Sp;
-        const GridParams& g2 = ONE ? A.g1 : A.segs[A.sseg[s2]].g;
-        CellGeom G2;
-        cell_geom(A, g2, s2, G2);
-        int ring2 = 0;
-        if (go) {
-          const double nhi2 = next_shell(C.rmax2, lo2, hi2, nc, 38.0);
-          ring2 = ring_for(g2, G2.edge, nhi2);
-          if (ring2 > g2.nb[0] || ring2 > g2.nb[1] || ring2 > g2.nb[2]) {
-            if (hl == 0) redo_cell<DENSE>(A, s);
-            act = go = false;
-          } else {
-            lo2 = hi2;
-            hi2 = nhi2;
-          }
-        }
-        int nc2 = gather_half<DENSE>(S2, A, g2, go, s2, G2.r, G2.b, ring2, lo2, hi2);
-        // A shell that overflows is narrowed once (the one-cell pass takes
-        // the cell on if it still falls short).
-        const bool over2 = go && nc2 > kCandsP;
-        if (__ballot(over2)) {
-          if (over2) hi2 = shell_for(lo2, hi2, nc2, 38.0);
-          const int nc3 = gather_half<DENSE>(S2, A, g2, over2, s2, G2.r, G2.b, ring2, lo2, hi2);
-          if (over2) nc2 = nc3;
-        }
-        if (go && (nc2 < 0 || nc2 > kCandsP)) {
-          if (hl == 0) {
-            if (nc2 < 0) A.dcells[atomicAdd(&A.st->n_dense_cells, 1)] = s;
-            else redo_cell<DENSE>(A, s);
-          }
-          act = go = false;
-        }
-        if (!go) nc2 = 0;
-        sort_pair(S2, nc2);
-        if (clip_pair<false>(S2, nc2, C, 0ull, 0) && go) {
-          if (hl == 0) redo_cell<DENSE>(A, s);
-          act = go = false;
-        }
-        if (go && !(4.0 * C.rmax2 <= hi2 * (1.0 - 1e-12))) {
-          if (hl == 0) redo_cell<DENSE>(A, s);
-          act = false;
-        }
-      }
-      break;
-    }
     if (__ballot(go) == 0ull) break;
     if (go) {
+      int s3 = s;
+      if constexpr (!DENSE) asm volatile("" : "+v"(s3));
+      const GridParams& g3 = DENSE ? g : (ONE ? A.g1 : A.segs[A.sseg[s3]].g);
+      CellGeom fresh3;
+      if constexpr (!DENSE) cell_geom(A, g3, s3, fresh3);
+      const CellGeom& G3 = DENSE ? G : fresh3;
       const double nhi2 = next_shell(C.rmax2, lo2, hi2, nc, 38.0);
-      ring = ring_for(g, edge, nhi2);
+      ring = ring_for(g3, G3.edge, nhi2);
       if (shell == kShells1 || ring > g.nb[0] || ring > g.nb[1] || ring > g.nb[2]) {
         if (hl == 0) redo_cell<DENSE>(A, s);
         act = go = false;
@@ -2400,7 +2365,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
 
 // Two cells per wavefront: cells 2w and 2w + 1 of the launch.
 template <bool ONE, bool KEEP>
-__global__ __launch_bounds__(64) void k_tess_pair(TessArgs A) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_tess_pair(TessArgs A) {
   __shared__ PairLds lds[2];
   const int64_t s64 = 2 * xcd_block() + (__lane_id() >> 5);
   const bool act = s64 < A.n;
