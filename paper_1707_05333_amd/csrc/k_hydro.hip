@@ -298,6 +298,9 @@ __device__ void seg_min_dt(double v, int seg, bool active, SegStatus* segst) {
   }
 }
 
+// With Qs (the step) the charges are kept and U and w written in internal
+// order; without it (component calls) U and w, either of which may be NULL,
+// are the caller's arrays in slot order.
 template <typename R>
 __global__ __launch_bounds__(kThreads) void k_cell_state(const SegDesc* __restrict__ segs,
                                                          const int32_t* __restrict__ sseg, int64_t n,
@@ -350,11 +353,16 @@ __global__ __launch_bounds__(kThreads) void k_cell_state(const SegDesc* __restri
     const double wx = eta * vx + dwx, wy = eta * vy + dwy, wz = eta * vz + dwz;
     const double rx = vx - wx, ry = vy - wy, rz = vz - wz;
     dti = hp.cfl * Rr / (cs + sqrt(rx * rx + ry * ry + rz * rz));
-    w[3 * s] = wx;
-    w[3 * s + 1] = wy;
-    w[3 * s + 2] = wz;
+    const int64_t o = Qs ? s : q;
+    if (w) {
+      w[3 * o] = wx;
+      w[3 * o + 1] = wy;
+      w[3 * o + 2] = wz;
+    }
+    if (U) {
 #pragma unroll
-    for (int k = 0; k < 5; ++k) U[5 * s + k] = (R)u[k];
+      for (int k = 0; k < 5; ++k) U[5 * o + k] = (R)u[k];
+    }
     if (!(dti > 0.0 && dti < 1e300)) {
       seg_fail(st, segst, seg, F_NONFINITE, (int)s);
       dti = 1e300;
@@ -389,6 +397,7 @@ __global__ __launch_bounds__(64) MM_MAX_WAVES(sizeof(R) == 8 ? 2 : 4) void k_gra
                                                        const unsigned long long* __restrict__ soff,
                                                        const NbrEntry<R>* __restrict__ nbr,
                                                        const double* __restrict__ minv, int limit, R* __restrict__ G,
+                                                       const int32_t* __restrict__ g_rows,
                                                        const double* __restrict__ w, const SegStatus* dt_src,
                                                        double dt_fixed, R* __restrict__ Uh,
                                                        FluxCell<R>* __restrict__ rec, const double* __restrict__ geo,
@@ -523,8 +532,9 @@ __global__ __launch_bounds__(64) MM_MAX_WAVES(sizeof(R) == 8 ? 2 : 4) void k_gra
     }
   }
   if (G) {
+    const int64_t o = g_rows ? g_rows[s] : s;
 #pragma unroll
-    for (int k = 0; k < 15; ++k) G[15 * s + k] = g[k];
+    for (int k = 0; k < 15; ++k) G[15 * o + k] = g[k];
   }
   if (rec) {
     FluxCell<R> C;
@@ -556,29 +566,28 @@ __global__ __launch_bounds__(64) MM_MAX_WAVES(sizeof(R) == 8 ? 2 : 4) void k_gra
   }
 }
 
+// Half-step predictor of one simulation's cells, in whatever order the caller
+// keeps them: a cell's rate needs its own rows only.
 template <typename R>
-__global__ __launch_bounds__(kThreads) void k_predict(const SegDesc* __restrict__ segs,
-                                                      const int32_t* __restrict__ sseg, int64_t n,
+__global__ __launch_bounds__(kThreads) void k_predict(const SegDesc* __restrict__ segs, int64_t n,
                                                       const R* __restrict__ U, const R* __restrict__ G,
-                                                      const double* __restrict__ w, const SegStatus* dt_src,
-                                                      double dt_fixed, R* __restrict__ Uh, SegStatus* segst) {
-  const int64_t s = xcd_block() * blockDim.x + threadIdx.x;
+                                                      const double* __restrict__ w, double dt, R* __restrict__ Uh,
+                                                      SegStatus* segst) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n) return;
-  const int seg = sseg[s];
-  const HydroParams& hp = segs[seg].hp;
+  const HydroParams& hp = segs[0].hp;
   R ui[5], g[15], rt[5], uh[5];
 #pragma unroll
   for (int q = 0; q < 5; ++q) ui[q] = U[5 * s + q];
 #pragma unroll
   for (int k = 0; k < 15; ++k) g[k] = G[15 * s + k];
   const R wv[3] = {(R)w[3 * s], (R)w[3 * s + 1], (R)w[3 * s + 2]};
-  const double dt = seg_dt(segs, dt_src, seg, dt_fixed);
   state_rate(ui, g, wv, (R)(hp.gamma - 1.0), hp.predictor_frame == 0, rt);
   const R hdt = (R)(0.5 * dt);
 #pragma unroll
   for (int q = 0; q < 5; ++q) uh[q] = ui[q] + hdt * rt[q];
   if (apply_floors(uh, (R)(hp.gamma - 1.0), (R)hp.rho_floor, (R)hp.p_floor))
-    atomicAdd(&segst[seg].floor_hits[1], 1ull);
+    atomicAdd(&segst[0].floor_hits[1], 1ull);
 #pragma unroll
   for (int q = 0; q < 5; ++q) Uh[5 * s + q] = uh[q];
 }
@@ -846,20 +855,25 @@ __global__ __launch_bounds__(64) MM_MAX_WAVES(8) void k_entropy_gradient(
   if (recx) recx[s] = XCell<R>{xi, {g[0], g[1], g[2]}};
 }
 
+// Face kernel records from the caller's rows (slot order).
 template <typename R>
-__global__ void k_pack_flux_cells(int64_t n, const R* __restrict__ U, const R* __restrict__ G,
-                                  const double* __restrict__ w, const double* __restrict__ geo,
-                                  const double* __restrict__ spos, FluxCell<R>* __restrict__ rec) {
+__global__ __launch_bounds__(kThreads) void k_pack_flux_cells(int64_t n, const int32_t* __restrict__ perm,
+                                                              const R* __restrict__ U, const R* __restrict__ G,
+                                                              const double* __restrict__ w,
+                                                              const double* __restrict__ geo,
+                                                              const double* __restrict__ spos,
+                                                              FluxCell<R>* __restrict__ rec) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n) return;
+  const int64_t o = perm[s];
   FluxCell<R> C;
 #pragma unroll
-  for (int q = 0; q < 5; ++q) C.U[q] = U[5 * s + q];
+  for (int q = 0; q < 5; ++q) C.U[q] = U[5 * o + q];
 #pragma unroll
-  for (int k = 0; k < 15; ++k) C.G[k] = G[15 * s + k];
+  for (int k = 0; k < 15; ++k) C.G[k] = G[15 * o + k];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    C.w[a] = w[3 * s + a];
+    C.w[a] = w[3 * o + a];
     C.c[a] = geo[4 * s + 1 + a];
     C.r[a] = spos[3 * s + a];
   }
@@ -1122,28 +1136,28 @@ void launch_cell_state(const SegDesc* segs, const int32_t* sseg, int64_t n, cons
 template <typename R>
 void launch_gradient(const SegDesc* segs, const int32_t* sseg, int64_t n, const R* U,
                      const unsigned long long* counts, const unsigned long long* soff, const NbrEntry<R>* nbr,
-                     const double* minv, int limit, R* G, const double* w, const SegStatus* dt_src, double dt_fixed,
-                     R* U_half, FluxCell<R>* rec, const double* geo, const double* spos, SegStatus* segst,
+                     const double* minv, int limit, R* G, const int32_t* g_rows, const double* w,
+                     const SegStatus* dt_src, double dt_fixed, R* U_half, FluxCell<R>* rec, const double* geo, const double* spos, SegStatus* segst,
                      hipStream_t st) {
   if (n <= 0) return;
   hipLaunchKernelGGL(k_gradient<R>, dim3(blocks_for(n, 64)), dim3(64), 0, st, segs, sseg, n, U, counts, soff, nbr,
-                     minv, limit, G, w, dt_src, dt_fixed, U_half, rec, geo, spos, segst);
+                     minv, limit, G, g_rows, w, dt_src, dt_fixed, U_half, rec, geo, spos, segst);
 }
 
 template <typename R>
-void launch_pack_flux_cells(int64_t n, const R* U, const R* G, const double* w, const double* geo,
-                            const double* spos, FluxCell<R>* rec, hipStream_t st) {
+void launch_pack_flux_cells(int64_t n, const int32_t* perm, const R* U, const R* G, const double* w,
+                            const double* geo, const double* spos, FluxCell<R>* rec, hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_pack_flux_cells<R>, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, n, U, G, w, geo,
-                     spos, rec);
+  hipLaunchKernelGGL(k_pack_flux_cells<R>, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, n, perm, U, G, w,
+                     geo, spos, rec);
 }
 
 template <typename R>
-void launch_predict(const SegDesc* segs, const int32_t* sseg, int64_t n, const R* U, const R* G, const double* w,
-                    const SegStatus* dt_src, double dt_fixed, R* U_half, SegStatus* segst, hipStream_t st) {
+void launch_predict(const SegDesc* segs, int64_t n, const R* U, const R* G, const double* w, double dt, R* U_half,
+                    SegStatus* segst, hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_predict<R>, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, segs, sseg, n, U, G, w,
-                     dt_src, dt_fixed, U_half, segst);
+  hipLaunchKernelGGL(k_predict<R>, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, segs, n, U, G, w, dt,
+                     U_half, segst);
 }
 
 template <typename R>
@@ -1304,12 +1318,12 @@ void launch_init_charges(const SegDesc* segs, const int32_t* sseg, int64_t n, co
                                      const double*, double*, R*, double*, DevStatus*, SegStatus*, hipStream_t);   \
   template void launch_gradient<R>(const SegDesc*, const int32_t*, int64_t, const R*, const unsigned long long*,  \
                                    const unsigned long long*, const NbrEntry<R>*, const double*, int, R*,         \
-                                   const double*, const SegStatus*, double, R*, FluxCell<R>*, const double*,      \
-                                   const double*, SegStatus*, hipStream_t);                                       \
-  template void launch_pack_flux_cells<R>(int64_t, const R*, const R*, const double*, const double*,              \
-                                          const double*, FluxCell<R>*, hipStream_t);                              \
-  template void launch_predict<R>(const SegDesc*, const int32_t*, int64_t, const R*, const R*, const double*,     \
-                                  const SegStatus*, double, R*, SegStatus*, hipStream_t);                         \
+                                   const int32_t*, const double*, const SegStatus*, double, R*, FluxCell<R>*,     \
+                                   const double*, const double*, SegStatus*, hipStream_t);                        \
+  template void launch_pack_flux_cells<R>(int64_t, const int32_t*, const R*, const R*, const double*,             \
+                                          const double*, const double*, FluxCell<R>*, hipStream_t);               \
+  template void launch_predict<R>(const SegDesc*, int64_t, const R*, const R*, const double*, double, R*,         \
+                                  SegStatus*, hipStream_t);                                                       \
   template void launch_flux<R>(const SegDesc*, int64_t, const unsigned long long*, const Face*,                    \
                                const FluxCell<R>*, const SegStatus*, double, R*, SegStatus*, hipStream_t,         \
                                const XCell<R>*, R*, float*);                                                      \

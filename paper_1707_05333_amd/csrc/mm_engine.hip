@@ -338,7 +338,7 @@ void enqueue_hydro(Engine& E, double* pos, double* w_slots, double* Q, int64_t n
   if (ent) launch_entropy_state<R>(n, E.perm, E.geo, S_slots, E.Ss, Xe, E.stream);
   E.mark(4);
   launch_gradient<R>(E.segs, E.sseg, n, U, E.counts, E.soff, (const NbrEntry<R>*)E.nbr, E.minv, kLimitMaskBit0,
-                     ent ? (R*)E.G : nullptr, E.w, E.segst, 0.0, Uh, nullptr, nullptr, nullptr, E.segst, E.stream);
+                     ent ? (R*)E.G : nullptr, nullptr, E.w, E.segst, 0.0, Uh, nullptr, nullptr, nullptr, E.segst, E.stream);
   if (ent)
     launch_entropy_gradient<R>(E.segs, E.sseg, n, Xe, E.counts, E.soff, (const NbrEntry<R>*)E.nbr, E.minv,
                                kLimitMaskBit0, U, (const R*)E.G, E.w, E.segst, Xh, nullptr, E.stream);
@@ -354,8 +354,8 @@ void enqueue_hydro(Engine& E, double* pos, double* w_slots, double* Q, int64_t n
     if (E.timing) (void)hipEventRecord(E.ev[10], E.stream);
   }
   E.mark(5);
-  launch_gradient<R>(E.segs, E.sseg, n, Uh, E.counts, E.soff, (const NbrEntry<R>*)E.nbr, E.minv, kLimitMaskBit1, nullptr, E.w, nullptr,
-                     0.0, nullptr, rec, E.geo, E.spos, E.segst, E.stream);
+  launch_gradient<R>(E.segs, E.sseg, n, Uh, E.counts, E.soff, (const NbrEntry<R>*)E.nbr, E.minv, kLimitMaskBit1, nullptr,
+                     nullptr, E.w, nullptr, 0.0, nullptr, rec, E.geo, E.spos, E.segst, E.stream);
   if (ent)
     launch_entropy_gradient<R>(E.segs, E.sseg, n, Xh, E.counts, E.soff, (const NbrEntry<R>*)E.nbr, E.minv,
                                kLimitMaskBit1, nullptr, nullptr, nullptr, E.segst, nullptr, recx, E.stream);

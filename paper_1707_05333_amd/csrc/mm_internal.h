@@ -356,6 +356,8 @@ void launch_build_mesh(const double* spos, const double* geo, int64_t n, const S
 // Hydro kernels, instantiated for double (MM_FP64) and float (MM_MIXED).
 // Slot-space arrays (Q, pos, w, prim) are indexed through perm.  dt_src
 // (may be NULL, then dt_fixed applies) holds each segment's CFL minimum.
+// With Qs, the charges go to Qs and U and w to internal order; without it U
+// and w (either may be NULL) go to slot order.
 template <typename R>
 void launch_cell_state(const SegDesc* segs, const int32_t* sseg, int64_t n, const double* Q_slots,
                        const int32_t* perm, const double* geo, double* Qs, R* U, double* w, DevStatus* st_dev,
@@ -363,21 +365,24 @@ void launch_cell_state(const SegDesc* segs, const int32_t* sseg, int64_t n, cons
 // Limiter selection of the gradient kernel: off, on, or the segment's own
 // limit_mask bit 0 (first gradient) / bit 1 (second gradient).
 enum : int { kLimitOff = 0, kLimitOn = 1, kLimitMaskBit0 = 2, kLimitMaskBit1 = 3 };
-// Gradients of U (to G when set); with U_half set, the half-step predictor
+// Gradients of U (to G when set: cell s to row g_rows[s], or to row s where
+// g_rows is NULL); with U_half set, the half-step predictor
 // (needs w); with rec set, the face kernel's cell records (needs w, geo and
 // spos).
 template <typename R>
 void launch_gradient(const SegDesc* segs, const int32_t* sseg, int64_t n, const R* U,
                      const unsigned long long* counts, const unsigned long long* soff, const NbrEntry<R>* nbr,
-                     const double* minv, int limit, R* G, const double* w, const SegStatus* dt_src, double dt_fixed,
-                     R* U_half, FluxCell<R>* rec, const double* geo, const double* spos, SegStatus* segst,
+                     const double* minv, int limit, R* G, const int32_t* g_rows, const double* w,
+                     const SegStatus* dt_src, double dt_fixed, R* U_half, FluxCell<R>* rec, const double* geo, const double* spos, SegStatus* segst,
                      hipStream_t st);
+// The face kernel's records from U, G and w in slot order.
 template <typename R>
-void launch_pack_flux_cells(int64_t n, const R* U, const R* G, const double* w, const double* geo,
-                            const double* spos, FluxCell<R>* rec, hipStream_t st);
+void launch_pack_flux_cells(int64_t n, const int32_t* perm, const R* U, const R* G, const double* w,
+                            const double* geo, const double* spos, FluxCell<R>* rec, hipStream_t st);
+// The half-step predictor alone (one segment; rows in any order, all alike).
 template <typename R>
-void launch_predict(const SegDesc* segs, const int32_t* sseg, int64_t n, const R* U, const R* G, const double* w,
-                    const SegStatus* dt_src, double dt_fixed, R* U_half, SegStatus* segst, hipStream_t st);
+void launch_predict(const SegDesc* segs, int64_t n, const R* U, const R* G, const double* w, double dt, R* U_half,
+                    SegStatus* segst, hipStream_t st);
 // nf_dev (device count, may be NULL) overrides nf_host, which then only
 // bounds the launch.
 // Entropy charges S = m P rho^-gamma of primitive states (slot order).

@@ -2,6 +2,8 @@
 tessellation of every such size against the oracle's."""
 from __future__ import annotations
 
+import ctypes
+
 import pytest
 
 import workloads as W
@@ -37,3 +39,40 @@ def test_lattice_starts(orc, shape, jitter, precision):
     mm, info, om = mesh_pair(orc, pos, box, precision=precision)
     assert om.status == 0 and om.delta_min > 1e-12
     compare_mesh(mm, om, ftol=1e-9)
+
+
+# The component calls write the caller's rows directly, unless an output lies
+# over an input (or over the other output): the results are the same bits.
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_component_outputs_over_inputs(orc, precision):
+    torch = pytest.importorskip("torch")
+    shape, box = (11, 9, 10), (1.0, 1.0, 1.0)
+    mm, _, _ = mesh_pair(orc, W.jittered_lattice(shape, box, jitter=0.2, seed=5), box, precision=precision)
+    n = mm.n
+    rng = torch.Generator().manual_seed(3)
+    prim = torch.rand(n, 5, generator=rng, dtype=torch.float64).add(0.5).to(mm.device)
+    Q = mm.init_charges(prim)
+    U, w, dt, _ = mm.cell_state(Q)
+    G = mm.gradients(U)
+    Uh = mm.predict(U, G, w, dt)
+    rs, dptr = U.element_size(), lambda t, at=0: ctypes.c_void_p(t.data_ptr() + at)
+
+    def state(buf, u_at, w_at, q):
+        d = ctypes.c_double()
+        mm._check(mm.lib.mm_cell_state(mm.ctx, dptr(q), dptr(buf, u_at), dptr(buf, w_at), ctypes.byref(d), None))
+        assert d.value == dt
+        return buf
+
+    # U over the charges, w behind them; then w over the charges.
+    for u_at, w_at in ((0, 40 * n), (40 * n, 0)):
+        buf = torch.zeros(80 * n, dtype=torch.uint8, device=mm.device)
+        buf[:40 * n].view(torch.float64).copy_(Q.view(-1))
+        state(buf, u_at, w_at, buf)
+        assert torch.equal(buf[u_at:u_at + 5 * rs * n].view(U.dtype).view(n, 5), U)
+        assert torch.equal(buf[w_at:w_at + 24 * n].view(torch.float64).view(n, 3), w)
+    # The half-step state over the state, and over the gradients.
+    for over in (U, G):
+        a = [t.clone() for t in (U, G)]
+        out = a[0] if over is U else a[1]
+        mm._check(mm.lib.mm_predict(mm.ctx, dptr(a[0]), dptr(a[1]), dptr(w), float(dt), dptr(out)))
+        assert torch.equal(out.view(-1)[:5 * n].view(n, 5), Uh)
