@@ -22,12 +22,22 @@ inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t - 1) / t
 constexpr int kGroup = 8;                        // lanes per cell in the assembly
 constexpr int kMeshThreads = 256;
 constexpr int kCellsPerBlock = kMeshThreads / kGroup;
+constexpr int kSearch = 16;                      // staged entries read per step of a search
+static_assert(kMaxFaces % kSearch == 0, "whole steps within a row");
 
 // Eight lanes per cell; lane l takes the cell's faces l, l + 8, ... (a lane
 // walks two or three faces: more cells per wavefront than with sixteen
 // lanes, whose last lanes idle while the first take a second face).
 // The packed prefix sum off[] holds, for cell s, the index of its first
 // unique face in its low 32 bits.
+// Bound by the address unit (95% busy): the scattered loads of a face's
+// neighbour.  The search for a face that the neighbour owns reads 16 staged
+// entries of 4 bytes at once, the first of them before the list's length is
+// known (one round for most lists, where 8-byte entries took eight a round
+// behind the length): 0.779 -> 0.742 ms FP64 and 0.687 -> 0.646 mixed at
+// 1,000,000 cells, 38.0 -> 33.8 us at 46,656.  Eight entries at once are as
+// fast there and 1 us slower at 46,656; fewer wavefronts (3 per SIMD: 0.763)
+// and more (6: 0.881), and stores past the cache (0.762), are slower.
 template <typename R>
 __global__ __launch_bounds__(kMeshThreads) void k_build_mesh(
     const double* __restrict__ spos, const double* __restrict__ geo, int64_t n, const SegDesc* __restrict__ segs,
@@ -55,13 +65,18 @@ __global__ __launch_bounds__(kMeshThreads) void k_build_mesh(
     }
     const double rx = spos[3 * s], ry = spos[3 * s + 1], rz = spos[3 * s + 2];
     const double cix = geo[4 * s + 1], ciy = geo[4 * s + 2], ciz = geo[4 * s + 3];
+    const int group0 = __lane_id() & ~(kGroup - 1);   // first lane of the group
+    int ranked = 0;
     for (int e = l; e < nf; e += kGroup) {
       const StageNbr Nb = stage_nb[s * kMaxFaces + e];
       const StageGeo F = stage_geo[s * kMaxFaces + e];
-      const int j = Nb.j;
-      const int code = Nb.meta & 255;
-      const bool owned = (Nb.meta >> 8) & 1;
-      const int orank = Nb.meta >> 16;
+      const int j = (int)(Nb >> 5);
+      const int code = (int)(Nb & 31u);
+      const bool owned = Nb > owned_above(s);
+      // Rank among the cell's owned faces.
+      const unsigned own = (unsigned)(__ballot(owned) >> group0) & ((1u << kGroup) - 1u);
+      const int orank = ranked + __popc(own & ((1u << l) - 1u));
+      ranked += __popc(own);
       int kx, ky, kz;
       decode(code, kx, ky, kz);
       // centroid displacement d = (c_j + s) - c_i = (r_j + s - r_i) + (c_j - r_j) - (c_i - r_i)
@@ -107,29 +122,31 @@ __global__ __launch_bounds__(kMeshThreads) void k_build_mesh(
         }
       } else {
         // The same face in the neighbour's list: neighbour s, opposite image.
-        // Two staged entries per 16-byte load (rows are 512-byte aligned).
-        const int want = 26 - code;
+        // Its rank among the owned faces there is counted on the way (this
+        // cell's index is the higher, so the neighbour owns it).
+        const StageNbr want = ((StageNbr)s << 5) | (StageNbr)(26 - code), above = owned_above(j);
         const int nfj = (int)(counts[j] >> 32);
-        const int4* row = reinterpret_cast<const int4*>(stage_nb + (int64_t)j * kMaxFaces);
-        // Eight entries per round, their loads issued together.
-        int found_meta = -1;
-        for (int t = 0; t < nfj && found_meta < 0; t += 8) {
-          int4 G[4];
+        const uint4* row = reinterpret_cast<const uint4*>(stage_nb + (int64_t)j * kMaxFaces);
+        int rank = 0, found = -1;
+        int t = 0;
+        do {
+          uint4 G[kSearch / 4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) G[u] = row[(t >> 1) + u];   // rows hold kMaxFaces entries: in bounds
+          for (int u = 0; u < kSearch / 4; ++u) G[u] = row[(t >> 2) + u];   // rows hold kMaxFaces entries: in bounds
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int e0 = t + 2 * u;
-            if (found_meta < 0 && e0 < nfj && G[u].x == (int)s && (G[u].y & 255) == want) found_meta = G[u].y;
-            if (found_meta < 0 && e0 + 1 < nfj && G[u].z == (int)s && (G[u].w & 255) == want) found_meta = G[u].w;
+          for (int u = 0; u < kSearch; ++u) {
+            const StageNbr g = (u & 3) == 0 ? G[u >> 2].x : (u & 3) == 1 ? G[u >> 2].y : (u & 3) == 2 ? G[u >> 2].z : G[u >> 2].w;
+            if (t + u < nfj && g == want) found = rank;
+            rank += g > above;
           }
-        }
-        if (found_meta < 0 || !((found_meta >> 8) & 1)) {
+          t += kSearch;
+        } while (t < nfj && found < 0);
+        if (found < 0) {
           bad |= F_ASYM;
           st->asym_cell = (int)s;
           st->asym_nbr = j;
         } else {
-          const int64_t fid = (int64_t)(off[j] & 0xffffffffull) + (found_meta >> 16);
+          const int64_t fid = (int64_t)(off[j] & 0xffffffffull) + found;
           if (fid < face_cap) entry = (int32_t)(fid | 0x80000000ll);
           else bad |= F_FACECAP;
         }

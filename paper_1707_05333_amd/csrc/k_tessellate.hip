@@ -980,6 +980,16 @@ __device__ int clip_candidates(TessLds& S, const int nc, CellRegs& C) {
   return 0;
 }
 
+// Staged neighbour of a plane of cell s: a candidate's (neighbour, image)
+// word, or the cell's own image across a box plane (-1 - p: axis p / 2, sign by
+// parity).
+__device__ inline StageNbr staged_nbr(int s, int pc) {
+  if (pc >= 0) return (StageNbr)pc;
+  const int bp = -1 - pc;
+  const int step = (bp >> 1) == 0 ? 1 : ((bp >> 1) == 1 ? 3 : 9);
+  return ((StageNbr)s << 5) | (StageNbr)((bp & 1) ? 13 - step : 13 + step);
+}
+
 // Faces, volume and centroid of the finished cell; writes the cell's outputs.
 __device__ int finish_cell(TessLds& S, const TessArgs& A, const int s, const CellRegs& C) {
   const int lane = __lane_id();
@@ -1059,26 +1069,12 @@ __device__ int finish_cell(TessLds& S, const TessArgs& A, const int s, const Cel
   const double czr = wave_sum(keep ? 0.75 * vol * fz : 0.0) * iV;
   if (!(V > 0.0)) return F_VOLUME;
 
-  int j = s, code = 13;
-  if (keep) {
-    const int pc = S.pcand[p];
-    if (pc >= 0) {
-      j = pc >> 5;
-      code = pc & 31;
-    } else {
-      const int bp = -1 - pc;   // box plane: axis bp/2, sign by parity
-      const int step = (bp >> 1) == 0 ? 1 : ((bp >> 1) == 1 ? 3 : 9);
-      code = (bp & 1) ? 13 - step : 13 + step;
-    }
-  }
-  const bool owned = keep && (j > s || (j == s && code > 13));
+  StageNbr nb = 0;
+  if (keep) nb = staged_nbr(s, S.pcand[p]);
+  const bool owned = keep && nb > owned_above(s);
   const unsigned long long MK = __ballot(keep), MO = __ballot(owned);
   if (keep) {
     const int idx = __popcll(MK & lanes_below());
-    const int orank = __popcll(MO & lanes_below());
-    StageNbr nb;
-    nb.j = j;
-    nb.meta = code | ((owned ? 1 : 0) << 8) | (orank << 16);
     A.stage_nb[(int64_t)s * kMaxFaces + idx] = nb;
     StageGeo& F = A.stage_geo[(int64_t)s * kMaxFaces + idx];
     F.A = Af;
@@ -2147,22 +2143,12 @@ __device__ int finish_pair(PairLds& S, const TessArgs& A, const bool act, const 
   const double czr = half_sum((keep[0] ? 0.75 * vol[0] * fz[0] : 0.0) + (keep[1] ? 0.75 * vol[1] * fz[1] : 0.0)) * iV;
   if (act && !(V > 0.0)) return F_VOLUME;
 
-  int jj[2] = {s, s}, code[2] = {13, 13};
+  StageNbr nb[2] = {0, 0};
   bool owned[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    if (keep[k]) {
-      const int pc = S.pcand[hl + 32 * k];
-      if (pc >= 0) {
-        jj[k] = pc >> 5;
-        code[k] = pc & 31;
-      } else {
-        const int bp = -1 - pc;   // box plane: axis bp/2, sign by parity
-        const int step = (bp >> 1) == 0 ? 1 : ((bp >> 1) == 1 ? 3 : 9);
-        code[k] = (bp & 1) ? 13 - step : 13 + step;
-      }
-    }
-    owned[k] = keep[k] && (jj[k] > s || (jj[k] == s && code[k] > 13));
+    if (keep[k]) nb[k] = staged_nbr(s, S.pcand[hl + 32 * k]);
+    owned[k] = keep[k] && nb[k] > owned_above(s);
   }
   // Faces staged in plane-slot order (planes 0-31 in lane order, then the rest).
   const unsigned MK0 = hbits(__ballot(keep[0])), MK1 = hbits(__ballot(keep[1]));
@@ -2171,11 +2157,7 @@ __device__ int finish_pair(PairLds& S, const TessArgs& A, const bool act, const 
   for (int k = 0; k < 2; ++k) {
     if (keep[k]) {
       const int idx = k ? __popc(MK0) + __popc(MK1 & hbelow()) : __popc(MK0 & hbelow());
-      const int orank = k ? __popc(MO0) + __popc(MO1 & hbelow()) : __popc(MO0 & hbelow());
-      StageNbr nb;
-      nb.j = jj[k];
-      nb.meta = code[k] | ((owned[k] ? 1 : 0) << 8) | (orank << 16);
-      A.stage_nb[(int64_t)s * kMaxFaces + idx] = nb;
+      A.stage_nb[(int64_t)s * kMaxFaces + idx] = nb[k];
       StageGeo& F = A.stage_geo[(int64_t)s * kMaxFaces + idx];
       F.A = Af[k];
       F.f[0] = fx[k];

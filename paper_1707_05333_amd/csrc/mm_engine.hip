@@ -50,7 +50,7 @@ int64_t engine_bytes_per_cell(int precision) {
   const int64_t per_cell = 4 * 6                                       // key, perm, sseg, deferred, dcells, redo
                            + 8 * (3 + 4 + 1 + 6 + 1 + 1)               // spos, geo, rmax2, minv, counts, off
                            + 16 + 8 + 4                                // bucket count, offset, sub-table base; sub-offsets
-                           + (int64_t)kMaxFaces * (sizeof(StageNbr) + sizeof(StageGeo))
+                           + (int64_t)kMaxFaces * (8 + sizeof(StageGeo))   // staged faces (their neighbours take half of the 8)
                            + kListPerCell * (4 + (r == 4 ? sizeof(NbrEntry<float>) : sizeof(NbrEntry<double>)))
                            + r * (5 + 15 + 5) + 8 * (3 + 5 + 3)        // U, G, Uh, w, Qs, pos0
                            + (r == 4 ? sizeof(FluxCell<float>) : sizeof(FluxCell<double>));

@@ -103,11 +103,12 @@ struct SegDesc {
 };
 
 // One face of a cell as written by the tessellation kernel (cell-local list),
-// split so that a search of a neighbour's list reads 8 bytes per entry.
-struct StageNbr {
-  int32_t j;        // neighbour cell (internal index)
-  int32_t meta;     // bits 0-7 image code, bit 8 owned, bits 16-31 rank among owned faces
-};
+// split so that a search of a neighbour's list reads 4 bytes per entry:
+// (j << 5) | image code of the neighbour (2^26 cells at most).
+using StageNbr = uint32_t;
+// A face is stored once, by the cell of lower index (a face between images of
+// one cell by the side with the higher code): entries of cell s above this.
+inline __host__ __device__ StageNbr owned_above(int64_t s) { return ((uint32_t)s << 5) | 13u; }
 struct StageGeo {
   double A;         // area
   double f[3];      // area centroid minus the generator
@@ -140,7 +141,6 @@ struct __align__(16) FluxCell {
   double pad[sizeof(R) == 4 ? 2 : 0];
 };
 
-static_assert(sizeof(StageNbr) == 8, "two staged entries per 16-byte load");
 static_assert(sizeof(FluxCell<float>) == 144 && sizeof(FluxCell<double>) == 240, "face kernel record sizes");
 
 // Per-cell neighbour entry used by the gradient kernels: neighbour index,
