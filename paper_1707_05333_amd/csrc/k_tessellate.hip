@@ -176,12 +176,12 @@ __device__ __forceinline__ unsigned long long plane_bits(uint32_t t) {
 // correctly rounded division outside the normal range, where the estimate
 // would over- or underflow.
 __device__ __forceinline__ double rcp_nr(double x) {
-  if (fabs(x) > 1e-280 && fabs(x) < 1e280) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
-  }
-  return 1.0 / x;
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  r = fma(fma(-x, r, 1.0), r, r);
+  const bool in = fabs(x) > 1e-280 && fabs(x) < 1e280;
+  if (__ballot(!in)) r = in ? r : 1.0 / x;   // (a branch that the wavefront takes or leaves as one)
+  return r;
 }
 
 // 1/sqrt(x) for x > 0 likewise: the hardware estimate and two Newton steps
@@ -1413,7 +1413,7 @@ struct __align__(16) PairLds {
       double4 cd[kCandsP];
       int32_t cjk[kCandsP];
       uint8_t order[kCandsP];
-      uint16_t elist[kVertsP];
+      uint16_t elist[kVertsP + 2];     // (and a spare place)
     };
     struct {                           // in the epilogue
       double vx[kVertsP], vy[kVertsP], vz[kVertsP];
@@ -1430,9 +1430,18 @@ __device__ __forceinline__ int hlane() { return __lane_id() & 31; }
 // The 32 bits of a wavefront mask that belong to this lane's half.
 __device__ __forceinline__ unsigned hbits(unsigned long long m) { return (unsigned)(m >> (__lane_id() & 32)); }
 __device__ __forceinline__ unsigned hbelow() { return (1u << hlane()) - 1u; }
-// All lanes of each half whose 32 bits of m are not all zero.
+// All lanes of the halves named (of the wavefront's values).
+__device__ __forceinline__ unsigned long long halves(bool low, bool high) {
+  const unsigned a = low ? ~0u : 0u, b = high ? ~0u : 0u;
+  return ((unsigned long long)b << 32) | a;
+}
+// All lanes of each half whose 32 bits of m are not all zero.  (The upper half
+// is taken opaque: the compiler would make its test a 64-bit compare, which
+// only the vector unit has.)
 __device__ __forceinline__ unsigned long long halves_of(unsigned long long m) {
-  return ((unsigned)m ? 0xffffffffull : 0ull) | ((m >> 32) ? 0xffffffff00000000ull : 0ull);
+  unsigned hi = (unsigned)(m >> 32);
+  asm volatile("" : "+s"(hi));
+  return halves((unsigned)m != 0u, hi != 0u);
 }
 
 // Inclusive prefix sum within each half: row shifts by 1, 2, 4 and 8 inside
@@ -1531,9 +1540,13 @@ __device__ void init_box_pair(PairLds& S, const GridParams& g, PairRegs& C) {
 }
 
 __device__ inline double farthest_bound_pair(const PairRegs& C) {
+  // (the vertices are taken opaque: the compiler would otherwise form their
+  // squares ahead of the test that needs them, in every cut)
+  double ax = C.v0x, ay = C.v0y, az = C.v0z, bx = C.v1x, by = C.v1y, bz = C.v1z;
+  asm volatile("" : "+v"(ax), "+v"(ay), "+v"(az), "+v"(bx), "+v"(by), "+v"(bz));
   double m2 = 0.0;
-  if (lane_on(C.L0w)) m2 = C.v0x * C.v0x + C.v0y * C.v0y + C.v0z * C.v0z;
-  if (lane_on(C.L1w)) m2 = fmax(m2, C.v1x * C.v1x + C.v1y * C.v1y + C.v1z * C.v1z);
+  if (lane_on(C.L0w)) m2 = ax * ax + ay * ay + az * az;
+  if (lane_on(C.L1w)) m2 = fmax(m2, bx * bx + by * by + bz * bz);
   return half_max_bound(m2);
 }
 
@@ -1877,49 +1890,58 @@ __device__ unsigned long long cube_start(PairLds& S, const GridParams& g, const 
 // in the two halves, and a step past one is a fraction of a cut (with one
 // candidate index for both halves, 22 of a lattice cell's 26 candidates
 // went through the cut for a half or the other; now its own 17).
+// A cut is some 140 vector instructions and, for the per-half masks, control
+// and exec branches, some 100 scalar ones.  The four wavefronts of a SIMD keep
+// its vector unit three quarters busy and its share of the scalar unit half, in
+// one dependent chain per wavefront, so both kinds count: with 150 scalar ones
+// (per-half refresh counters, a branch around every listed edge, free slots
+// counted for every cut, 64-bit mask tests) the pass took 3.72 ms instead of
+// 3.42 on the Sod tube of 1,048,576 cells, 3.76 instead of 3.41 on a blast of
+// 884,736 and 1.62 instead of 1.49 on a Gresho vortex of 425,984.  Six vector
+// instructions less at the side of that chain changed nothing measurable.
 // cubew: the halves whose planes take the slot of their candidate's rank
-// (cube_start, only with RANKS); k: the half's first candidate.  Returns 0 or a failure
-// bit for this half's cell.
+// (cube_start, only with RANKS); k: the half's first candidate.  Returns whether
+// this half's cell ran out of plane or vertex slots.
 template <bool RANKS>
-__device__ int clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned long long cubew, int k) {
+__device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned long long cubew, int k) {
   const int hl = hlane();
-  constexpr unsigned long long LO = 0xffffffffull, HI = ~LO;
   // The per-half state is held as wavefront masks (a half's 32 bits all set
-  // or all clear) and per-half counters, which the compiler keeps in scalar
-  // registers: a lane's own flag is a select on the mask, and the loop's
-  // control is scalar work apart from the compares behind its ballots.
+  // or all clear), which the compiler keeps in scalar registers: a lane's own
+  // flag is a select on the mask, and the loop's control is scalar work apart
+  // from the compares behind its ballots.
   unsigned long long donew = __ballot(k >= nc);   // halves that stopped
-  unsigned long long stalew = 0ull;                // rmax2 older than the last cut
-  unsigned long long failp = 0ull, failv = 0ull;  // halves out of plane or vertex slots
-  int since0 = 0, since1 = 0;                      // cuts since each half's last bound
+  unsigned long long stalew = 0ull;               // rmax2 older than the last cut
+  unsigned long long failw = 0ull;                // halves out of plane or vertex slots
+  int since = 0;                                  // cuts since the last bounds
   double lim = 2.0 * C.rmax2;
   double4 q = make_double4(0.0, 0.0, 0.0, 0.0);
+  const int last = nc - 1;
+  k = lane_on(donew) ? 0 : k - 1;                 // the candidate in q
+  auto bounds = [&]() {
+    const double nb = farthest_bound_pair(C);
+    if (lane_on(stalew)) {
+      C.rmax2 = nb;
+      lim = 2.0 * nb;
+    }
+    stalew = 0ull;
+    since = 0;
+  };
   for (;;) {
     // To the next candidate that cuts.  A half that found its own waits with
     // it; one that is stopped by the bound or out of candidates is done.
     unsigned long long M0w = 0ull, M1w = 0ull;       // vertices cut off
     unsigned long long cutw = 0ull;                  // halves with a candidate that cuts
     for (unsigned long long seekw = ~donew; seekw;) {
-      if (lane_on(seekw)) {
-        q = S.cd[k];
-        ++k;
-      }
+      k += lane_on(seekw) ? 1 : 0;
+      q = S.cd[k];
       // Stop test of each half: farther images cannot cut its cell.  A bound
       // older than the last cut is refreshed and the test taken again.
-      const unsigned long long farw = __ballot(q.w >= lim) & seekw;
+      unsigned long long farw = __ballot(q.w >= lim) & seekw;
       if (farw) {
-        const double nb = farthest_bound_pair(C);
-        const unsigned long long refw = farw & stalew;
-        if (lane_on(refw)) {
-          C.rmax2 = nb;
-          lim = 2.0 * nb;
-        }
-        stalew &= ~refw;
-        if (refw & LO) since0 = 0;
-        if (refw & HI) since1 = 0;
-        const unsigned long long stopw = (farw & ~refw) | (refw & __ballot(q.w >= lim));
-        donew |= stopw;
-        seekw &= ~stopw;
+        bounds();
+        farw &= __ballot(q.w >= lim);
+        donew |= farw;
+        seekw &= ~farw;
       }
       const unsigned long long n0 = __ballot(q.x * C.v0x + q.y * C.v0y + q.z * C.v0z > q.w) & seekw & C.L0w;
       const unsigned long long n1 = __ballot(q.x * C.v1x + q.y * C.v1y + q.z * C.v1z > q.w) & seekw & C.L1w;
@@ -1928,7 +1950,7 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned l
       M1w |= n1;
       cutw |= hitw;
       seekw &= ~hitw;
-      const unsigned long long endw = __ballot(k >= nc) & seekw;
+      const unsigned long long endw = __ballot(k >= last) & seekw;
       donew |= endw;
       seekw &= ~endw;
     }
@@ -1937,12 +1959,8 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned l
 
     // Plane slot: the next unused one (a cell that needs more goes to the
     // one-cell pass, which reuses the slots of faces cut away).
-    const unsigned p = RANKS && lane_on(cubew) ? (unsigned)(k - 1) : (unsigned)C.np;
-    const unsigned long long fullw = __ballot(p >= (unsigned)kPlanesP) & cutw;
-    failp |= fullw;
-    donew |= fullw;
-    const unsigned long long gow = cutw & ~fullw;
-    if (lane_on(gow)) C.np = RANKS ? max(C.np, (int)p + 1) : (int)p + 1;
+    const unsigned p = RANKS && lane_on(cubew) ? (unsigned)k : (unsigned)C.np;
+    if (lane_on(cutw)) C.np = RANKS ? max(C.np, (int)p + 1) : (int)p + 1;
     // The half's kept vertices as a set over its 64 slots (bit v: slot v,
     // the first register's 32 slots, then the second's).
     const unsigned long long K =
@@ -1955,47 +1973,44 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned l
       return (int)((m0 & 1u) | ((m1 & 1u) << 1) | ((m2 & 1u) << 2));
     };
     int bm0 = 0, bm1 = 0;
-    if (lane_on(gow & M0w)) bm0 = boundary(C.t0);
-    if (lane_on(gow & M1w)) bm1 = boundary(C.t1);
+    if (lane_on(M0w)) bm0 = boundary(C.t0);
+    if (lane_on(M1w)) bm1 = boundary(C.t1);
     const int nb = __popc(bm0) + __popc(bm1);
     const int incl = half_incl_scan(nb);
     const int pre = incl - nb;
-    // Boundary edges of each half, and its free slots after the cut.
+    // Boundary edges of each half, and its free slots after the cut: the
+    // second register's count only in a half with more boundary edges than
+    // free slots in the first.
     const int B0 = __builtin_amdgcn_readlane(incl, 31), B1 = __builtin_amdgcn_readlane(incl, 63);
     const unsigned long long F0w = ~C.L0w | M0w, F1w = ~C.L1w | M1w;
-    const int nfree0 = __popc((unsigned)F0w) + __popc((unsigned)F1w);
-    const int nfree1 = __popc((unsigned)(F0w >> 32)) + __popc((unsigned)(F1w >> 32));
-    const unsigned long long roomw = (B0 <= nfree0 ? LO : 0ull) | (B1 <= nfree1 ? HI : 0ull);
-    failv |= gow & ~roomw;
-    donew |= gow & ~roomw;
-    const unsigned long long doitw = gow & roomw;
+    const int f0 = __popc((unsigned)F0w), f1 = __popc((unsigned)(F0w >> 32));
+    const unsigned long long spillw = halves(B0 > f0, B1 > f1) & cutw;
+    unsigned long long badw = __ballot(p >= (unsigned)kPlanesP) & cutw;
+    if (spillw)
+      badw |= halves(B0 > f0 + __popc((unsigned)F1w), B1 > f1 + __popc((unsigned)(F1w >> 32))) & cutw;
+    failw |= badw;
+    const unsigned long long doitw = cutw & ~badw;
     if (lane_on(doitw) && hl == 0) {
       S.pl[p] = make_double4(q.x, q.y, q.z, h);
       // (the slot's byte offset is taken opaque: derived from the plane
       // row's address the compiler forms it with a 64-bit multiply-add)
       unsigned p4 = p << 2;
       asm volatile("" : "+v"(p4));
-      *(int32_t*)((char*)S.pcand + p4) = S.cjk[k - 1];
+      *(int32_t*)((char*)S.pcand + p4) = S.cjk[k];
     }
     // Each removed vertex lists its boundary edges from position pre, the
     // first register's, then the second's (only when a removed vertex
-    // lies there).
-    if (lane_on(doitw & M0w)) {
-      int e = pre;
-      const int ta0 = C.t0 & 255, tb0 = (C.t0 >> 8) & 255, tc0 = (C.t0 >> 16) & 255;
-      if (bm0 & 1) S.elist[e++] = (uint16_t)(ta0 | (tb0 << 8));
-      if (bm0 & 2) S.elist[e++] = (uint16_t)(tb0 | (tc0 << 8));
-      if (bm0 & 4) S.elist[e++] = (uint16_t)(tc0 | (ta0 << 8));
-    }
-    if (doitw & M1w) {
-      if (lane_on(doitw & M1w)) {
-        int e = pre + __popc(bm0);
-        const int ta1 = C.t1 & 255, tb1 = (C.t1 >> 8) & 255, tc1 = (C.t1 >> 16) & 255;
-        if (bm1 & 1) S.elist[e++] = (uint16_t)(ta1 | (tb1 << 8));
-        if (bm1 & 2) S.elist[e++] = (uint16_t)(tb1 | (tc1 << 8));
-        if (bm1 & 4) S.elist[e++] = (uint16_t)(tc1 | (ta1 << 8));
-      }
-    }
+    // lies there).  Every edge is written, one that is not on the boundary to
+    // a spare place: cheaper than a branch around each.
+    auto list_edges = [&](uint32_t T, int bm, int e) {
+      S.elist[(bm & 1) ? e : kVertsP] = (uint16_t)T;
+      e += bm & 1;
+      S.elist[(bm & 2) ? e : kVertsP] = (uint16_t)(T >> 8);
+      e += (bm >> 1) & 1;
+      S.elist[(bm & 4) ? e : kVertsP] = (uint16_t)((T >> 16) | (T << 8));
+    };
+    if (lane_on(doitw & M0w)) list_edges(C.t0, bm0, pre);
+    if (lane_on(doitw & M1w)) list_edges(C.t1, bm1, pre + __popc(bm0));
     wave_sync();   // every E lookup above is done before any write below
 
     // Boundary edge r goes to the free slot of rank r (the first register's
@@ -2007,8 +2022,6 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned l
     const int r0 = __popc(F0 & hbelow());
     const int B = (__lane_id() & 32) ? B1 : B0;
     const unsigned long long new0w = __ballot(r0 < B) & F0w & doitw;
-    const unsigned long long spillw = (B0 > __popc((unsigned)F0w) ? LO : 0ull) |
-                                      (B1 > __popc((unsigned)(F0w >> 32)) ? HI : 0ull);
     unsigned long long new1w = 0ull;
     int r1 = 0;
     if (doitw & spillw) {
@@ -2036,28 +2049,13 @@ __device__ int clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned l
     wave_sync();
     C.L0w = (C.L0w & ~(M0w & doitw)) | new0w;
     C.L1w = (C.L1w & ~(M1w & doitw)) | new1w;
-    donew |= __ballot(k >= nc);
-    // The bound is refreshed every fourth cut of a half.
+    donew |= __ballot(k >= last) | badw;
+    // The bounds are refreshed every fourth cut.
     stalew |= doitw;
-    if (doitw & LO) ++since0;
-    if (doitw & HI) ++since1;
-    const unsigned long long refw = (since0 == 4 ? LO : 0ull) | (since1 == 4 ? HI : 0ull);
-    if (refw) {
-      const double nb2 = farthest_bound_pair(C);
-      if (lane_on(refw)) {
-        C.rmax2 = nb2;
-        lim = 2.0 * nb2;
-      }
-      stalew &= ~refw;
-      if (refw & LO) since0 = 0;
-      if (refw & HI) since1 = 0;
-    }
+    if (++since == 4) bounds();
   }
-  if (stalew) {
-    const double nb = farthest_bound_pair(C);
-    if (lane_on(stalew)) C.rmax2 = nb;
-  }
-  return lane_on(failp) ? F_PLANES : lane_on(failv) ? F_VERTS : 0;
+  if (stalew) bounds();
+  return lane_on(failw);
 }
 
 // Faces, volume and centroid of each half's finished cell (as finish_cell;
