@@ -586,8 +586,8 @@ __device__ int gather_runs(TessLds& S, const TessArgs& A, const GridParams& g, c
   return nc;
 }
 
-// The lean passes' gather: images with lo2 <= |d|^2 < hi2 from the stencil of
-// half-width `ring`, by rows of buckets along x, for G lanes per cell (a
+// The lean passes' gather: images with lo2 <= |d|^2 < hi2 from a window of
+// buckets, by rows of buckets along x, for G lanes per cell (a
 // wavefront, or a half of one: G = 64 or 32).  Along a row the buckets of one
 // tile are consecutive in the cell order, so a row of the window is one run
 // of points, or two where the window crosses the end of a tile or of the box
@@ -615,9 +615,26 @@ __device__ inline RowRun row_run(int t, int left, int nb) {
   return R;
 }
 
-template <int G, int CAP, typename LDS>
+// The window of buckets that a gather takes about the generator's bucket: along
+// axis a from `below(a)` buckets below it, `width(a)` buckets.  Either the same
+// on every side, or of at most kPackRing buckets a side, packed into one
+// register.
+struct RingWindow {
+  int ring;
+  __device__ int below(int) const { return ring; }
+  __device__ int width(int) const { return 2 * ring + 1; }
+};
+constexpr int kPackRing = 15;
+struct PackedWindow {
+  unsigned w = 0;
+  __device__ void set(int a, int below, int above) { w |= (unsigned)(below | (below + above + 1) << 4) << (9 * a); }
+  __device__ int below(int a) const { return (int)(w >> (9 * a)) & 15; }
+  __device__ int width(int a) const { return (int)(w >> (9 * a + 4)) & 31; }
+};
+
+template <int G, int CAP, typename LDS, typename Window>
 __device__ int gather_rows(LDS& S, const TessArgs& A, const GridParams& g, bool act, const int s, const double r[3],
-                           const int b[3], const int ring, const double lo2, const double hi2) {
+                           const int b[3], const Window window, const double lo2, const double hi2) {
   const int gl = __lane_id() & (G - 1);
   // This group's bits of a wavefront mask, as a count and a count below.
   auto count = [&](unsigned long long m) {
@@ -628,7 +645,7 @@ __device__ int gather_rows(LDS& S, const TessArgs& A, const GridParams& g, bool 
     if constexpr (G == 64) return __popcll(m & lanes_below());
     else return __popc((unsigned)(m >> (__lane_id() & 32)) & ((1u << gl) - 1u));
   };
-  const int W = 2 * ring + 1, rows = act ? W * W : 0;
+  const int W = window.width(1), rows = act ? W * window.width(2) : 0;
   const WidthDiv D = width_div((unsigned)W);
   const int rows_max = (int)wave_umax32((unsigned)rows);
   int nc = 0;
@@ -637,7 +654,7 @@ __device__ int gather_rows(LDS& S, const TessArgs& A, const GridParams& g, bool 
     const int o = r0 + gl;
     const bool have = o < rows;
     const int q = have ? (int)div_width((unsigned)o, D) : 0;
-    const int ty = b[1] + (have ? o - q * W - ring : 0), tz = b[2] + (have ? q - ring : 0);
+    const int ty = b[1] + (have ? o - q * W - window.below(1) : 0), tz = b[2] + (have ? q - window.below(2) : 0);
     const int ky = ty < 0 ? -1 : (ty >= g.nb[1] ? 1 : 0), kz = tz < 0 ? -1 : (tz >= g.nb[2] ? 1 : 0);
     const int y = ty - ky * g.nb[1], z = tz - kz * g.nb[2];
     // The row's part of bucket_key, which stays the same along x.
@@ -647,8 +664,8 @@ __device__ int gather_rows(LDS& S, const TessArgs& A, const GridParams& g, bool 
     const int slab = ey * ez, line = (y - y0) + ey * (z - z0);
     const double sy = ky * g.L[1], sz = kz * g.L[2];
     const int code_yz = 3 * (ky + 1) + 9 * (kz + 1);
-    int t = b[0] - ring;
-    const int t_end = act ? b[0] + ring + 1 : t;
+    int t = b[0] - window.below(0);
+    const int t_end = act ? t + window.width(0) : t;
     while (__ballot(t < t_end)) {
       const int left = t_end - t;
       const RowRun R0 = row_run(t, left, g.nb[0]);
@@ -1185,7 +1202,7 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
   }
   // The first passes' gather: by rows, or two-level near dense regions.
   auto gather_first = [&](int ring, double lo2, double hi2) {
-    if constexpr (MODE == 0) return gather_rows<64, kCands>(S, A, g, true, s, r, b, ring, lo2, hi2);
+    if constexpr (MODE == 0) return gather_rows<64, kCands>(S, A, g, true, s, r, b, RingWindow{ring}, lo2, hi2);
     else return gather(S, A, g, s, r, b, ring, lo2, hi2);
   };
   if (MODE < 2) {
@@ -1550,6 +1567,52 @@ __device__ inline double farthest_bound_pair(const PairRegs& C) {
   return half_max_bound(m2);
 }
 
+// Half-width of the box about a query sphere, a little outward.
+__device__ inline double query_radius(const GridParams& g, const double hi2) {
+  return sqrt(hi2) * (1.0 + 1e-9) + 1e-9 * fmin(g.hb[0], fmin(g.hb[1], g.hb[2]));
+}
+
+// Where a point that still cuts each half's cell may lie, about its generator:
+// a point x cuts a vertex v only from inside the sphere about v through the
+// generator, and for the vertices within half the radius already gathered
+// (4 v^2 <= lo2) every such point has been seen.  The box around the spheres of
+// the others, as distances below (lo) and above (hi) the generator in units of
+// the query radius rq, at most one.  Single precision, rounded outward.
+// After its first radius an irregular cell needs a few farther points at most,
+// near its two or three farthest vertices: a quarter or so of the shell's
+// volume.  With whole shells the dense pass took 27.4 ms instead of 25.7 on two
+// polytropes of 4,000,000 points and handed on cells whose shells overflowed
+// their candidate slots (the one-cell dense pass 6.9 ms instead of 3.7), and the
+// lean pass 2.14 ms instead of 1.87 on 300,001 random points.
+struct FarBox {
+  float lo[3], hi[3];
+};
+__device__ inline FarBox far_box(const PairRegs& C, const double lo2, const double rq) {
+  const double iq = rcp_nr(rq);
+  FarBox F;
+  float lo[3] = {0.f, 0.f, 0.f}, hi[3] = {0.f, 0.f, 0.f};
+  auto add = [&](bool live, double x, double y, double z) {
+    const double m2 = x * x + y * y + z * z;
+    if (live && 4.0 * m2 * (1.0 + 1e-9) >= lo2) {
+      const float v[3] = {(float)(x * iq), (float)(y * iq), (float)(z * iq)};
+      const float rad = sqrtf((float)(m2 * iq * iq)) * (1.f + 4e-6f);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        hi[a] = fmaxf(hi[a], rad + v[a]);
+        lo[a] = fmaxf(lo[a], rad - v[a]);
+      }
+    }
+  };
+  add(lane_on(C.L0w), C.v0x, C.v0y, C.v0z);
+  add(lane_on(C.L1w), C.v1x, C.v1y, C.v1z);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    F.hi[a] = fminf(__uint_as_float(half_umax32(__float_as_uint(hi[a]))), 1.f);
+    F.lo[a] = fminf(__uint_as_float(half_umax32(__float_as_uint(lo[a]))), 1.f);
+  }
+  return F;
+}
+
 // The dense pass's gather of both halves: images with lo2 <= |d|^2 < hi2 from
 // each half's stencil of half-width `ring`, one stencil bucket per lane at a
 // time (the stencils are small, and more buckets per lane spill registers:
@@ -1560,10 +1623,11 @@ __device__ inline double farthest_bound_pair(const PairRegs& C) {
 // (act: the half has a cell).
 __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams& g, const int s, const double r[3],
                                 const int b[3], const int ring, const int chunk, const int W3, const WidthDiv& D,
-                                const double lo2, const double hi2, int nc);
+                                const double lo2, const double hi2, const double rq, const FarBox& F, int nc);
 
 __device__ int gather_pair(PairLds& S, const TessArgs& A, const GridParams& g, bool act, const int s,
-                           const double r[3], const int b[3], const int ring, const double lo2, const double hi2) {
+                           const double r[3], const int b[3], const int ring, const double lo2, const double hi2,
+                           const double rq, const FarBox& F) {
   const int hl = hlane();
   const int W = 2 * ring + 1, W3 = act ? W * W * W : 0;
   const WidthDiv D = width_div((unsigned)W);
@@ -1572,7 +1636,7 @@ __device__ int gather_pair(PairLds& S, const TessArgs& A, const GridParams& g, b
   for (int chunk = 0; chunk < W3max; chunk += 32) {
     const StencilBucket B = stencil_bucket(A, g, b, ring, chunk + hl, W3, D);
     if (__ballot(B.cnt > kDense)) {
-      nc = gather_runs_pair(S, A, g, s, r, b, ring, chunk, W3, D, lo2, hi2, nc);
+      nc = gather_runs_pair(S, A, g, s, r, b, ring, chunk, W3, D, lo2, hi2, rq, F, nc);
       continue;
     }
     const int maxc = (int)wave_umax32((unsigned)B.cnt);
@@ -1610,12 +1674,14 @@ __device__ int gather_pair(PairLds& S, const TessArgs& A, const GridParams& g, b
 // inside the box; each half takes its runs 32 at a time, a lane finding the
 // bucket of its run by a binary search over the half's run prefix sums.
 // The per-point test is the plain path's, so the candidates are the same.
+// A lane reads two points of its run at a time (one at a time: 27.4 ms instead
+// of 26.4 for the polytropes' dense pass; three as fast, four 26.6).
+constexpr int kRunPoints = 2;
 __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams& g, const int s, const double r[3],
                                 const int b[3], const int ring, const int chunk, const int W3, const WidthDiv& D,
-                                const double lo2, const double hi2, int nc) {
+                                const double lo2, const double hi2, const double rq, const FarBox& F, int nc) {
   const int hl = hlane();
   const int h0 = __lane_id() & 32;   // first lane of this half
-  const double rq = sqrt(hi2) * (1.0 + 1e-9) + 1e-9 * fmin(g.hb[0], fmin(g.hb[1], g.hb[2]));
   {
     int bb[3] = {0, 0, 0};
     int64_t key = 0;
@@ -1627,8 +1693,8 @@ __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams&
       bool meet = true;
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        qlo[a] = (r[a] - rq) - sh[a];
-        qhi[a] = (r[a] + rq) - sh[a];
+        qlo[a] = (r[a] - rq * (double)F.lo[a]) - sh[a];
+        qhi[a] = (r[a] + rq * (double)F.hi[a]) - sh[a];
         const double tlo = qlo[a] * g.inv_hb[a], thi = qhi[a] * g.inv_hb[a];
         if (thi < (double)bb[a] || (tlo >= (double)(bb[a] + 1) && bb[a] < g.nb[a] - 1)) meet = false;
       }
@@ -1682,27 +1748,37 @@ __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams&
         count = a1 - a0;
       }
       const int maxc = (int)wave_umax32((unsigned)count);
-      for (int k = 0; k < maxc; ++k) {
-        const int j = start + k;
-        const bool v = k < count && j != s;
-        double x = 0, y = 0, z = 0;
-        if (v) {
-          x = A.spos[3 * (int64_t)j];
-          y = A.spos[3 * (int64_t)j + 1];
-          z = A.spos[3 * (int64_t)j + 2];
-        }
-        const double dx = (x + sx) - r[0], dy = (y + sy) - r[1], dz = (z + sz) - r[2];
-        const double d2 = dx * dx + dy * dy + dz * dz;
-        const bool keep = v && d2 >= lo2 && d2 < hi2;
-        const unsigned mk = hbits(__ballot(keep));
-        if (keep) {
-          const int idx = nc + __popc(mk & hbelow());
-          if (idx < kCandsP) {
-            S.cd[idx] = make_double4(dx, dy, dz, 0.5 * d2);
-            S.cjk[idx] = (j << 5) | code_o;
+      for (int k0 = 0; k0 < maxc; k0 += kRunPoints) {
+        double dx[kRunPoints], dy[kRunPoints], dz[kRunPoints], d2[kRunPoints];
+        bool keep[kRunPoints];
+#pragma unroll
+        for (int u = 0; u < kRunPoints; ++u) {
+          const int j = start + k0 + u;
+          const bool v = k0 + u < count && j != s;
+          double x = 0, y = 0, z = 0;
+          if (v) {
+            x = A.spos[3 * (int64_t)j];
+            y = A.spos[3 * (int64_t)j + 1];
+            z = A.spos[3 * (int64_t)j + 2];
           }
+          dx[u] = (x + sx) - r[0];
+          dy[u] = (y + sy) - r[1];
+          dz[u] = (z + sz) - r[2];
+          d2[u] = dx[u] * dx[u] + dy[u] * dy[u] + dz[u] * dz[u];
+          keep[u] = v && d2[u] >= lo2 && d2[u] < hi2;
         }
-        nc += __popc(mk);
+#pragma unroll
+        for (int u = 0; u < kRunPoints; ++u) {
+          const unsigned mk = hbits(__ballot(keep[u]));
+          if (keep[u]) {
+            const int idx = nc + __popc(mk & hbelow());
+            if (idx < kCandsP) {
+              S.cd[idx] = make_double4(dx[u], dy[u], dz[u], 0.5 * d2[u]);
+              S.cjk[idx] = ((start + k0 + u) << 5) | code_o;
+            }
+          }
+          nc += __popc(mk);
+        }
       }
     }
   }
@@ -2207,14 +2283,6 @@ __device__ inline void redo_cell(const TessArgs& A, int s) {
   A.redo[atomicAdd(DENSE ? &A.st->n_dredo : &A.st->n_redo, 1)] = s;
 }
 
-template <bool DENSE>
-__device__ __forceinline__ int gather_half(PairLds& S, const TessArgs& A, const GridParams& g, bool act, const int s,
-                                           const double r[3], const int b[3], const int ring, const double lo2,
-                                           const double hi2) {
-  if constexpr (DENSE) return gather_pair(S, A, g, act, s, r, b, ring, lo2, hi2);
-  else return gather_rows<32, kCandsP>(S, A, g, act, s, r, b, ring, lo2, hi2);
-}
-
 // One cell per half of the wavefront (act: the half has a cell, s).
 // DENSE = false: the lean first pass over every cell; cells of dense
 // buckets are left to the dense passes (listed by the sort), and a cell
@@ -2273,6 +2341,9 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
   // in this pass (the polytropes' background 1.5 times the one-cell pass's
   // time).
   bool work = act;
+  PackedWindow window;   // (lean pass)
+#pragma unroll
+  for (int a = 0; a < 3; ++a) window.set(a, ring, ring);
   for (int shell = 0;; ++shell) {
     int s1 = s;
     if constexpr (!DENSE) asm volatile("" : "+v"(s1));
@@ -2280,7 +2351,18 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
     CellGeom fresh;
     if constexpr (!DENSE) cell_geom(A, g1, s1, fresh);
     const CellGeom& G1 = DENSE ? G : fresh;
-    int nc = gather_half<DENSE>(S, A, g1, work, s1, G1.r, G1.b, ring, lo2, hi2);
+    // The images of this round for the halves in `on`.
+    auto gather_half = [&](bool on) {
+      if constexpr (DENSE) {
+        const double rq = query_radius(g1, hi2);
+        FarBox F{{1.f, 1.f, 1.f}, {1.f, 1.f, 1.f}};
+        if (shell > 0) F = far_box(C, lo2, rq);
+        return gather_pair(S, A, g1, on, s1, G1.r, G1.b, ring, lo2, hi2, rq, F);
+      } else {
+        return gather_rows<32, kCandsP>(S, A, g1, on, s1, G1.r, G1.b, window, lo2, hi2);
+      }
+    };
+    int nc = gather_half(work);
     if (!DENSE && work && nc < 0) {
       if (hl == 0) A.dcells[atomicAdd(&A.st->n_dense_cells, 1)] = s;
       act = work = false;
@@ -2294,7 +2376,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
     const bool over = work && nc > kCandsP && (!DENSE || shell == 0);
     if (__ballot(over)) {
       if (over) hi2 = shell_for(lo2, hi2, nc, 38.0);
-      const int nc2 = gather_half<DENSE>(S, A, g1, over, s1, G1.r, G1.b, ring, lo2, hi2);
+      const int nc2 = gather_half(over);
       if (over) nc = nc2;
     }
     // Too many candidates, or (lean pass, first radius) few: a thin region,
@@ -2316,21 +2398,34 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
     }
     bool go = work && !(4.0 * C.rmax2 <= hi2 * (1.0 - 1e-12));
     if (__ballot(go) == 0ull) break;
-    if (go) {
+    {
       int s3 = s;
       if constexpr (!DENSE) asm volatile("" : "+v"(s3));
       const GridParams& g3 = DENSE ? g : (ONE ? A.g1 : A.segs[A.sseg[s3]].g);
       CellGeom fresh3;
       if constexpr (!DENSE) cell_geom(A, g3, s3, fresh3);
       const CellGeom& G3 = DENSE ? G : fresh3;
-      const double nhi2 = next_shell(C.rmax2, lo2, hi2, nc, 38.0);
-      ring = ring_for(g3, G3.edge, nhi2);
-      if (shell == kShells1 || ring > g.nb[0] || ring > g.nb[1] || ring > g.nb[2]) {
-        if (hl == 0) redo_cell<DENSE>(A, s);
-        act = go = false;
-      } else {
-        lo2 = hi2;
-        hi2 = nhi2;
+      if (go) {
+        const double nhi2 = next_shell(C.rmax2, lo2, hi2, nc, 38.0);
+        ring = ring_for(g3, G3.edge, nhi2);
+        if (shell == kShells1 || (!DENSE && ring > kPackRing) || ring > g.nb[0] || ring > g.nb[1] || ring > g.nb[2]) {
+          if (hl == 0) redo_cell<DENSE>(A, s);
+          act = go = false;
+        } else {
+          lo2 = hi2;
+          hi2 = nhi2;
+        }
+      }
+      if constexpr (!DENSE) {
+        const double rq = query_radius(g3, hi2);
+        const FarBox F = far_box(C, lo2, rq);
+        window = PackedWindow();
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const double t = G3.r[a] - G3.b[a] * g3.hb[a];
+          window.set(a, max(0, min(ring, -(int)floor((t - rq * (double)F.lo[a]) * g3.inv_hb[a]))),
+                     max(0, min(ring, (int)floor((t + rq * (double)F.hi[a]) * g3.inv_hb[a]))));
+        }
       }
     }
     work = go;

@@ -4,6 +4,7 @@ from __future__ import annotations
 
 import ctypes
 
+import numpy as np
 import pytest
 
 import workloads as W
@@ -76,3 +77,19 @@ def test_component_outputs_over_inputs(orc, precision):
         out = a[0] if over is U else a[1]
         mm._check(mm.lib.mm_predict(mm.ctx, dptr(a[0]), dptr(a[1]), dptr(w), float(dt), dptr(out)))
         assert torch.equal(out.view(-1)[:5 * n].view(n, 5), Uh)
+
+
+# Cells that go on after their first radius take only the points near their
+# farthest vertices: irregular points in few buckets a side, in a long box, and
+# a cluster of dense buckets on a thin background.
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,box,cluster", [(130, (1.0, 1.0, 1.0), 0), (700, (3.0, 1.0, 1.0), 0),
+                                           (2500, (1.0, 1.5, 1.0), 0), (2400, (1.0, 1.0, 1.0), 1400)])
+def test_shells_after_the_first(orc, n, box, cluster, precision):
+    pos = W.poisson_points(n, box, seed=17 + n)
+    if cluster:
+        rng = np.random.default_rng(n)
+        pos[:cluster] = 0.5 + 0.03 * rng.standard_normal((cluster, 3)).clip(-4, 4)
+    mm, info, om = mesh_pair(orc, pos, box, precision=precision)
+    assert om.status == 0 and om.delta_min > 1e-12
+    compare_mesh(mm, om, ftol=1e-9)
