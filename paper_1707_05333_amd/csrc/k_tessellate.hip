@@ -616,13 +616,18 @@ __device__ inline RowRun row_run(int t, int left, int nb) {
 }
 
 // The window of buckets that a gather takes about the generator's bucket: along
-// axis a from `below(a)` buckets below it, `width(a)` buckets.  Either the same
-// on every side, or of at most kPackRing buckets a side, packed into one
-// register.
+// axis a from `below(a)` buckets below it, `width(a)` buckets.  The same on
+// every side, side by side, or of at most kPackRing buckets a side, packed into
+// one register.
 struct RingWindow {
   int ring;
   __device__ int below(int) const { return ring; }
   __device__ int width(int) const { return 2 * ring + 1; }
+};
+struct SideWindow {
+  int lo[3], hi[3];
+  __device__ int below(int a) const { return lo[a]; }
+  __device__ int width(int a) const { return lo[a] + hi[a] + 1; }
 };
 constexpr int kPackRing = 15;
 struct PackedWindow {
@@ -1157,6 +1162,55 @@ __device__ inline double next_shell(double rmax2, double lo2, double hi2, int nc
   return n2;
 }
 
+// Half-width of the box about a query sphere, a little outward.
+__device__ inline double query_radius(const GridParams& g, const double hi2) {
+  return sqrt(hi2) * (1.0 + 1e-9) + 1e-9 * fmin(g.hb[0], fmin(g.hb[1], g.hb[2]));
+}
+
+// Where a point that still cuts each half's cell may lie, about its generator:
+// a point x cuts a vertex v only from inside the sphere about v through the
+// generator, and for the vertices within half the radius already gathered
+// (4 v^2 <= lo2) every such point has been seen.  The box around the spheres of
+// the others, as distances below (lo) and above (hi) the generator in units of
+// the query radius rq, at most one.  Single precision, rounded outward.
+// After its first radius an irregular cell needs a few farther points at most,
+// near its two or three farthest vertices: a quarter or so of the shell's
+// volume.  With whole shells the dense pass took 27.4 ms instead of 25.7 on two
+// polytropes of 4,000,000 points and handed on cells whose shells overflowed
+// their candidate slots (the one-cell dense pass 6.9 ms instead of 3.7), and the
+// lean pass 2.14 ms instead of 1.87 on 300,001 random points; the one-cell lean
+// pass takes it too (the polytropes' 5.14 -> 4.68 ms).
+struct FarBox {
+  float lo[3], hi[3];
+};
+template <typename Regs, typename Max>
+__device__ inline FarBox far_box(const Regs& C, const unsigned long long live0, const unsigned long long live1,
+                                 const double lo2, const double rq, Max max_of) {
+  const double iq = rcp_nr(rq);
+  FarBox F;
+  float lo[3] = {0.f, 0.f, 0.f}, hi[3] = {0.f, 0.f, 0.f};
+  auto add = [&](bool live, double x, double y, double z) {
+    const double m2 = x * x + y * y + z * z;
+    if (live && 4.0 * m2 * (1.0 + 1e-9) >= lo2) {
+      const float v[3] = {(float)(x * iq), (float)(y * iq), (float)(z * iq)};
+      const float rad = sqrtf((float)(m2 * iq * iq)) * (1.f + 4e-6f);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        hi[a] = fmaxf(hi[a], rad + v[a]);
+        lo[a] = fmaxf(lo[a], rad - v[a]);
+      }
+    }
+  };
+  add(lane_on(live0), C.v0x, C.v0y, C.v0z);
+  add(lane_on(live1), C.v1x, C.v1y, C.v1z);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    F.hi[a] = fminf(__uint_as_float(max_of(__float_as_uint(hi[a]))), 1.f);
+    F.lo[a] = fminf(__uint_as_float(max_of(__float_as_uint(lo[a]))), 1.f);
+  }
+  return F;
+}
+
 // Builds the cell of internal generator s.
 // MODE 0 (first pass of the cells the two-cell pass hands on): candidates
 //   within the grid's filter radius; a cell whose candidates do not cover
@@ -1263,7 +1317,23 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
       }
       lo2 = hi2;
       hi2 = nhi2;
-      int nc2 = gather_first( nring, lo2, hi2);
+      auto gather_shell = [&]() {
+        if constexpr (MODE == 0) {
+          const double rq = query_radius(g, hi2);
+          const FarBox F = far_box(C, C.L0, C.L1, lo2, rq, wave_umax32);
+          SideWindow window;
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            const double t = r[a] - b[a] * g.hb[a];
+            window.lo[a] = max(0, min(nring, -uniform_i32((int)floor((t - rq * (double)F.lo[a]) * g.inv_hb[a]))));
+            window.hi[a] = max(0, min(nring, uniform_i32((int)floor((t + rq * (double)F.hi[a]) * g.inv_hb[a]))));
+          }
+          return gather_rows<64, kCands>(S, A, g, true, s, r, b, window, lo2, hi2);
+        } else {
+          return gather_first(nring, lo2, hi2);
+        }
+      };
+      int nc2 = gather_shell();
       if (nc2 < 0) {
         return kToDense;
       }
@@ -1271,7 +1341,7 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
       // the shell pass; the next shell goes on from there.
       for (int t = 0; nc2 > kCands && t < 2; ++t) {
         hi2 = lo2 + 0.5 * (hi2 - lo2);
-        nc2 = gather_first( nring, lo2, hi2);
+        nc2 = gather_shell();
       }
       if (nc2 > kCands) {
         rm2 = C.rmax2;
@@ -1565,52 +1635,6 @@ __device__ inline double farthest_bound_pair(const PairRegs& C) {
   if (lane_on(C.L0w)) m2 = ax * ax + ay * ay + az * az;
   if (lane_on(C.L1w)) m2 = fmax(m2, bx * bx + by * by + bz * bz);
   return half_max_bound(m2);
-}
-
-// Half-width of the box about a query sphere, a little outward.
-__device__ inline double query_radius(const GridParams& g, const double hi2) {
-  return sqrt(hi2) * (1.0 + 1e-9) + 1e-9 * fmin(g.hb[0], fmin(g.hb[1], g.hb[2]));
-}
-
-// Where a point that still cuts each half's cell may lie, about its generator:
-// a point x cuts a vertex v only from inside the sphere about v through the
-// generator, and for the vertices within half the radius already gathered
-// (4 v^2 <= lo2) every such point has been seen.  The box around the spheres of
-// the others, as distances below (lo) and above (hi) the generator in units of
-// the query radius rq, at most one.  Single precision, rounded outward.
-// After its first radius an irregular cell needs a few farther points at most,
-// near its two or three farthest vertices: a quarter or so of the shell's
-// volume.  With whole shells the dense pass took 27.4 ms instead of 25.7 on two
-// polytropes of 4,000,000 points and handed on cells whose shells overflowed
-// their candidate slots (the one-cell dense pass 6.9 ms instead of 3.7), and the
-// lean pass 2.14 ms instead of 1.87 on 300,001 random points.
-struct FarBox {
-  float lo[3], hi[3];
-};
-__device__ inline FarBox far_box(const PairRegs& C, const double lo2, const double rq) {
-  const double iq = rcp_nr(rq);
-  FarBox F;
-  float lo[3] = {0.f, 0.f, 0.f}, hi[3] = {0.f, 0.f, 0.f};
-  auto add = [&](bool live, double x, double y, double z) {
-    const double m2 = x * x + y * y + z * z;
-    if (live && 4.0 * m2 * (1.0 + 1e-9) >= lo2) {
-      const float v[3] = {(float)(x * iq), (float)(y * iq), (float)(z * iq)};
-      const float rad = sqrtf((float)(m2 * iq * iq)) * (1.f + 4e-6f);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        hi[a] = fmaxf(hi[a], rad + v[a]);
-        lo[a] = fmaxf(lo[a], rad - v[a]);
-      }
-    }
-  };
-  add(lane_on(C.L0w), C.v0x, C.v0y, C.v0z);
-  add(lane_on(C.L1w), C.v1x, C.v1y, C.v1z);
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    F.hi[a] = fminf(__uint_as_float(half_umax32(__float_as_uint(hi[a]))), 1.f);
-    F.lo[a] = fminf(__uint_as_float(half_umax32(__float_as_uint(lo[a]))), 1.f);
-  }
-  return F;
 }
 
 // The dense pass's gather of both halves: images with lo2 <= |d|^2 < hi2 from
@@ -2356,7 +2380,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
       if constexpr (DENSE) {
         const double rq = query_radius(g1, hi2);
         FarBox F{{1.f, 1.f, 1.f}, {1.f, 1.f, 1.f}};
-        if (shell > 0) F = far_box(C, lo2, rq);
+        if (shell > 0) F = far_box(C, C.L0w, C.L1w, lo2, rq, half_umax32);
         return gather_pair(S, A, g1, on, s1, G1.r, G1.b, ring, lo2, hi2, rq, F);
       } else {
         return gather_rows<32, kCandsP>(S, A, g1, on, s1, G1.r, G1.b, window, lo2, hi2);
@@ -2418,7 +2442,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
       }
       if constexpr (!DENSE) {
         const double rq = query_radius(g3, hi2);
-        const FarBox F = far_box(C, lo2, rq);
+        const FarBox F = far_box(C, C.L0w, C.L1w, lo2, rq, half_umax32);
         window = PackedWindow();
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
