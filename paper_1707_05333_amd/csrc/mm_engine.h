@@ -30,6 +30,15 @@ GridParams make_grid(const mm_params& p, int64_t n, double rfac, int64_t base);
 HydroParams hydro_params(const mm_params& p);
 bool params_ok(const mm_params* p, std::string& why);
 
+// Host mirror of an arena's status, laid out as the arena holds it (its buffers
+// start on multiples of kArenaAlign, the launch set's status behind that of the
+// one segment), so that one copy fills both.
+constexpr size_t kArenaAlign = 256;
+struct ArenaStatus {
+  alignas(kArenaAlign) SegStatus seg;
+  alignas(kArenaAlign) DevStatus set;
+};
+
 struct Engine {
   int precision = MM_FP64;
   int64_t ncap = 0, slot_cap = 0, fcap = 0, nbcap = 0, sell_cap = 0;
@@ -103,7 +112,7 @@ struct Engine {
   // status mirrors: nothing is allocated, and no events exist (no stage
   // timing).  MM_ECAPACITY when they do not fit.
   mm_status init_arena(int precision, int64_t ncap, int64_t fcap, void* arena, size_t bytes, SegDesc* seg_host,
-                       SegStatus* seg_status_host, DevStatus* status_host, hipStream_t stream);
+                       ArenaStatus* status_host, hipStream_t stream);
   // Bytes init_arena needs (its alignment included).
   static size_t arena_bytes(int precision, int64_t ncap, int64_t fcap);
   void set_capacity(int precision, int64_t ncap, int64_t slot_cap, int64_t fcap, int segcap);

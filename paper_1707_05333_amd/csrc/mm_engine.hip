@@ -28,7 +28,7 @@ struct Reserver {
       ok &= hipMalloc(p, b) == hipSuccess;
       return;
     }
-    const size_t at = (used + 255) & ~size_t(255);
+    const size_t at = (used + kArenaAlign - 1) & ~(kArenaAlign - 1);
     used = at + b;
     if (!base || used > cap) {
       *p = nullptr;
@@ -216,7 +216,7 @@ size_t Engine::arena_bytes(int prec, int64_t n_cap, int64_t f_cap) {
 }
 
 mm_status Engine::init_arena(int prec, int64_t n_cap, int64_t f_cap, void* arena, size_t bytes, SegDesc* seg_host,
-                             SegStatus* seg_status_host, DevStatus* status_host, hipStream_t s) {
+                             ArenaStatus* status_host, hipStream_t s) {
   *this = Engine();
   set_capacity(prec, n_cap, n_cap, f_cap, 1);
   stream = s;
@@ -229,8 +229,10 @@ mm_status Engine::init_arena(int prec, int64_t n_cap, int64_t f_cap, void* arena
   reserve_buffers(*this, R, false);
   if (!R.ok || !arena) return fail(MM_ECAPACITY, "the buffers do not fit the arena");
   segs_host = seg_host;
-  segst_host = seg_status_host;
-  st_host = status_host;
+  segst_host = &status_host->seg;
+  st_host = &status_host->set;
+  if ((char*)st - (char*)segst != (char*)st_host - (char*)segst_host)
+    return fail(MM_EINVAL, "the status mirror does not match the arena's");
   return MM_OK;
 }
 
@@ -390,9 +392,10 @@ mm_status Engine::readback() {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(MM_EHIP, std::string("launch: ") + hipGetErrorString(e));
   if (arena_mode) {
-    e = hipMemcpyAsync(st_host, st, sizeof(DevStatus), hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess && nseg > 0)
-      e = hipMemcpyAsync(segst_host, segst, sizeof(SegStatus) * nseg, hipMemcpyDeviceToHost, stream);
+    // (both statuses in one copy: two took 163 us instead of 151 for a step of
+    // 1,000 points)
+    e = hipMemcpyAsync(segst_host, segst, sizeof(ArenaStatus::set) + ((char*)st - (char*)segst),
+                       hipMemcpyDeviceToHost, stream);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return fail(MM_EHIP, std::string("status readback: ") + hipGetErrorString(e));

@@ -397,8 +397,7 @@ std::mutex g_static_mu;
 void* g_scratch_dev[kMaxDevices];          // device address of scratch, per device (set once)
 mm_ctx g_static_ctx[kMaxDevices];          // one context per device, carved from its scratch
 SegDesc g_static_seg[kMaxDevices];         // host mirrors of the one segment and its status
-SegStatus g_static_segst[kMaxDevices];
-DevStatus g_static_st[kMaxDevices];
+ArenaStatus g_static_status[kMaxDevices];
 
 mm_status static_fail(mm_status code, const std::string& msg) {
   g_create_err = msg;
@@ -442,7 +441,7 @@ mm_status mm_step_static(const mm_params* p, int64_t n, double* pos, double* w, 
   c->p = *p;
   c->have_mesh = false;
   if (mm_status r = c->E.init_arena(p->precision, kStaticPoints, kStaticFaces, g_scratch_dev[dev], kScratchBytes,
-                                    &g_static_seg[dev], &g_static_segst[dev], &g_static_st[dev],
+                                    &g_static_seg[dev], &g_static_status[dev],
                                     (hipStream_t)hip_stream))
     return static_fail(r, c->E.err);
   const mm_status r = step_common(c, n, pos, w, Q, nullptr, nullptr, dt_max, info);
