@@ -1480,10 +1480,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
 // and 48 candidates, 5 KB of LDS per cell, so 32 cells fit a CU (twice the
 // one-cell pass): the usual cell of the uniform inputs (about 16 faces, 28
 // vertices, 29 candidates) fits with room to spare.  A cell that needs more
-// slots, more distance shells than its pass takes (one extra in the lean
-// pass, three in the dense one), or (lean pass) a thin region's wider first
-// radius is handed to the one-cell pass of its kind, which builds it as
-// before; a lean cell whose stencil holds a dense bucket is listed for the
+// slots, more than three extra distance shells, or (lean pass) a thin region's
+// wider first radius is handed to the one-cell pass of its kind, which builds
+// it as before; a lean cell whose stencil holds a dense bucket is listed for the
 // dense passes.  Values that are uniform per cell are uniform per half here:
 // held in each lane of the half, and the half's 32 bits of every ballot are
 // its masks (the cut loop keeps its per-half flags as wavefront masks and
