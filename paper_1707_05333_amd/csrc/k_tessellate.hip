@@ -1996,8 +1996,11 @@ __device__ unsigned long long cube_start(PairLds& S, const GridParams& g, const 
 // (per-half refresh counters, a branch around every listed edge, free slots
 // counted for every cut, 64-bit mask tests) the pass took 3.72 ms instead of
 // 3.42 on the Sod tube of 1,048,576 cells, 3.76 instead of 3.41 on a blast of
-// 884,736 and 1.62 instead of 1.49 on a Gresho vortex of 425,984.  Six vector
-// instructions less at the side of that chain changed nothing measurable.
+// 884,736 and 1.62 instead of 1.49 on a Gresho vortex of 425,984; some 20 more
+// (a lane of its own for the plane, masks for a spill that did not happen, the
+// halves' stale bounds) cost 3.46 instead of 3.40, 3.44 instead of 3.38 and 1.52
+// instead of 1.48.  Six vector instructions less at the side of that chain
+// changed nothing measurable.
 // cubew: the halves whose planes take the slot of their candidate's rank
 // (cube_start, only with RANKS); k: the half's first candidate.  Returns whether
 // this half's cell ran out of plane or vertex slots.
@@ -2009,7 +2012,6 @@ __device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned 
   // flag is a select on the mask, and the loop's control is scalar work apart
   // from the compares behind its ballots.
   unsigned long long donew = __ballot(k >= nc);   // halves that stopped
-  unsigned long long stalew = 0ull;               // rmax2 older than the last cut
   unsigned long long failw = 0ull;                // halves out of plane or vertex slots
   int since = 0;                                  // cuts since the last bounds
   double lim = 2.0 * C.rmax2;
@@ -2017,12 +2019,8 @@ __device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned 
   const int last = nc - 1;
   k = lane_on(donew) ? 0 : k - 1;                 // the candidate in q
   auto bounds = [&]() {
-    const double nb = farthest_bound_pair(C);
-    if (lane_on(stalew)) {
-      C.rmax2 = nb;
-      lim = 2.0 * nb;
-    }
-    stalew = 0ull;
+    C.rmax2 = farthest_bound_pair(C);   // (the same again for a half without a cut since)
+    lim = 2.0 * C.rmax2;
     since = 0;
   };
   for (;;) {
@@ -2037,8 +2035,10 @@ __device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned 
       // older than the last cut is refreshed and the test taken again.
       unsigned long long farw = __ballot(q.w >= lim) & seekw;
       if (farw) {
-        bounds();
-        farw &= __ballot(q.w >= lim);
+        if (since) {
+          bounds();
+          farw &= __ballot(q.w >= lim);
+        }
         donew |= farw;
         seekw &= ~farw;
       }
@@ -2049,9 +2049,7 @@ __device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned 
       M1w |= n1;
       cutw |= hitw;
       seekw &= ~hitw;
-      const unsigned long long endw = __ballot(k >= last) & seekw;
-      donew |= endw;
-      seekw &= ~endw;
+      seekw &= __ballot(k < last);   // (one out of candidates is done after the other's cut, below)
     }
     if (cutw == 0ull) break;
     const double h = q.w;
@@ -2083,20 +2081,12 @@ __device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned 
     const int B0 = __builtin_amdgcn_readlane(incl, 31), B1 = __builtin_amdgcn_readlane(incl, 63);
     const unsigned long long F0w = ~C.L0w | M0w, F1w = ~C.L1w | M1w;
     const int f0 = __popc((unsigned)F0w), f1 = __popc((unsigned)(F0w >> 32));
-    const unsigned long long spillw = halves(B0 > f0, B1 > f1) & cutw;
+    const bool spill = max(B0 - f0, B1 - f1) > 0;
     unsigned long long badw = __ballot(p >= (unsigned)kPlanesP) & cutw;
-    if (spillw)
-      badw |= halves(B0 > f0 + __popc((unsigned)F1w), B1 > f1 + __popc((unsigned)(F1w >> 32))) & cutw;
+    if (spill)
+      badw |= halves(B0 > f0 + __popc((unsigned)F1w), B1 > f1 + __popc((unsigned)(F1w >> 32)));
     failw |= badw;
     const unsigned long long doitw = cutw & ~badw;
-    if (lane_on(doitw) && hl == 0) {
-      S.pl[p] = make_double4(q.x, q.y, q.z, h);
-      // (the slot's byte offset is taken opaque: derived from the plane
-      // row's address the compiler forms it with a 64-bit multiply-add)
-      unsigned p4 = p << 2;
-      asm volatile("" : "+v"(p4));
-      *(int32_t*)((char*)S.pcand + p4) = S.cjk[k];
-    }
     // Each removed vertex lists its boundary edges from position pre, the
     // first register's, then the second's (only when a removed vertex
     // lies there).  Every edge is written, one that is not on the boundary to
@@ -2117,13 +2107,23 @@ __device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned 
     // The second register takes part only in a half with more boundary
     // edges than free slots in the first.
     const double4 qp = make_double4(q.x, q.y, q.z, h);
+    // The lanes that build vertices write the plane, all the same (a lane of
+    // its own would be one more branch).
+    auto put_plane = [&]() {
+      S.pl[p] = qp;
+      // (the slot's byte offset is taken opaque: derived from the plane
+      // row's address the compiler forms it with a 64-bit multiply-add)
+      unsigned p4 = p << 2;
+      asm volatile("" : "+v"(p4));
+      *(int32_t*)((char*)S.pcand + p4) = S.cjk[k];
+    };
     const unsigned F0 = hbits(F0w);
     const int r0 = __popc(F0 & hbelow());
     const int B = (__lane_id() & 32) ? B1 : B0;
     const unsigned long long new0w = __ballot(r0 < B) & F0w & doitw;
     unsigned long long new1w = 0ull;
     int r1 = 0;
-    if (doitw & spillw) {
+    if (spill) {
       r1 = __popc(F0) + __popc(hbits(F1w) & hbelow());
       new1w = __ballot(r1 < B) & F1w & doitw;
     }
@@ -2135,6 +2135,7 @@ __device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned 
       S.E[__umul24(x, kPlanesP) + y] = (uint8_t)hl;
       S.E[__umul24(y, kPlanesP) + p] = (uint8_t)hl;
       S.E[__umul24(p, kPlanesP) + x] = (uint8_t)hl;
+      put_plane();
     }
     if (lane_on(new1w)) {
       const unsigned xy = S.elist[r1];
@@ -2144,16 +2145,16 @@ __device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned 
       S.E[__umul24(x, kPlanesP) + y] = (uint8_t)(hl + 32);
       S.E[__umul24(y, kPlanesP) + p] = (uint8_t)(hl + 32);
       S.E[__umul24(p, kPlanesP) + x] = (uint8_t)(hl + 32);
+      put_plane();
     }
     wave_sync();
     C.L0w = (C.L0w & ~(M0w & doitw)) | new0w;
     C.L1w = (C.L1w & ~(M1w & doitw)) | new1w;
     donew |= __ballot(k >= last) | badw;
     // The bounds are refreshed every fourth cut.
-    stalew |= doitw;
     if (++since == 4) bounds();
   }
-  if (stalew) bounds();
+  if (since) bounds();
   return lane_on(failw);
 }
 
