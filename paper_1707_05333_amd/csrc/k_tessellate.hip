@@ -34,6 +34,21 @@ namespace mm {
 
 namespace {
 
+// The passes share their code, inlined into several kernels, and which of them
+// builds a cell may follow from what else the launch holds; the cell may not.
+// So no product here is fused into a sum by the compiler's choice (which
+// differs from one copy to the next): every fused multiply-add is written out.
+// With the choice left to it, |d|^2 came out in two roundings from the dense
+// pass's two gathers, of which a cell's neighbour in the wavefront decides.
+#pragma clang fp contract(off)
+
+__device__ __forceinline__ double dot3(double ax, double ay, double az, double bx, double by, double bz) {
+  return fma(az, bz, fma(ax, bx, ay * by));
+}
+__device__ __forceinline__ double norm2(double x, double y, double z) { return dot3(x, y, z, x, y, z); }
+// a b - c d
+__device__ __forceinline__ double diff2(double a, double b, double c, double d) { return fma(a, b, -(c * d)); }
+
 #ifndef MM_TESS_WAVES
 #define MM_TESS_WAVES 1
 #endif
@@ -203,13 +218,13 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
 // do (c is the new plane of a cut, a and b the planes of the edge it cuts).
 __device__ __forceinline__ void intersect3(const double4 a, const double4 b, const double4 c, double& x, double& y,
                                            double& z) {
-  const double abx = a.y * b.z - a.z * b.y, aby = a.z * b.x - a.x * b.z, abz = a.x * b.y - a.y * b.x;
-  const double det = c.x * abx + c.y * aby + c.z * abz;
-  const double ux = a.w * b.x - b.w * a.x, uy = a.w * b.y - b.w * a.y, uz = a.w * b.z - b.w * a.z;
+  const double abx = diff2(a.y, b.z, a.z, b.y), aby = diff2(a.z, b.x, a.x, b.z), abz = diff2(a.x, b.y, a.y, b.x);
+  const double det = dot3(c.x, c.y, c.z, abx, aby, abz);
+  const double ux = diff2(a.w, b.x, b.w, a.x), uy = diff2(a.w, b.y, b.w, a.y), uz = diff2(a.w, b.z, b.w, a.z);
   const double inv = rcp_nr(det);
-  x = (uy * c.z - uz * c.y + c.w * abx) * inv;
-  y = (uz * c.x - ux * c.z + c.w * aby) * inv;
-  z = (ux * c.y - uy * c.x + c.w * abz) * inv;
+  x = fma(c.w, abx, diff2(uy, c.z, uz, c.y)) * inv;
+  y = fma(c.w, aby, diff2(uz, c.x, ux, c.z)) * inv;
+  z = fma(c.w, abz, diff2(ux, c.y, uy, c.x)) * inv;
 }
 
 __device__ void fail_cell(const TessArgs& A, int s, int seg, int bit) {
@@ -262,7 +277,7 @@ __device__ void init_box(TessLds& S, const GridParams& g, CellRegs& C) {
   C.L0 = 0xffull;
   C.L1 = 0ull;
   C.np = 6;
-  C.rmax2 = wave_max_bound(lane < 8 ? C.v0x * C.v0x + C.v0y * C.v0y + C.v0z * C.v0z : 0.0);
+  C.rmax2 = wave_max_bound(lane < 8 ? norm2(C.v0x, C.v0y, C.v0z) : 0.0);
 }
 
 // Smallest stencil half-width whose buckets contain every image closer than
@@ -336,7 +351,7 @@ __device__ inline bool may_cut(const double4* vl, int nv, double dx, double dy, 
   bool out = false;
   for (int t = 0; t < nv; ++t) {
     const double4 v = vl[t];
-    out |= dx * v.x + dy * v.y + dz * v.z > h;
+    out |= dot3(dx, dy, dz, v.x, v.y, v.z) > h;
   }
   return out;
 }
@@ -354,7 +369,7 @@ __device__ inline bool box_may_cut(const double4* vl, int nv, const double lo[3]
     const double ex = fmax(0.0, fmax(lo[0] - v.x, v.x - hi[0]));
     const double ey = fmax(0.0, fmax(lo[1] - v.y, v.y - hi[1]));
     const double ez = fmax(0.0, fmax(lo[2] - v.z, v.z - hi[2]));
-    out |= ex * ex + ey * ey + ez * ez < v.w * (1.0 + 1e-9) + slack;
+    out |= norm2(ex, ey, ez) < fma(v.w, 1.0 + 1e-9, slack);
   }
   return out;
 }
@@ -392,7 +407,7 @@ __device__ inline bool vert_near_box(const double4 v, const double lo[3], const 
   const double ex = fmax(0.0, fmax(lo[0] - v.x, v.x - hi[0]));
   const double ey = fmax(0.0, fmax(lo[1] - v.y, v.y - hi[1]));
   const double ez = fmax(0.0, fmax(lo[2] - v.z, v.z - hi[2]));
-  return ex * ex + ey * ey + ez * ez < v.w * (1.0 + 1e-9) + slack;
+  return norm2(ex, ey, ez) < fma(v.w, 1.0 + 1e-9, slack);
 }
 
 // box_may_cut for every lane with `ask` set (false for the others); called
@@ -428,8 +443,8 @@ __device__ inline bool images_may_cut(bool ask, const double4* vl, int nv, const
     const int l = __builtin_ctzll(r);
     const double x = readlane_d(dx, l), y = readlane_d(dy, l), z = readlane_d(dz, l);
     const double h = 0.5 * readlane_d(d2, l) * (1.0 - 1e-12);
-    bool t = x * V.a.x + y * V.a.y + z * V.a.z > h;
-    if (V.two) t |= x * V.b.x + y * V.b.y + z * V.b.z > h;
+    bool t = dot3(x, y, z, V.a.x, V.a.y, V.a.z) > h;
+    if (V.two) t |= dot3(x, y, z, V.b.x, V.b.y, V.b.z) > h;
     if (__ballot(t) != 0ull && lane == l) res = true;
   }
   return res;
@@ -453,6 +468,11 @@ __device__ int gather_runs(TessLds& S, const TessArgs& A, const GridParams& g, c
   const double rq = sqrt(hi2) * (1.0 + 1e-9) + 1e-9 * fmin(g.hb[0], fmin(g.hb[1], g.hb[2]));
   LaneVerts V{};
   if (vl) V = lane_verts(vl, nv);
+  // A bucket wall u (in buckets) under a shift, relative to the generator and
+  // moved by a share of the bucket.
+  auto wall = [&](int a, double u, double shift, double share) {
+    return fma(share, g.hb[a], fma(u, g.hb[a], shift) - r[a]);
+  };
   for (int half = 0; half < 2; ++half) {
     int bb[3] = {0, 0, 0};
     int64_t key = 0;
@@ -477,8 +497,8 @@ __device__ int gather_runs(TessLds& S, const TessArgs& A, const GridParams& g, c
       if (meet && vl) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          blo[a] = (bb[a] * g.hb[a] + sh[a]) - r[a] - 1e-9 * g.hb[a];
-          bhi[a] = ((bb[a] + 1) * g.hb[a] + sh[a]) - r[a] + 1e-9 * g.hb[a];
+          blo[a] = wall(a, bb[a], sh[a], -1e-9);
+          bhi[a] = wall(a, bb[a] + 1, sh[a], 1e-9);
         }
       }
     }
@@ -538,12 +558,12 @@ __device__ int gather_runs(TessLds& S, const TessArgs& A, const GridParams& g, c
         double lo[3] = {0.0, 0.0, 0.0}, hi[3] = {0.0, 0.0, 0.0};
         if (row) {
           const double is = 1.0 / ss;
-          lo[0] = (bx_o + x0 * is) * g.hb[0] + sx - r[0] - 1e-9 * g.hb[0];
-          lo[1] = (by_o + ry * is) * g.hb[1] + sy - r[1] - 1e-9 * g.hb[1];
-          lo[2] = (bz_o + rz * is) * g.hb[2] + sz - r[2] - 1e-9 * g.hb[2];
-          hi[0] = (bx_o + (x0 + nx) * is) * g.hb[0] + sx - r[0] + 1e-9 * g.hb[0];
-          hi[1] = (by_o + (ry + 1) * is) * g.hb[1] + sy - r[1] + 1e-9 * g.hb[1];
-          hi[2] = (bz_o + (rz + 1) * is) * g.hb[2] + sz - r[2] + 1e-9 * g.hb[2];
+          lo[0] = wall(0, fma((double)x0, is, (double)bx_o), sx, -1e-9);
+          lo[1] = wall(1, fma((double)ry, is, (double)by_o), sy, -1e-9);
+          lo[2] = wall(2, fma((double)rz, is, (double)bz_o), sz, -1e-9);
+          hi[0] = wall(0, fma((double)(x0 + nx), is, (double)bx_o), sx, 1e-9);
+          hi[1] = wall(1, fma((double)(ry + 1), is, (double)by_o), sy, 1e-9);
+          hi[2] = wall(2, fma((double)(rz + 1), is, (double)bz_o), sz, 1e-9);
         }
         take = boxes_may_cut(row, vl, nv, V, lo, hi, 1e-12 * hi2);
       }
@@ -568,7 +588,7 @@ __device__ int gather_runs(TessLds& S, const TessArgs& A, const GridParams& g, c
           z = A.spos[3 * (int64_t)j + 2];
         }
         const double dx = (x + sx) - r[0], dy = (y + sy) - r[1], dz = (z + sz) - r[2];
-        const double d2 = dx * dx + dy * dy + dz * dz;
+        const double d2 = norm2(dx, dy, dz);
         bool keep = v && (d2 >= lo2) && (d2 < hi2);
         if (vl) keep = images_may_cut(keep, vl, nv, V, dx, dy, dz, d2);
         const unsigned long long mk = __ballot(keep);
@@ -713,7 +733,7 @@ __device__ int gather_rows(LDS& S, const TessArgs& A, const GridParams& g, bool 
           dx[u] = (x + (k < c0 ? sx0 : sx1)) - r[0];
           dy[u] = (yy + sy) - r[1];
           dz[u] = (zz + sz) - r[2];
-          d2[u] = dx[u] * dx[u] + dy[u] * dy[u] + dz[u] * dz[u];
+          d2[u] = norm2(dx[u], dy[u], dz[u]);
           keep[u] = v && d2[u] >= lo2 && d2[u] < hi2;
         }
 #pragma unroll
@@ -778,8 +798,7 @@ __device__ int gather(TessLds& S, const TessArgs& A, const GridParams& g, const 
       }
       const double dx0 = (x0 + B0.sx) - r[0], dy0 = (y0 + B0.sy) - r[1], dz0 = (z0 + B0.sz) - r[2];
       const double dx1 = (x1 + B1.sx) - r[0], dy1 = (y1 + B1.sy) - r[1], dz1 = (z1 + B1.sz) - r[2];
-      const double d20 = dx0 * dx0 + dy0 * dy0 + dz0 * dz0;
-      const double d21 = dx1 * dx1 + dy1 * dy1 + dz1 * dz1;
+      const double d20 = norm2(dx0, dy0, dz0), d21 = norm2(dx1, dy1, dz1);
       bool keep0 = v0 && (d20 >= lo2) && (d20 < hi2);
       bool keep1 = v1 && (d21 >= lo2) && (d21 < hi2);
       if (vl) {
@@ -859,8 +878,8 @@ __device__ inline int uniform_i32(int x) { return __builtin_amdgcn_readfirstlane
 // Squared distance bound of the farthest live vertex (float, rounded up).
 __device__ inline double farthest_bound(const CellRegs& C) {
   double m2 = 0.0;
-  if (lane_on(C.L0)) m2 = C.v0x * C.v0x + C.v0y * C.v0y + C.v0z * C.v0z;
-  if (C.L1 != 0ull && lane_on(C.L1)) m2 = fmax(m2, C.v1x * C.v1x + C.v1y * C.v1y + C.v1z * C.v1z);
+  if (lane_on(C.L0)) m2 = norm2(C.v0x, C.v0y, C.v0z);
+  if (C.L1 != 0ull && lane_on(C.L1)) m2 = fmax(m2, norm2(C.v1x, C.v1y, C.v1z));
   return wave_max_bound(m2);
 }
 
@@ -895,9 +914,9 @@ __device__ int clip_candidates(TessLds& S, const int nc, CellRegs& C) {
     const bool two = C.L1 != 0ull;
     // The test runs on every slot; the live masks (wavefront-uniform) keep
     // the live ones.
-    const unsigned long long M0 = __ballot(q.x * C.v0x + q.y * C.v0y + q.z * C.v0z > h) & C.L0;
+    const unsigned long long M0 = __ballot(dot3(q.x, q.y, q.z, C.v0x, C.v0y, C.v0z) > h) & C.L0;
     unsigned long long M1 = 0ull;
-    if (two) M1 = __ballot(q.x * C.v1x + q.y * C.v1y + q.z * C.v1z > h) & C.L1;
+    if (two) M1 = __ballot(dot3(q.x, q.y, q.z, C.v1x, C.v1y, C.v1z) > h) & C.L1;
     if ((M0 | M1) == 0ull) continue;
     const bool live0 = lane_on(C.L0), live1 = two && lane_on(C.L1);
     const bool out0 = lane_on(M0), out1 = lane_on(M1);
@@ -1065,20 +1084,20 @@ __device__ int finish_cell(TessLds& S, const TessArgs& A, const int s, const Cel
       const int tn = S.E[p * kPlanes + z] & (kVerts - 1);
       const double x1 = S.vx[t] - ox, y1 = S.vy[t] - oy, z1 = S.vz[t] - oz;
       const double x2 = S.vx[tn] - ox, y2 = S.vy[tn] - oy, z2 = S.vz[tn] - oz;
-      const double ar = 0.5 * ((y1 * z2 - z1 * y2) * nx + (z1 * x2 - x1 * z2) * ny + (x1 * y2 - y1 * x2) * nz);
+      const double ar = 0.5 * dot3(diff2(y1, z2, z1, y2), diff2(z1, x2, x1, z2), diff2(x1, y2, y1, x2), nx, ny, nz);
       as += ar;
-      mx += ar * (x1 + x2);
-      my += ar * (y1 + y2);
-      mz += ar * (z1 + z2);
+      mx = fma(ar, x1 + x2, mx);
+      my = fma(ar, y1 + y2, my);
+      mz = fma(ar, z1 + z2, mz);
       t = tn;
       ++it;
     } while (t != tstart && it < kVerts);
     walk_bad = (t != tstart);
     Af = as;
     const double i3a = 1.0 / (3.0 * as);
-    fx = ox + mx * i3a;
-    fy = oy + my * i3a;
-    fz = oz + mz * i3a;
+    fx = fma(mx, i3a, ox);
+    fy = fma(my, i3a, oy);
+    fz = fma(mz, i3a, oz);
   }
   if (__ballot(walk_bad)) return F_WALK;
   // A plane that only touches the cell gives no face (non-positive area).
@@ -1123,10 +1142,10 @@ __device__ int vertex_list(const CellRegs& C, double4* vl) {
   if (n > kPruneVerts) return 0;
   if (lane_on(C.L0))
     vl[__popcll(C.L0 & lanes_below())] =
-        make_double4(C.v0x, C.v0y, C.v0z, C.v0x * C.v0x + C.v0y * C.v0y + C.v0z * C.v0z);
+        make_double4(C.v0x, C.v0y, C.v0z, norm2(C.v0x, C.v0y, C.v0z));
   if (lane_on(C.L1))
     vl[n0 + __popcll(C.L1 & lanes_below())] =
-        make_double4(C.v1x, C.v1y, C.v1z, C.v1x * C.v1x + C.v1y * C.v1y + C.v1z * C.v1z);
+        make_double4(C.v1x, C.v1y, C.v1z, norm2(C.v1x, C.v1y, C.v1z));
   wave_sync();
   return n;
 }
@@ -1190,7 +1209,7 @@ __device__ inline FarBox far_box(const Regs& C, const unsigned long long live0, 
   FarBox F;
   float lo[3] = {0.f, 0.f, 0.f}, hi[3] = {0.f, 0.f, 0.f};
   auto add = [&](bool live, double x, double y, double z) {
-    const double m2 = x * x + y * y + z * z;
+    const double m2 = norm2(x, y, z);
     if (live && 4.0 * m2 * (1.0 + 1e-9) >= lo2) {
       const float v[3] = {(float)(x * iq), (float)(y * iq), (float)(z * iq)};
       const float rad = sqrtf((float)(m2 * iq * iq)) * (1.f + 4e-6f);
@@ -1237,7 +1256,7 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     b[a] = bucket_coord(r[a], g.inv_hb[a], g.nb[a]);
-    const double t = r[a] - b[a] * g.hb[a];
+    const double t = fma(-(double)b[a], g.hb[a], r[a]);
     edge[a] = fmax(0.0, fmin(t, g.hb[a] - t));
   }
   CellRegs C;
@@ -1263,7 +1282,7 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
     const int ring = dense ? min(g.ring, ring_for(g, edge, rloc * rloc)) : g.ring;
     double reach = 1e300;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) reach = fmin(reach, ring * g.hb[a] + edge[a]);
+    for (int a = 0; a < 3; ++a) reach = fmin(reach, fma((double)ring, g.hb[a], edge[a]));
     double hi2 = fmin(reach * reach, rloc * rloc);
     int nc = gather_first( ring, 0.0, hi2);
     if (nc < 0) {
@@ -1324,9 +1343,9 @@ __device__ int tess_cell(TessLds& S, const TessArgs& A, const int s, double& rm2
           SideWindow window;
 #pragma unroll
           for (int a = 0; a < 3; ++a) {
-            const double t = r[a] - b[a] * g.hb[a];
-            window.lo[a] = max(0, min(nring, -uniform_i32((int)floor((t - rq * (double)F.lo[a]) * g.inv_hb[a]))));
-            window.hi[a] = max(0, min(nring, uniform_i32((int)floor((t + rq * (double)F.hi[a]) * g.inv_hb[a]))));
+            const double t = fma(-(double)b[a], g.hb[a], r[a]);
+            window.lo[a] = max(0, min(nring, -uniform_i32((int)floor(fma(-rq, (double)F.lo[a], t) * g.inv_hb[a]))));
+            window.hi[a] = max(0, min(nring, uniform_i32((int)floor(fma(rq, (double)F.hi[a], t) * g.inv_hb[a]))));
           }
           return gather_rows<64, kCands>(S, A, g, true, s, r, b, window, lo2, hi2);
         } else {
@@ -1622,7 +1641,7 @@ __device__ void init_box_pair(PairLds& S, const GridParams& g, PairRegs& C) {
   C.L0w = __ballot(hl < 8);
   C.L1w = 0ull;
   C.np = 6;
-  C.rmax2 = half_max_bound(hl < 8 ? C.v0x * C.v0x + C.v0y * C.v0y + C.v0z * C.v0z : 0.0);
+  C.rmax2 = half_max_bound(hl < 8 ? norm2(C.v0x, C.v0y, C.v0z) : 0.0);
 }
 
 __device__ inline double farthest_bound_pair(const PairRegs& C) {
@@ -1631,16 +1650,36 @@ __device__ inline double farthest_bound_pair(const PairRegs& C) {
   double ax = C.v0x, ay = C.v0y, az = C.v0z, bx = C.v1x, by = C.v1y, bz = C.v1z;
   asm volatile("" : "+v"(ax), "+v"(ay), "+v"(az), "+v"(bx), "+v"(by), "+v"(bz));
   double m2 = 0.0;
-  if (lane_on(C.L0w)) m2 = ax * ax + ay * ay + az * az;
-  if (lane_on(C.L1w)) m2 = fmax(m2, bx * bx + by * by + bz * bz);
+  if (lane_on(C.L0w)) m2 = norm2(ax, ay, az);
+  if (lane_on(C.L1w)) m2 = fmax(m2, norm2(bx, by, bz));
   return half_max_bound(m2);
+}
+
+// Whether stencil bucket bb, under its image's shift sh, may hold a point of
+// the box F about the generator (query radius rq): qlo and qhi receive the
+// box's sides in the bucket's own image.  Bucket bb holds the points with
+// floor(x / hb) = bb (the last one also those rounding to nb).
+__device__ inline bool bucket_meets(const GridParams& g, const double r[3], const int bb[3], const double sh[3],
+                                    const double rq, const FarBox& F, double qlo[3], double qhi[3]) {
+  bool meet = true;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    qlo[a] = fma(-rq, (double)F.lo[a], r[a]) - sh[a];
+    qhi[a] = fma(rq, (double)F.hi[a], r[a]) - sh[a];
+    const double tlo = qlo[a] * g.inv_hb[a], thi = qhi[a] * g.inv_hb[a];
+    if (thi < (double)bb[a] || (tlo >= (double)(bb[a] + 1) && bb[a] < g.nb[a] - 1)) meet = false;
+  }
+  return meet;
 }
 
 // The dense pass's gather of both halves: images with lo2 <= |d|^2 < hi2 from
 // each half's stencil of half-width `ring`, one stencil bucket per lane at a
 // time (the stencils are small, and more buckets per lane spill registers:
 // 10% slower with four).  A chunk of the stencil that holds a dense bucket,
-// in either half, is taken by the two-level gather of both halves.  Returns
+// in either half, is taken by the two-level gather of both halves.  A shell
+// after the first radius (far) takes only the buckets that meet its box, in
+// either gather: the images a cell finds, and with them whether they fit its
+// slots, do not depend on the cell in the other half.  Returns
 // the number of images this half found (more than kCandsP: an overflow, of
 // which only the first kCandsP are stored).  Called by the whole wavefront
 // (act: the half has a cell).
@@ -1650,14 +1689,20 @@ __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams&
 
 __device__ int gather_pair(PairLds& S, const TessArgs& A, const GridParams& g, bool act, const int s,
                            const double r[3], const int b[3], const int ring, const double lo2, const double hi2,
-                           const double rq, const FarBox& F) {
+                           const double rq, const FarBox& F, const bool far) {
   const int hl = hlane();
   const int W = 2 * ring + 1, W3 = act ? W * W * W : 0;
   const WidthDiv D = width_div((unsigned)W);
   const int W3max = (int)wave_umax32((unsigned)W3);
   int nc = 0;
   for (int chunk = 0; chunk < W3max; chunk += 32) {
-    const StencilBucket B = stencil_bucket(A, g, b, ring, chunk + hl, W3, D);
+    int bb[3] = {0, 0, 0};
+    StencilBucket B = stencil_bucket(A, g, b, ring, chunk + hl, W3, D, bb);
+    if (far && B.cnt > 0) {
+      const double sh[3] = {B.sx, B.sy, B.sz};
+      double qlo[3], qhi[3];
+      if (!bucket_meets(g, r, bb, sh, rq, F, qlo, qhi)) B.cnt = 0;
+    }
     if (__ballot(B.cnt > kDense)) {
       nc = gather_runs_pair(S, A, g, s, r, b, ring, chunk, W3, D, lo2, hi2, rq, F, nc);
       continue;
@@ -1673,7 +1718,7 @@ __device__ int gather_pair(PairLds& S, const TessArgs& A, const GridParams& g, b
         z = A.spos[3 * (int64_t)j + 2];
       }
       const double dx = (x + B.sx) - r[0], dy = (y + B.sy) - r[1], dz = (z + B.sz) - r[2];
-      const double d2 = dx * dx + dy * dy + dz * dz;
+      const double d2 = norm2(dx, dy, dz);
       const bool keep = v && d2 >= lo2 && d2 < hi2;
       const unsigned mk = hbits(__ballot(keep));
       if (keep) {
@@ -1713,15 +1758,7 @@ __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams&
     if (B.cnt > 0) {
       const double sh[3] = {B.sx, B.sy, B.sz};
       double qlo[3], qhi[3];
-      bool meet = true;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        qlo[a] = (r[a] - rq * (double)F.lo[a]) - sh[a];
-        qhi[a] = (r[a] + rq * (double)F.hi[a]) - sh[a];
-        const double tlo = qlo[a] * g.inv_hb[a], thi = qhi[a] * g.inv_hb[a];
-        if (thi < (double)bb[a] || (tlo >= (double)(bb[a] + 1) && bb[a] < g.nb[a] - 1)) meet = false;
-      }
-      if (meet) {
+      if (bucket_meets(g, r, bb, sh, rq, F, qlo, qhi)) {
         if (B.cnt <= kDense || B.cnt > kDenseMax) {
           nr = 1;
         } else {
@@ -1787,7 +1824,7 @@ __device__ int gather_runs_pair(PairLds& S, const TessArgs& A, const GridParams&
           dx[u] = (x + sx) - r[0];
           dy[u] = (y + sy) - r[1];
           dz[u] = (z + sz) - r[2];
-          d2[u] = dx[u] * dx[u] + dy[u] * dy[u] + dz[u] * dz[u];
+          d2[u] = norm2(dx[u], dy[u], dz[u]);
           keep[u] = v && d2[u] >= lo2 && d2[u] < hi2;
         }
 #pragma unroll
@@ -1944,12 +1981,13 @@ __device__ unsigned long long cube_start(PairLds& S, const GridParams& g, const 
   const double4 A = S.cd[ia], B = S.cd[ib], P = S.cd[pm];
   double vx, vy, vz;
   intersect3(A, B, P, vx, vy, vz);
-  const double det = P.x * (A.y * B.z - A.z * B.y) + P.y * (A.z * B.x - A.x * B.z) + P.z * (A.x * B.y - A.y * B.x);
+  const double det =
+      dot3(P.x, P.y, P.z, diff2(A.y, B.z, A.z, B.y), diff2(A.z, B.x, A.x, B.z), diff2(A.x, B.y, A.y, B.x));
   bool in = det > 0.0 && fabs(vx) < 0.5 * g.L[0] && fabs(vy) < 0.5 * g.L[1] && fabs(vz) < 0.5 * g.L[2];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const double4 o = S.cd[k == 0 ? kp[1 - sx] : (k == 1 ? kp[3 - sy] : kp[5 - sz])];
-    in = in && o.x * vx + o.y * vy + o.z * vz < o.w;
+    in = in && dot3(o.x, o.y, o.z, vx, vy, vz) < o.w;
   }
   okw &= ~halves_of(__ballot(!in));
   if (okw == 0ull) return 0ull;
@@ -1973,7 +2011,7 @@ __device__ unsigned long long cube_start(PairLds& S, const GridParams& g, const 
   }
   wave_sync();
   C.L0w = (C.L0w & ~okw) | corner;
-  const double nb = half_max_bound(vx * vx + vy * vy + vz * vz);   // (finite in the halves that take it)
+  const double nb = half_max_bound(norm2(vx, vy, vz));   // (finite in the halves that take it)
   if (lane_on(okw)) {
     const unsigned used = hbits(usedw);
     C.rmax2 = nb;
@@ -2042,8 +2080,8 @@ __device__ bool clip_pair(PairLds& S, const int nc, PairRegs& C, const unsigned 
         donew |= farw;
         seekw &= ~farw;
       }
-      const unsigned long long n0 = __ballot(q.x * C.v0x + q.y * C.v0y + q.z * C.v0z > q.w) & seekw & C.L0w;
-      const unsigned long long n1 = __ballot(q.x * C.v1x + q.y * C.v1y + q.z * C.v1z > q.w) & seekw & C.L1w;
+      const unsigned long long n0 = __ballot(dot3(q.x, q.y, q.z, C.v0x, C.v0y, C.v0z) > q.w) & seekw & C.L0w;
+      const unsigned long long n1 = __ballot(dot3(q.x, q.y, q.z, C.v1x, C.v1y, C.v1z) > q.w) & seekw & C.L1w;
       const unsigned long long hitw = halves_of(n0 | n1);
       M0w |= n0;
       M1w |= n1;
@@ -2207,11 +2245,11 @@ __device__ int finish_pair(PairLds& S, const TessArgs& A, const bool act, const 
         const int z = (a == p) ? cq : (bq == p ? a : bq);
         const int tn = S.E[p * kPlanesP + z] & (kVertsP - 1);
         const double x2 = S.vx[tn] - ox, y2 = S.vy[tn] - oy, z2 = S.vz[tn] - oz;
-        const double ar = 0.5 * ((y1 * z2 - z1 * y2) * nx + (z1 * x2 - x1 * z2) * ny + (x1 * y2 - y1 * x2) * nz);
+        const double ar = 0.5 * dot3(diff2(y1, z2, z1, y2), diff2(z1, x2, x1, z2), diff2(x1, y2, y1, x2), nx, ny, nz);
         as += ar;
-        mx += ar * (x1 + x2);
-        my += ar * (y1 + y2);
-        mz += ar * (z1 + z2);
+        mx = fma(ar, x1 + x2, mx);
+        my = fma(ar, y1 + y2, my);
+        mz = fma(ar, z1 + z2, mz);
         x1 = x2;
         y1 = y2;
         z1 = z2;
@@ -2221,9 +2259,9 @@ __device__ int finish_pair(PairLds& S, const TessArgs& A, const bool act, const 
       walk_bad |= (t != tstart);
       Af[k] = as;
       const double i3a = rcp_nr(3.0 * as);
-      fx[k] = ox + mx * i3a;
-      fy[k] = oy + my * i3a;
-      fz[k] = oz + mz * i3a;
+      fx[k] = fma(mx, i3a, ox);
+      fy[k] = fma(my, i3a, oy);
+      fz[k] = fma(mz, i3a, oz);
     }
   }
   if (hbits(__ballot(walk_bad))) return F_WALK;
@@ -2287,7 +2325,7 @@ __device__ inline void cell_geom(const TessArgs& A, const GridParams& g, const i
   for (int a = 0; a < 3; ++a) {
     G.r[a] = A.spos[3 * (int64_t)s + a];
     G.b[a] = bucket_coord(G.r[a], g.inv_hb[a], g.nb[a]);
-    const double t = G.r[a] - G.b[a] * g.hb[a];
+    const double t = fma(-(double)G.b[a], g.hb[a], G.r[a]);
     G.edge[a] = fmax(0.0, fmin(t, g.hb[a] - t));
   }
 }
@@ -2297,7 +2335,7 @@ __device__ inline void cell_geom(const TessArgs& A, const GridParams& g, const i
 // found (counts go as the shell's volume, r^3 - lo^3).
 __device__ inline double shell_for(double lo2, double hi2, int nc, double want) {
   const double lo3 = lo2 * sqrt(lo2), hi3 = hi2 * sqrt(hi2);
-  const double r = cbrt(lo3 + (want / (double)nc) * (hi3 - lo3));
+  const double r = cbrt(fma(want / (double)nc, hi3 - lo3, lo3));
   return r * r;
 }
 
@@ -2352,7 +2390,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
   int ring = cnt > 4u ? min(g.ring, ring_for(g, edge, rloc * rloc)) : g.ring;
   double reach = 1e300;
 #pragma unroll
-  for (int a = 0; a < 3; ++a) reach = fmin(reach, ring * g.hb[a] + edge[a]);
+  for (int a = 0; a < 3; ++a) reach = fmin(reach, fma((double)ring, g.hb[a], edge[a]));
   double lo2 = 0.0, hi2 = fmin(reach * reach, rloc * rloc);
   // The first radius, then, for a cell whose candidates do not reach twice
   // its farthest vertex, up to kShells1 more distance shells, as in the
@@ -2389,7 +2427,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
         const double rq = query_radius(g1, hi2);
         FarBox F{{1.f, 1.f, 1.f}, {1.f, 1.f, 1.f}};
         if (shell > 0) F = far_box(C, C.L0w, C.L1w, lo2, rq, half_umax32);
-        return gather_pair(S, A, g1, on, s1, G1.r, G1.b, ring, lo2, hi2, rq, F);
+        return gather_pair(S, A, g1, on, s1, G1.r, G1.b, ring, lo2, hi2, rq, F, shell > 0);
       } else {
         return gather_rows<32, kCandsP>(S, A, g1, on, s1, G1.r, G1.b, window, lo2, hi2);
       }
@@ -2454,9 +2492,9 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
         window = PackedWindow();
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-          const double t = G3.r[a] - G3.b[a] * g3.hb[a];
-          window.set(a, max(0, min(ring, -(int)floor((t - rq * (double)F.lo[a]) * g3.inv_hb[a]))),
-                     max(0, min(ring, (int)floor((t + rq * (double)F.hi[a]) * g3.inv_hb[a]))));
+          const double t = fma(-(double)G3.b[a], g3.hb[a], G3.r[a]);
+          window.set(a, max(0, min(ring, -(int)floor(fma(-rq, (double)F.lo[a], t) * g3.inv_hb[a]))),
+                     max(0, min(ring, (int)floor(fma(rq, (double)F.hi[a], t) * g3.inv_hb[a]))));
         }
       }
     }
