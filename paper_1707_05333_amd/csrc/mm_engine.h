@@ -86,9 +86,14 @@ struct Engine {
   int64_t n = 0, n_faces = 0, nbt = 0;
   // List lengths of the last tessellation read back (none yet: -1); they
   // size the list passes' grids only.  last_dense_cap: the listed dense
-  // cells the last two-cell dense pass took.
+  // cells the last two-cell dense pass took.  lists_new: a tessellation has
+  // been enqueued since the last readback (a readback after any other call
+  // finds the counters cleared, which says nothing about the next mesh: two
+  // polytropes of 1,048,576 points tessellated after a cell_state call took
+  // 41 ms with such lengths and 20 ms with those of their last mesh).
   TessHints hints;
   int64_t last_dense_cap = 0;
+  bool lists_new = false;
   // First-pass candidate radius in mean spacings.  It changes only the
   // work, never the cells (clipping is always in order of distance, ties
   // broken by neighbour and image).  With the first pass taking up to three

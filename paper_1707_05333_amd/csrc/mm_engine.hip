@@ -317,6 +317,7 @@ void Engine::enqueue_tessellation(const double* pos, int64_t n_slots, const int3
                                      rmax2, deferred, dcells, redo, hints, nseg == 1 ? &segs_host[0].g : nullptr,
                                      precision == MM_MIXED, st,
                                      segst, stream);
+  lists_new = true;
   mark(2);
   launch_mesh_scan(counts, n_cells, off, soff, scan_tmp, st, stream);
   launch_build_mesh(spos, geo, n_cells, segs, sseg, stage_nb, stage_geo, counts, off, soff, fcap, sell_cap, faces, csr,
@@ -400,6 +401,8 @@ mm_status Engine::readback() {
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return fail(MM_EHIP, std::string("status readback: ") + hipGetErrorString(e));
   table_in_flight = false;
+  if (!lists_new) return MM_OK;
+  lists_new = false;
   const DevStatus& s = *st_host;
   hints.dense_cells = s.n_dense_cells;
   hints.redo = s.n_redo;

@@ -53,3 +53,20 @@ def test_dense_cells_do_not_follow_from_their_order(precision):
     for _ in range(5):
         assert mm.tessellate(dev(pos)) == info
         assert _unlike(_mesh(mm), mesh) == []
+
+
+def test_lists_survive_the_component_calls():
+    # The list lengths that size the next tessellation's passes are those of
+    # the last tessellation, whatever calls come between: the same cells are
+    # handed on, by the same passes.
+    import paper_1707_05333_amd as M
+    pos, prim = _cluster(20000, 12000, seed=3)
+    _case("tessellate, cell_state, tessellate", n=len(pos))
+    mm = M.MovingMesh(len(pos), M.make_params(box=BOX))
+    first = mm.tessellate(dev(pos))
+    mesh = _mesh(mm)
+    Q = mm.init_charges(dev(prim))
+    for _ in range(2):
+        mm.cell_state(Q)
+        assert mm.tessellate(dev(pos)) == first
+        assert _unlike(_mesh(mm), mesh) == []
