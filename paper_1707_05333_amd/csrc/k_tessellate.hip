@@ -138,6 +138,28 @@ __device__ __forceinline__ int wave_excl_scan(int x, int* total) {
   return v - x;
 }
 
+// Inclusive prefix sum within each half: row shifts by 1, 2, 4 and 8 inside
+// each row of 16 lanes (lanes shifted in from outside the row read 0), then
+// the last lane of row 0 added to row 1 and that of row 2 to row 3.  Called
+// by the whole wavefront.
+__device__ __forceinline__ int half_incl_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+  return x;
+}
+
+// Exclusive prefix sum in the order lane 0, 32, 1, 33, ...; *total gets the
+// wave's sum.  Called by the whole wavefront.
+__device__ __forceinline__ int paired_excl_scan(int x, int* total) {
+  const int y = __shfl_xor(x, 32, 64);
+  const int incl = half_incl_scan(x + y);
+  *total = __builtin_amdgcn_readlane(incl, 63);
+  return incl - (x + y) + ((__lane_id() & 32) ? y : 0);
+}
+
 // Wave-wide reductions with DPP lane moves (no LDS round trip): within each
 // row of 16 lanes by quad permutes and row rotations, then across rows by
 // the row broadcasts; lane 63 ends with the result, read as a scalar.
@@ -954,7 +976,7 @@ __device__ int clip_candidates(TessLds& S, const int nc, CellRegs& C) {
     const int bm1 = out1 ? boundary(C.t1) : 0;
     const int nbl = __popc(bm0) + __popc(bm1);
     int B;
-    const int pre = wave_excl_scan(nbl, &B);
+    const int pre = paired_excl_scan(nbl, &B);
 
     const unsigned long long F0 = ~L0 | M0, F1 = ~L1 | M1;   // free slots after the cut
     const int nf0 = __popcll(F0);
@@ -963,7 +985,8 @@ __device__ int clip_candidates(TessLds& S, const int nc, CellRegs& C) {
       S.pl[p] = make_double4(q.x, q.y, q.z, h);
       S.pcand[p] = S.cjk[c];   // the neighbour itself: later shells reuse the candidate slots
     }
-    // Boundary edges into a list, in prefix order.
+    // Boundary edges into a list, in prefix order (lane l, then lane l + 32: the
+    // order of the two-cell passes, whose lanes hold these two slots).
     int e = pre;
 #pragma unroll
     for (int sl = 0; sl < 2; ++sl) {
@@ -1032,6 +1055,12 @@ __device__ inline StageNbr staged_nbr(int s, int pc) {
 }
 
 // Faces, volume and centroid of the finished cell; writes the cell's outputs.
+// The steps are those of finish_pair, operation by operation, and a cut hands
+// out slots as the two-cell passes do: a dense region's cell is bitwise the same
+// from either pass.  Which one builds it follows from the lengths of the lists
+// (k_tess_rest takes dense cells one by one, so does k_tess_pass1_dense those
+// beyond the two-cell pass's grid): from the mesh before, and from the other
+// simulations of the launch.
 __device__ int finish_cell(TessLds& S, const TessArgs& A, const int s, const CellRegs& C) {
   const int lane = __lane_id();
   const bool live0 = lane_on(C.L0), live1 = lane_on(C.L1);
@@ -1070,8 +1099,9 @@ __device__ int finish_cell(TessLds& S, const TessArgs& A, const int s, const Cel
   bool walk_bad = false;
   if (valid) {
     const double4 P = S.pl[p];
-    dl = sqrt(2.0 * P.w);
-    const double idl = 1.0 / dl;
+    const double w2 = 2.0 * P.w;   // the plane's |d|^2
+    const double idl = rsqrt_nr(w2);
+    dl = w2 * idl;
     const double nx = P.x * idl, ny = P.y * idl, nz = P.z * idl;
     const int tstart = S.first[p];
     const double ox = S.vx[tstart], oy = S.vy[tstart], oz = S.vz[tstart];
@@ -1094,7 +1124,7 @@ __device__ int finish_cell(TessLds& S, const TessArgs& A, const int s, const Cel
     } while (t != tstart && it < kVerts);
     walk_bad = (t != tstart);
     Af = as;
-    const double i3a = 1.0 / (3.0 * as);
+    const double i3a = rcp_nr(3.0 * as);
     fx = fma(mx, i3a, ox);
     fy = fma(my, i3a, oy);
     fz = fma(mz, i3a, oz);
@@ -1104,7 +1134,7 @@ __device__ int finish_cell(TessLds& S, const TessArgs& A, const int s, const Cel
   const bool keep = valid && Af > 0.0;
   const double vol = keep ? Af * dl / 6.0 : 0.0;
   const double V = wave_sum(vol);
-  const double iV = 1.0 / V;
+  const double iV = rcp_nr(V);
   const double cxr = wave_sum(keep ? 0.75 * vol * fx : 0.0) * iV;
   const double cyr = wave_sum(keep ? 0.75 * vol * fy : 0.0) * iV;
   const double czr = wave_sum(keep ? 0.75 * vol * fz : 0.0) * iV;
@@ -1547,19 +1577,6 @@ __device__ __forceinline__ unsigned long long halves_of(unsigned long long m) {
   unsigned hi = (unsigned)(m >> 32);
   asm volatile("" : "+s"(hi));
   return halves((unsigned)m != 0u, hi != 0u);
-}
-
-// Inclusive prefix sum within each half: row shifts by 1, 2, 4 and 8 inside
-// each row of 16 lanes (lanes shifted in from outside the row read 0), then
-// the last lane of row 0 added to row 1 and that of row 2 to row 3.  Called
-// by the whole wavefront.
-__device__ __forceinline__ int half_incl_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
-  return x;
 }
 
 // Reductions over each half: within rows of 16 by quad permutes and row

@@ -317,9 +317,10 @@ void launch_mesh_scan(const unsigned long long* counts, int64_t n, unsigned long
                       unsigned long long* tmp, DevStatus* st_dev, hipStream_t st);
 
 // Lengths of an earlier tessellation's cell lists (-1: none yet).  They size
-// the grids of the passes that read the lists, never their results (those
-// passes walk their lists with a grid stride; the two-cell dense pass hands
-// listed cells beyond its grid to the one-cell dense pass).
+// the grids of the passes that read the lists, and say whether one launch
+// takes them all; never their results (the passes walk their lists with a grid
+// stride, and a dense region's cell is bitwise the same from the two-cell dense
+// pass and from the one-cell one, which takes listed cells beyond the grid).
 struct TessHints {
   int64_t dense_cells = -1;   // cells listed for the dense passes
   int64_t redo = -1;          // cells the lean two-cell pass handed on

@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from gpu_common import dev
+from gpu_common import compare_mesh, dev
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +70,58 @@ def test_lists_survive_the_component_calls():
         mm.cell_state(Q)
         assert mm.tessellate(dev(pos)) == first
         assert _unlike(_mesh(mm), mesh) == []
+
+
+@pytest.mark.parametrize("n,n_in", [(6000, 4500), (20000, 12000)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_mesh_does_not_follow_from_the_one_before(orc, precision, n, n_in):
+    # A new context takes every dense cell in the two-cell pass; one whose last
+    # mesh had none takes all lists in one launch, cell by cell; one whose last
+    # mesh had a few dense cells takes most of them beyond the two-cell pass's
+    # grid.  (What the passes hand on, which the call reports, may differ.)
+    import paper_1707_05333_amd as M
+    pos, _ = _cluster(n, n_in, seed=n)
+    _case("mesh after others", n=n, precision=precision)
+    p = M.make_params(box=BOX, precision=precision)
+    mm = M.MovingMesh(n, p)
+    mm.tessellate(dev(pos))
+    mesh = _mesh(mm)
+    om = orc.tessellate(pos, BOX, certificate=True)
+    assert om.status == 0 and om.delta_min > 1e-12
+    compare_mesh(mm, om, ftol=1e-9)
+    few = W.jittered_lattice((17, 18, 17), BOX, jitter=0.2, seed=2)
+    for dense in (0, 12):
+        other = few.copy()
+        other[:dense] = 0.52 + 1e-3 * (few[:dense] - 0.5)   # within one bucket
+        mm = M.MovingMesh(n, p)
+        mm.tessellate(dev(other))
+        mm.tessellate(dev(pos))
+        assert _unlike(_mesh(mm), mesh) == [], f"after {dense} dense cells"
+
+
+@pytest.mark.parametrize("n,n_in", [(2400, 1400), (3600, 300), (6000, 4500)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_clustered_simulation_alone_and_in_a_mix(precision, n, n_in):
+    import paper_1707_05333_amd as M
+    pos, prim = _cluster(n, n_in, seed=n + 1)
+    big = W.c1_uniform_random_velocity(n_side=18)
+    _case("clustered simulation", n=n, precision=precision)
+    p = M.make_params(box=BOX, precision=precision)
+    pb = M.make_params(box=big.box, precision=precision, **big.params)
+
+    def run(before, beside):
+        B = M.Batch(M.batch_footprint(20000, precision), max_sims=4, precision=precision)
+        if before or beside:
+            other = B.admit(pb, dev(big.pos), dev(big.prim))
+        if before:
+            B.step()
+        if before and not beside:
+            B.evict(other)
+        s = B.admit(p, dev(pos), dev(prim))
+        for _ in range(3):
+            assert all(r["status"] == 0 for r in B.step())
+        return B.read(s)
+
+    alone = run(False, False)
+    for before, beside in ((False, True), (True, True), (True, False)):
+        assert _unlike(run(before, beside), alone) == [], (before, beside)
