@@ -231,7 +231,7 @@ mm_status mm_init_entropy(mm_ctx *ctx, const double *prim, double *S);
  * entropy charges (caller order); mach: dev [n] float out, each cell's
  * largest face Mach number (1 without compression), or NULL.  With
  * mach_threshold = 0 the charges Q are exactly those of mm_step.
- * Errors as mm_step (S, like pos and Q, keeps its values on an error), and
+ * Errors as mm_step (S and mach, like pos and Q, keep their values on an error), and
  * MM_EINVAL with half_step_mesh = 1. */
 mm_status mm_step_entropy(mm_ctx *ctx, int64_t n, double *pos, double *w, double *Q, double *S, float *mach,
                           double dt_max, mm_step_info *info);

@@ -934,11 +934,12 @@ __device__ inline void cell_flux_sum(int64_t s, const unsigned long long* counts
 }
 
 // The charges, positions, mesh velocities and (with the switch) entropy
-// charges after the step, into the caller's slot-order arrays.  Cells of a
-// segment that has failed already are left alone; should a charge come out
-// non-finite here, the host puts the failed segment's state back (k_restore)
+// charges and Mach numbers after the step, into the caller's slot-order arrays.
+// Cells of a segment that failed in an earlier kernel are left alone; should a
+// charge come out non-finite here, every cell of its segment is written all the
+// same (F_UPDATE says so), and the host puts the segment's state back (k_restore)
 // before the call returns: the start-of-step charges, entropy charges and
-// positions stay in Qs, Ss and spos.  (Writing internal copies first and
+// positions stay in Qs, Ss and spos, and the caller's Mach numbers go to mach0.  (Writing internal copies first and
 // committing them in a second kernel took 64 bytes per cell more each way:
 // 0.04 ms of the 1M-cell step and a launch of every small one.)
 template <typename R>
@@ -954,13 +955,15 @@ __global__ __launch_bounds__(64) MM_MAX_WAVES(4) void k_update(const SegDesc* __
                                                      const SegStatus* dt_src, DevStatus* st, SegStatus* segst,
                                                      bool drift_from_slots, const double* __restrict__ Ss,
                                                      const R* __restrict__ phiX, const float* __restrict__ machF,
-                                                     double* __restrict__ Sc, float* __restrict__ machc) {
+                                                     double* __restrict__ Sc, float* __restrict__ machc,
+                                                     float* __restrict__ mach0) {
   const int64_t s = xcd_block() * blockDim.x + threadIdx.x;
   if (s >= n) return;
   const int seg = sseg[s];
   const HydroParams& hp = segs[seg].hp;
   double acc[5], Q[5];
-  if (segst[seg].flags || (st->flags & F_FACECAP)) return;
+  const int failed = segst[seg].flags;
+  if ((failed && !(failed & F_UPDATE)) || (st->flags & F_FACECAP)) return;
   cell_flux_sum<R>(s, counts, soff, csr, phi, acc);
 #pragma unroll
   for (int q = 0; q < 5; ++q) Q[q] = Qs[5 * s + q] + acc[q];
@@ -1042,31 +1045,35 @@ __global__ __launch_bounds__(64) MM_MAX_WAVES(4) void k_update(const SegDesc* __
   }
   if (Ss) {
     Sc[c] = Snew;
-    if (machc) machc[c] = mx;
+    if (machc) {
+      mach0[s] = machc[c];
+      machc[c] = mx;
+    }
     if (!isfinite(Snew)) bad = 1;
   }
-  if (bad) seg_fail(st, segst, seg, F_NONFINITE, (int)s);
+  if (bad) seg_fail(st, segst, seg, F_NONFINITE | F_UPDATE, (int)s);
 }
 
 // Puts the start-of-step charges, positions and entropy charges of every
-// failed segment back into the caller's arrays (of all of them after an
-// overflow of the shared face capacity).
+// segment that failed in the update back into the caller's arrays, and the Mach
+// numbers that they held.
 __global__ __launch_bounds__(kThreads) void k_restore(const int32_t* __restrict__ sseg, int64_t n,
                                                       const int32_t* __restrict__ perm,
-                                                      const DevStatus* __restrict__ st,
                                                       const SegStatus* __restrict__ segst,
                                                       const double* __restrict__ Q0, const double* __restrict__ pos0,
-                                                      const double* __restrict__ S0, double* __restrict__ Qc,
-                                                      double* __restrict__ posc, double* __restrict__ Sc) {
+                                                      const double* __restrict__ S0, const float* __restrict__ mach0,
+                                                      double* __restrict__ Qc, double* __restrict__ posc,
+                                                      double* __restrict__ Sc, float* __restrict__ machc) {
   const int64_t s = xcd_block() * blockDim.x + threadIdx.x;
   if (s >= n) return;
-  if (!segst[sseg[s]].flags && !(st->flags & F_FACECAP)) return;
+  if (!(segst[sseg[s]].flags & F_UPDATE)) return;
   const int64_t c = perm[s];
 #pragma unroll
   for (int q = 0; q < 5; ++q) Qc[5 * c + q] = Q0[5 * s + q];
 #pragma unroll
   for (int a = 0; a < 3; ++a) posc[3 * c + a] = pos0[3 * s + a];
   if (Sc) Sc[c] = S0[s];
+  if (machc) machc[c] = mach0[s];
 }
 
 template <typename R>
@@ -1224,19 +1231,19 @@ void launch_update(const SegDesc* segs, const int32_t* sseg, int64_t n, const un
                    const int32_t* perm, const double* Qs, double* Q_slots, const double* spos, const double* w,
                    double* pos_slots, double* w_slots, const SegStatus* dt_src, DevStatus* st_dev, SegStatus* segst,
                    hipStream_t st, bool drift_from_slots, const double* Ss, const R* phiX, const float* machF,
-                   double* S_slots, float* mach_slots) {
+                   double* S_slots, float* mach_slots, float* mach0) {
   if (n <= 0) return;
   hipLaunchKernelGGL(k_update<R>, dim3(blocks_for(n, 64)), dim3(64), 0, st, segs, sseg, n, counts, soff, csr,
                        phi, geo, perm, Qs, Q_slots, spos, w, pos_slots, w_slots, dt_src, st_dev, segst,
-                       drift_from_slots, Ss, phiX, machF, S_slots, mach_slots);
+                       drift_from_slots, Ss, phiX, machF, S_slots, mach_slots, mach0);
 }
 
-void launch_restore(const int32_t* sseg, int64_t n, const int32_t* perm, const DevStatus* st_dev,
-                    const SegStatus* segst, const double* Q0, const double* pos0, const double* S0, double* Q_slots,
-                    double* pos_slots, double* S_slots, hipStream_t st) {
+void launch_restore(const int32_t* sseg, int64_t n, const int32_t* perm, const SegStatus* segst, const double* Q0,
+                    const double* pos0, const double* S0, const float* mach0, double* Q_slots, double* pos_slots,
+                    double* S_slots, float* mach_slots, hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_restore, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, sseg, n, perm, st_dev, segst,
-                     Q0, pos0, S0, Q_slots, pos_slots, S_slots);
+  hipLaunchKernelGGL(k_restore, dim3(blocks_for(n, kThreads)), dim3(kThreads), 0, st, sseg, n, perm, segst, Q0, pos0,
+                     S0, mach0, Q_slots, pos_slots, S_slots, mach_slots);
 }
 
 template <typename R>
@@ -1358,7 +1365,7 @@ void launch_init_charges(const SegDesc* segs, const int32_t* sseg, int64_t n, co
                                  const unsigned long long*, const int32_t*, const R*, const double*,              \
                                  const int32_t*, const double*, double*, const double*, const double*, double*,   \
                                  double*, const SegStatus*, DevStatus*, SegStatus*, hipStream_t, bool,            \
-                                 const double*, const R*, const float*, double*, float*);                         \
+                                 const double*, const R*, const float*, double*, float*, float*);                 \
   template void launch_half_park<R>(const SegDesc*, const int32_t*, int64_t, const int32_t*, const R*,            \
                                     const double*, const SegStatus*, const double*, double*, R*, double*,         \
                                     hipStream_t);                                                                 \

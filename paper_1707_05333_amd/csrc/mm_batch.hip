@@ -277,7 +277,7 @@ mm_status mm_batch_step(mm_batch* b, mm_sim_info* info, int32_t info_cap, int32_
   E.enqueue_step(b->pos, b->w, b->Q, hi, b->slot_seg, n, nbt, any_fresh);
   if (mm_status r = E.readback()) return b->fail(r, E.err);
   E.finish_timing();
-  if (mm_status r = E.undo_failed(b->pos, b->Q, nullptr)) return b->fail(r, E.err);
+  if (mm_status r = E.undo_failed(b->pos, b->Q, nullptr, nullptr)) return b->fail(r, E.err);
   const DevStatus& g = *E.st_host;
   const bool global_cap = (g.flags & F_FACECAP) != 0;
   std::string msg;

@@ -82,6 +82,7 @@ struct Engine {
   DevStatus* st_host = nullptr;       // pinned mirror
   int nseg = 0;
   bool table_in_flight = false;       // work that reads the pinned table may still run
+  bool in_update = false;             // a segment of the last step failed in the update
   // Mesh currently held.
   int64_t n = 0, n_faces = 0, nbt = 0;
   // List lengths of the last tessellation read back (none yet: -1); they
@@ -151,10 +152,14 @@ struct Engine {
   // Waits for the stream and copies the status of the launch set and of
   // the first nseg segments to the host mirrors.
   mm_status readback();
-  // After the readback of a step: if a segment failed, puts the failed
-  // segments' start-of-step state back into the caller's arrays of the last
-  // enqueue_step and waits for it.
-  mm_status undo_failed(double* pos, double* Q, double* S);
+  // After the readback of a step: if segments failed in the update (a failure
+  // found before leaves the caller's arrays alone), puts their start-of-step
+  // state back into the caller's arrays of the last enqueue_step, and the Mach
+  // numbers these held, and waits for it.
+  mm_status undo_failed(double* pos, double* Q, double* S, float* mach);
+  // The caller's Mach numbers before the update (the shell pass's bounds are
+  // free once the cells are built).
+  float* mach0() const { return (float*)rmax2; }
   void finish_timing();
   // Status code and message for failure bits (of the whole set or a segment).
   mm_status check_flags(int flags, int bad_cell, std::string& msg) const;

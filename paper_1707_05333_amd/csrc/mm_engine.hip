@@ -368,7 +368,7 @@ void enqueue_hydro(Engine& E, double* pos, double* w_slots, double* Q, int64_t n
   E.mark(7);
   launch_update<R>(E.segs, E.sseg, n, E.counts, E.soff, E.csr, phi, E.geo, E.perm, E.Qs, Q, E.spos, E.w, pos, w_slots,
                    E.segst, E.st, E.segst, E.stream, half, ent ? E.Ss : nullptr, (const R*)E.phiX, E.machF, S_slots,
-                   mach_slots);
+                   mach_slots, E.mach0());
 }
 
 }  // namespace
@@ -401,6 +401,11 @@ mm_status Engine::readback() {
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return fail(MM_EHIP, std::string("status readback: ") + hipGetErrorString(e));
   table_in_flight = false;
+  in_update = (st_host->flags & F_UPDATE) != 0;
+  if (in_update) {
+    st_host->flags &= ~F_UPDATE;
+    for (int k = 0; k < nseg; ++k) segst_host[k].flags &= ~F_UPDATE;
+  }
   if (!lists_new) return MM_OK;
   lists_new = false;
   const DevStatus& s = *st_host;
@@ -411,9 +416,11 @@ mm_status Engine::readback() {
   return MM_OK;
 }
 
-mm_status Engine::undo_failed(double* pos, double* Q, double* S) {
-  if (!st_host->flags) return MM_OK;
-  launch_restore(sseg, n, perm, st, segst, Qs, remeshed ? pos0 : spos, Ss, Q, pos, S, stream);
+mm_status Engine::undo_failed(double* pos, double* Q, double* S, float* mach) {
+  if (!in_update) return MM_OK;
+  if (!Ss) S = nullptr;
+  if (!S) mach = nullptr;
+  launch_restore(sseg, n, perm, segst, Qs, remeshed ? pos0 : spos, Ss, mach0(), Q, pos, S, mach, stream);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   return e == hipSuccess ? MM_OK : fail(MM_EHIP, std::string("restoring the state: ") + hipGetErrorString(e));

@@ -39,6 +39,8 @@ enum : int {
   F_VOLUME = 1 << 9,      // non-positive cell volume
   F_BOX = 1 << 10,        // stencil wider than the periodic box allows
   F_DENSE = 1 << 11,      // a grid bucket holds more than kDenseMax points
+  F_UPDATE = 1 << 12,     // with F_NONFINITE: found by the update, which has written every cell of the segment
+                          // (a segment that failed before has none written); not reported
 };
 
 // Status of the whole launch set, read back once per call.
@@ -416,19 +418,19 @@ void launch_flux(const SegDesc* segs, int64_t nf_host, const unsigned long long*
 // Update of the charges with the floors after the step, and the drift, into
 // the caller's slot-order arrays Q, pos, w and (entropy column, Ss not NULL)
 // S and each cell's largest face Mach number (mach may be NULL).  Qs, Ss and
-// spos keep the start-of-step values in internal order: launch_restore puts
-// them back for every segment whose status holds a failure (all of them
-// after an overflow of the shared face capacity).
+// spos keep the start-of-step values in internal order and mach0 (scratch, n
+// values) receives the Mach numbers that mach held: launch_restore puts them
+// back for every segment that failed in the update.
 template <typename R>
 void launch_update(const SegDesc* segs, const int32_t* sseg, int64_t n, const unsigned long long* counts,
                    const unsigned long long* soff, const int32_t* csr, const R* phi, const double* geo,
                    const int32_t* perm, const double* Qs, double* Q_slots, const double* spos, const double* w,
                    double* pos_slots, double* w_slots, const SegStatus* dt_src, DevStatus* st_dev, SegStatus* segst,
                    hipStream_t st, bool drift_from_slots, const double* Ss, const R* phiX, const float* machF,
-                   double* S_slots, float* mach_slots);
-void launch_restore(const int32_t* sseg, int64_t n, const int32_t* perm, const DevStatus* st_dev,
-                    const SegStatus* segst, const double* Q0, const double* pos0, const double* S0, double* Q_slots,
-                    double* pos_slots, double* S_slots, hipStream_t st);
+                   double* S_slots, float* mach_slots, float* mach0);
+void launch_restore(const int32_t* sseg, int64_t n, const int32_t* perm, const SegStatus* segst, const double* Q0,
+                    const double* pos0, const double* S0, const float* mach0, double* Q_slots, double* pos_slots,
+                    double* S_slots, float* mach_slots, hipStream_t st);
 // Half-step mesh: U_half and w of internal cell s go to slot perm[s], and
 // pos_half[slot] = wrap(pos[slot] + w dt/2) (single segment, slots = cells).
 template <typename R>

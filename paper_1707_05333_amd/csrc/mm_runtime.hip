@@ -347,7 +347,7 @@ static mm_status step_common(mm_ctx* c, int64_t n, double* pos, double* w, doubl
   if (mm_status r = readback(c)) return r;
   fill_info(c, info, dt_max);
   c->E.finish_timing();
-  if (mm_status r = c->E.undo_failed(pos, Q, S)) return fail(c, r, c->E.err);
+  if (mm_status r = c->E.undo_failed(pos, Q, S, mach)) return fail(c, r, c->E.err);
   if (mm_status r = check_status(c)) return r;
   finish_mesh(c, n);
   return MM_OK;
