@@ -22,7 +22,10 @@ using namespace mm;
 
 namespace {
 
-constexpr int64_t kPoolBytesPerSlot = 8 * (3 + 5 + 3) + 4;   // pos, Q, w, slot segment
+// pos, Q, w, slot segment.  (The second w comes out of the 256 bytes per cell
+// that engine_bytes_per_cell counts beyond what the staged faces take, so the
+// footprint of a simulation stays what callers have budgeted with.)
+constexpr int64_t kPoolBytesPerSlot = 8 * (3 + 5 + 3) + 4;
 constexpr int64_t kPoolSlotsPerCell = 2;                      // slot pool over-provisioned against fragmentation
 constexpr int64_t kMinPoints = 3;
 
@@ -47,7 +50,11 @@ struct mm_batch {
   int precision = MM_FP64;
   int max_sims = 0;
   int64_t slot_cap = 0;
-  double *pos = nullptr, *Q = nullptr, *w = nullptr;
+  // w: mesh velocities of each simulation's last step.  A step writes w_next,
+  // and the two change places once it is known how it ended: a simulation that
+  // failed keeps those of its last step (copied over, so that a parked one has
+  // them in both).
+  double *pos = nullptr, *Q = nullptr, *w = nullptr, *w_next = nullptr;
   int32_t* slot_seg = nullptr;
   std::vector<Sim> sims;                                  // by id
   std::vector<std::pair<int64_t, int64_t>> free_ranges;   // [start, length), sorted by start
@@ -163,6 +170,7 @@ mm_status mm_batch_create(mm_batch** out, int32_t precision, int64_t hbm_budget,
     ok &= hipMalloc((void**)&b->pos, sizeof(double) * 3 * b->slot_cap) == hipSuccess;
     ok &= hipMalloc((void**)&b->Q, sizeof(double) * 5 * b->slot_cap) == hipSuccess;
     ok &= hipMalloc((void**)&b->w, sizeof(double) * 3 * b->slot_cap) == hipSuccess;
+    ok &= hipMalloc((void**)&b->w_next, sizeof(double) * 3 * b->slot_cap) == hipSuccess;
     ok &= hipMalloc((void**)&b->slot_seg, sizeof(int32_t) * b->slot_cap) == hipSuccess;
     if (!ok) r = MM_ENOMEM;
   }
@@ -180,7 +188,7 @@ mm_status mm_batch_create(mm_batch** out, int32_t precision, int64_t hbm_budget,
 mm_status mm_batch_destroy(mm_batch* b) {
   if (!b) return MM_EINVAL;
   if (b->E.stream || b->pos) (void)hipStreamSynchronize(b->E.stream);
-  void* ptrs[] = {b->pos, b->Q, b->w, b->slot_seg};
+  void* ptrs[] = {b->pos, b->Q, b->w, b->w_next, b->slot_seg};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   b->E.release();
@@ -274,12 +282,23 @@ mm_status mm_batch_step(mm_batch* b, mm_sim_info* info, int32_t info_cap, int32_
     b->layout_dirty = false;
   }
   E.n = n;
-  E.enqueue_step(b->pos, b->w, b->Q, hi, b->slot_seg, n, nbt, any_fresh);
+  E.enqueue_step(b->pos, b->w_next, b->Q, hi, b->slot_seg, n, nbt, any_fresh);
   if (mm_status r = E.readback()) return b->fail(r, E.err);
   E.finish_timing();
   if (mm_status r = E.undo_failed(b->pos, b->Q, nullptr, nullptr)) return b->fail(r, E.err);
   const DevStatus& g = *E.st_host;
   const bool global_cap = (g.flags & F_FACECAP) != 0;
+  if (g.flags) {
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < nseg && e == hipSuccess; ++k) {
+      const Sim& s = b->sims[b->order[k]];
+      if (E.segst_host[k].flags || global_cap)
+        e = hipMemcpyAsync(b->w_next + 3 * s.base, b->w + 3 * s.base, sizeof(double) * 3 * s.n,
+                           hipMemcpyDeviceToDevice, E.stream);
+    }
+    if (e != hipSuccess) return b->fail(MM_EHIP, std::string("keeping the mesh velocities: ") + hipGetErrorString(e));
+  }
+  std::swap(b->w, b->w_next);
   std::string msg;
   int out = 0;
   for (int k = 0; k < nseg; ++k) {

@@ -3,8 +3,10 @@ cell so hot that its fluxes overflow (pressure times velocity beyond the type's
 range), or an entropy charge that is not a number.  The update has then written
 the caller's arrays, and the call puts them back: positions, charges and
 entropy charges are bitwise those before the call, and so are the Mach numbers
-of the call before.  The mesh velocities of a single simulation, which may hold
-partial results after an error, show that the update ran."""
+of the call before; in a batch the mesh velocities are those of the last step,
+and the other simulations advance exactly as alone.  The mesh velocities of a
+single simulation, which may hold partial results after an error, show that the
+update ran."""
 import numpy as np
 import pytest
 
@@ -87,3 +89,44 @@ def test_entropy_step_is_undone(prec, what):
         S[37] = float("nan")
     mach = torch.full((wl.n,), -3.0, dtype=torch.float32, device="cuda")
     _fails_in_update(M, lambda: mm.step_entropy(pos, w, Q, S, mach), [pos, Q, S, mach], w)
+
+
+@pytest.mark.parametrize("prec,speeds", [("fp64", (102.58, 102.63, 102.68)), ("mixed", (12.66, 12.71, 12.76))])
+def test_batch_simulation_is_undone_alone(prec, speeds):
+    # Gas that falls in from all sides, a little slower than a fall whose first
+    # step overflows: some steps succeed, then one fails in its update.  What can
+    # be read of a failed simulation is the state and the mesh velocities of its
+    # last step.
+    import paper_1707_05333_amd as M
+    import torch
+    well = [W.c4_kelvin_helmholtz(1, n_min=1500, n_max=1600), W.c2_sod(shape=(32, 8, 8), box=(4.0, 1.0, 1.0))]
+    fall = W.c1_uniform_random_velocity(n_side=8)
+    start = [(well[0], well[0].prim)]
+    for e in speeds:
+        prim = np.ones((fall.n, 5))
+        prim[:, 1:4] = 10.0 ** e * (0.5 - fall.pos)
+        prim[:, 4] = 0.1 * 10.0 ** (2 * e)
+        start.append((fall, prim))
+    start.append((well[1], well[1].prim))
+    _case("batch", prec=prec, n=[wl.n for wl, _ in start])
+    par = [M.make_params(box=wl.box, precision=prec, **wl.params) for wl, _ in start]
+    B = M.Batch(2 * sum(M.batch_footprint(wl.n, prec) for wl, _ in start), max_sims=8, precision=prec)
+    ids = [B.admit(p, dev(wl.pos), dev(prim)) for (wl, prim), p in zip(start, par)]
+    steps, last, failed = 8, {}, {}
+    for _ in range(steps):
+        for r in B.step():
+            if r["status"] == 0:
+                last[r["sim"]] = B.read(r["sim"])
+            else:
+                assert r["status"] == MM_ENONFINITE
+                failed[r["sim"]] = r["steps"]
+        for s in failed:   # (and it stays what it was while the others go on)
+            if failed[s]:
+                assert [k for k, (a, b) in enumerate(zip(B.read(s), last[s])) if not torch.equal(a, b)] == []
+    assert max(failed.values()) > 0 and ids[0] not in failed and ids[-1] not in failed
+    for k in (0, -1):
+        alone = M.Batch(2 * M.batch_footprint(start[k][0].n, prec), max_sims=1, precision=prec)
+        s = alone.admit(par[k], dev(start[k][0].pos), dev(start[k][1]))
+        for _ in range(steps):
+            alone.step()
+        assert all(torch.equal(a, b) for a, b in zip(B.read(ids[k]), alone.read(s)))
