@@ -391,8 +391,12 @@ __device__ inline void list_dense(int64_t b, int64_t lo, int cnt, unsigned long 
 // Per bucket: a bucket of at most kDense points gets its slot order back
 // (ranks by counting, in registers: the scatter filled it in arrival order)
 // and its cells' positions; a denser one is listed for the block sort, which
-// does both.  Buckets above kDenseMax points fail the call (their points
-// stay where the scatter put them and are read whole).
+// does both.  Buckets above kDenseMax points fail the call: their points stay
+// where the scatter put them and are read whole.  They are listed in pieces of
+// kDenseMax cells (the last one ends with the bucket, over the one before), as
+// -1 - first cell, for the block sort to write positions and segments: a blown-up
+// state may have every point in one bucket, and this thread alone took 66 ms for
+// 262,144 of them.
 __global__ void k_bucket_prep(const unsigned long long* __restrict__ boff, int64_t nbt, const double* __restrict__ pos,
                               const int32_t* __restrict__ slot_seg, int32_t* perm, double* __restrict__ spos,
                               int32_t* __restrict__ sseg, unsigned long long* __restrict__ sbase,
@@ -419,7 +423,10 @@ __global__ void k_bucket_prep(const unsigned long long* __restrict__ boff, int64
   }
   if (cnt > kDenseMax) {
     seg_fail(st, segst, slot_seg ? slot_seg[perm[lo]] : 0, F_DENSE, (int)lo);
-    for (int64_t k = 0; k < cnt; ++k) put_cell(lo + k, perm[lo + k], pos, slot_seg, perm, spos, sseg);
+    const int pieces = (int)((cnt + kDenseMax - 1) / kDenseMax);
+    const int d0 = atomicAdd(&st->n_dense, pieces);
+    for (int k = 0; k < pieces; ++k)
+      dense[d0 + k] = (int32_t)(-1 - (k + 1 < pieces ? lo + (int64_t)k * kDenseMax : lo + cnt - kDenseMax));
     return;
   }
   list_dense(b, lo, (int)cnt, sbase, dense, dcells, st);
@@ -512,7 +519,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(SegDesc one, SegDe
 // Orders the points of each dense bucket by sub-bucket (x fastest), then by
 // slot, with a bitonic sort of (sub-bucket << 32 | slot) keys in LDS, and
 // writes the bucket's sub-bucket offsets: entry k counts its points in
-// sub-buckets below k (k = 0 .. s^3).  One block per bucket of the list.
+// sub-buckets below k (k = 0 .. s^3).  One block per entry of the list.
 constexpr int kDenseThreads = 256;
 
 __global__ __launch_bounds__(kDenseThreads) void k_dense_order(
@@ -525,6 +532,11 @@ __global__ __launch_bounds__(kDenseThreads) void k_dense_order(
   const int t = threadIdx.x;
   for (int it = blockIdx.x; it < nd; it += gridDim.x) {
     const int64_t b = dense[it];
+    if (b < 0) {   // a piece of a bucket beyond the sort
+      for (int64_t s = -1 - b + t; s < -1 - b + kDenseMax; s += kDenseThreads)
+        put_cell(s, perm[s], pos, slot_seg, perm, spos, sseg);
+      continue;
+    }
     const int64_t lo = (int64_t)boff[b];
     const int cnt = (int)((int64_t)boff[b + 1] - lo);
     const int s = sub_size((unsigned)cnt);

@@ -50,7 +50,8 @@ struct DevStatus {
   int max_faces;
   int bad_cell;                  // lowest internal cell index with a failure
   int n_overflow;                // of those, cells whose first-pass candidates overflowed
-  int n_dense;                   // buckets with a sub-grid (length of the sort's dense-bucket list)
+  int n_dense;                   // length of the sort's list of dense buckets (those with a sub-grid, and pieces of
+                                 // buckets beyond the sort)
   int n_dense_cells;             // cells for the dense first pass
   int n_redo;                    // cells the two-cell first pass hands to the one-cell one
   int n_dredo;                   // cells the two-cell dense pass hands to the one-cell one

@@ -4,6 +4,8 @@ points throughout: clusters hundreds of times denser than the mean, with
 thousands of cells for the dense passes and cells handed from pass to pass."""
 from __future__ import annotations
 
+import time
+
 import numpy as np
 import pytest
 
@@ -125,3 +127,38 @@ def test_clustered_simulation_alone_and_in_a_mix(precision, n, n_in):
     alone = run(False, False)
     for before, beside in ((False, True), (True, True), (True, False)):
         assert _unlike(run(before, beside), alone) == [], (before, beside)
+
+
+@pytest.mark.parametrize("fill", ["one spot", "nan"])
+def test_refusal_of_an_overfull_bucket_is_quick(fill):
+    # Every point in one bucket (a blown-up state: every position not a
+    # number): refused, in a time of the order of a tessellation of as many
+    # uniform points (2 ms; one thread that copied the bucket took 66 ms).
+    import torch
+    import paper_1707_05333_amd as M
+    n = 262144
+    _case("overfull bucket", n=n, fill=fill)
+    mm = M.MovingMesh(n, M.make_params(box=BOX))
+
+    def best(pos, fails):
+        t = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            if fails:
+                with pytest.raises(M.MMError) as e:
+                    mm.tessellate(pos)
+                assert e.value.name == ("MM_EINVAL" if fill == "nan" else "MM_ECAPACITY")
+            else:
+                mm.tessellate(pos)
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    if fill == "nan":
+        bad = torch.full((n, 3), float("nan"), dtype=torch.float64, device="cuda")
+    else:
+        bad = dev(0.52 + 1e-5 * np.random.default_rng(1).uniform(-1, 1, (n, 3)))
+    uniform = best(dev(W.poisson_points(n, BOX, seed=1)), False)
+    refused = best(bad, True)
+    print(f"uniform {1e3 * uniform:.2f} ms, refused {1e3 * refused:.2f} ms", flush=True)
+    assert refused < 12 * uniform
