@@ -290,25 +290,26 @@ __device__ void reset_status(DevStatus* s, SegStatus* segst, int nseg, bool reme
 
 __global__ void k_status_reset(DevStatus* s, SegStatus* segst, int nseg) { reset_status(s, segst, nseg, false); }
 
-// Start of a tessellation: block 0 resets the status and, with host_segs
-// set, copies the segment table from pinned host memory (one segment: the
-// descriptor travels as an argument, `one`); every block clears its part of
-// the bucket counters.
+// Start of a tessellation: block 0 resets the status; every block clears its
+// part of the bucket counters and, with host_segs set, copies its part of the
+// segment table from pinned host memory (one segment: the descriptor travels as
+// an argument, `one`).  One block's loads from the host are too few in flight for
+// a large table: with it and one block publishing the reports, a step of 16,384
+// simulations of 64 points took 8.0 ms instead of 5.5, and one of 4,096 2.04
+// instead of 1.48.
 __global__ __launch_bounds__(256) void k_begin(SegDesc one, const SegDesc* __restrict__ host_segs, SegDesc* segs,
                                                int nseg, bool remesh, uint32_t* __restrict__ bcount, int64_t nbt,
                                                DevStatus* st, SegStatus* segst) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < nbt) bcount[i] = 0u;
-  if (blockIdx.x != 0) return;
-  reset_status(st, segst, nseg, remesh);
-  if (remesh) return;
-  if (host_segs) {
+  if (host_segs && !remesh) {
     const uint64_t* src = reinterpret_cast<const uint64_t*>(host_segs);
     uint64_t* dst = reinterpret_cast<uint64_t*>(segs);
-    for (int64_t k = threadIdx.x; k < (int64_t)(sizeof(SegDesc) / 8) * nseg; k += blockDim.x) dst[k] = src[k];
-  } else if (threadIdx.x == 0) {
-    segs[0] = one;
+    for (int64_t k = i; k < (int64_t)(sizeof(SegDesc) / 8) * nseg; k += (int64_t)gridDim.x * blockDim.x) dst[k] = src[k];
   }
+  if (blockIdx.x != 0) return;
+  reset_status(st, segst, nseg, remesh);
+  if (!host_segs && !remesh && threadIdx.x == 0) segs[0] = one;
 }
 
 // Copies the status of the launch set and of its segments to pinned host
@@ -316,13 +317,13 @@ __global__ __launch_bounds__(256) void k_begin(SegDesc one, const SegDesc* __res
 __global__ __launch_bounds__(256) void k_publish(const DevStatus* __restrict__ st, const SegStatus* __restrict__ segst,
                                                  int nseg, DevStatus* host_st, SegStatus* host_segst) {
   static_assert(sizeof(DevStatus) % 8 == 0 && sizeof(SegStatus) % 8 == 0, "copied in 8-byte words");
-  const int t = threadIdx.x;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const uint64_t* a = reinterpret_cast<const uint64_t*>(st);
   uint64_t* b = reinterpret_cast<uint64_t*>(host_st);
-  if (t < (int)(sizeof(DevStatus) / 8)) b[t] = a[t];
+  if (t < (int64_t)(sizeof(DevStatus) / 8)) b[t] = a[t];
   const uint64_t* c = reinterpret_cast<const uint64_t*>(segst);
   uint64_t* d = reinterpret_cast<uint64_t*>(host_segst);
-  for (int64_t k = t; k < (int64_t)(sizeof(SegStatus) / 8) * nseg; k += blockDim.x) d[k] = c[k];
+  for (int64_t k = t; k < (int64_t)(sizeof(SegStatus) / 8) * nseg; k += (int64_t)gridDim.x * blockDim.x) d[k] = c[k];
 }
 
 // Bucket of a point in its segment's grid, or the grid's first bucket for a
@@ -633,7 +634,9 @@ void launch_status_reset(DevStatus* s, SegStatus* segst, int nseg, hipStream_t s
 
 void launch_publish(const DevStatus* s, const SegStatus* segst, int nseg, DevStatus* host_s, SegStatus* host_segst,
                     hipStream_t st) {
-  hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, st, s, segst, nseg, host_s, host_segst);
+  const int64_t words = (int64_t)(sizeof(SegStatus) / 8) * nseg;
+  const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>((words + 255) / 256, 1024));
+  hipLaunchKernelGGL(k_publish, dim3(blocks), dim3(256), 0, st, s, segst, nseg, host_s, host_segst);
 }
 
 void launch_sort(const double* pos, int64_t n_slots, const int32_t* slot_seg, const SegDesc* segs_host, SegDesc* segs,

@@ -129,6 +129,29 @@ def test_clustered_simulation_alone_and_in_a_mix(precision, n, n_in):
         assert _unlike(run(before, beside), alone) == [], (before, beside)
 
 
+def test_many_small_simulations():
+    # The table of the simulations and their reports go to the device and back
+    # in many blocks.
+    import paper_1707_05333_amd as M
+    wl = W.c1_uniform_random_velocity(n_side=4)
+    count, precision = 3000, "mixed"
+    _case("many simulations", n=wl.n, count=count)
+    B = M.Batch(M.batch_footprint(wl.n, precision) * count, max_sims=count, precision=precision)
+    pos, prim = dev(wl.pos), dev(wl.prim)
+    ids = [B.admit(M.make_params(box=wl.box, precision=precision, **{**wl.params, "cfl": 0.2 + 1e-5 * k}), pos, prim)
+           for k in range(count)]
+    for _ in range(2):
+        rep = B.step()
+    assert [r["sim"] for r in rep] == ids and all(r["status"] == 0 and r["steps"] == 2 for r in rep)
+    for k in (0, 1, 255, 256, 1023, 1500, count - 1):
+        A = M.Batch(M.batch_footprint(wl.n, precision) * 2, max_sims=1, precision=precision)
+        s = A.admit(M.make_params(box=wl.box, precision=precision, **{**wl.params, "cfl": 0.2 + 1e-5 * k}), pos, prim)
+        for _ in range(2):
+            r, = A.step()
+        assert rep[k]["dt"] == r["dt"] and rep[k]["t"] == r["t"]
+        assert _unlike(A.read(s), B.read(ids[k])) == []
+
+
 @pytest.mark.parametrize("fill", ["one spot", "nan"])
 def test_refusal_of_an_overfull_bucket_is_quick(fill):
     # Every point in one bucket (a blown-up state: every position not a
