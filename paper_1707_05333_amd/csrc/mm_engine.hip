@@ -156,7 +156,7 @@ void reserve_buffers(Engine& E, Res& R, bool single) {
   R(&E.redo, N);
   R(&E.spos, 3 * N);
   R(&E.geo, 4 * N);
-  R(&E.rmax2, N);
+  R(&E.rmax2, std::max(N, (slot_cap + 1) / 2));   // also the sort's arrival ranks, an int32 per slot
   R(&E.minv, 6 * N);
   R(&E.bcount, nbcap);
   R(&E.boff, nbcap + 1);
@@ -306,7 +306,7 @@ void Engine::enqueue_tessellation(const double* pos, int64_t n_slots, const int3
   nbt = n_buckets;
   mark(0);
   // The arrival ranks live in the shell pass's bounds, which are written
-  // only after the sort (8 bytes per cell: room for two slots per cell).
+  // only after the sort.
   if (nseg > 1) table_in_flight = true;
   launch_sort(pos, n_slots, slot_seg, segs_host, segs, nseg, remesh, n_buckets, bcount, boff, scan_tmp, sbase, soffs,
               key, (int32_t*)rmax2, perm, sseg, spos, dcells, st, segst, stream);
