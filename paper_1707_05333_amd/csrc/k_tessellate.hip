@@ -2498,6 +2498,7 @@ __device__ void pair_cell(PairLds& S, const TessArgs& A, bool act, const int s) 
         if (shell == kShells1 || (!DENSE && ring > kPackRing) || ring > g.nb[0] || ring > g.nb[1] || ring > g.nb[2]) {
           if (hl == 0) redo_cell<DENSE>(A, s);
           act = go = false;
+          ring = 0;   // (a window of a wider ring than kPackRing may pack to no width, which is divided by)
         } else {
           lo2 = hi2;
           hi2 = nhi2;
