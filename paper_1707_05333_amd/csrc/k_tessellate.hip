@@ -152,12 +152,15 @@ __device__ __forceinline__ int half_incl_scan(int x) {
 }
 
 // Exclusive prefix sum in the order lane 0, 32, 1, 33, ...; *total gets the
-// wave's sum.  Called by the whole wavefront.
+// wave's sum.  (The swap of the lower half of one copy with the upper half of
+// another leaves lane l's value in lanes l and l + 32, and that of l + 32 likewise.)
+// Called by the whole wavefront.
 __device__ __forceinline__ int paired_excl_scan(int x, int* total) {
-  const int y = __shfl_xor(x, 32, 64);
-  const int incl = half_incl_scan(x + y);
+  const auto r = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
+  const int low = (int)r[0], both = low + (int)r[1];
+  const int incl = half_incl_scan(both);
   *total = __builtin_amdgcn_readlane(incl, 63);
-  return incl - (x + y) + ((__lane_id() & 32) ? y : 0);
+  return incl - both + ((__lane_id() & 32) ? low : 0);
 }
 
 // Wave-wide reductions with DPP lane moves (no LDS round trip): within each
