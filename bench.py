@@ -712,8 +712,9 @@ def main():
     t_cells = stage_ms["cells"] * 1e-3
     ach = TESS_FLOP_PER_CELL * n / t_cells / 1e12
     # (The stage's launches: the two-cells-per-wavefront pass over every
-    # cell, then the list-driven passes, which exit at once on uniform inputs.)
-    roofline = {"bound": "alu", "kernel": "k_tess_pair + k_tess_pass1_redo + k_tess_pass1_dense + k_tess_pass2",
+    # cell, then one pass over the cells it handed on, which are none or few on
+    # uniform inputs; clustered ones take four list passes instead.)
+    roofline = {"bound": "alu", "kernel": "k_tess_pair + k_tess_rest",
                 "achieved": ach,
                 "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_FP64_TFLOPS,
                 "traffic": tess_traffic(n) if args.workload == "sod" else None,

@@ -206,9 +206,10 @@ mm_status mm_fluxes(mm_ctx *ctx, const void *U_half, const void *grad_half, cons
  * Q: dev [n][5] in/out; info: host out (may be NULL).  Waits for the
  * stream once, at the end.  MM_EINVAL when p.mach_threshold > 0 (use
  * mm_step_entropy).
- * On any error pos and Q hold the values they had before the call when it
- * returns (a failed step is not written out, or put back), so the caller can
- * retry from them: after MM_ECAPACITY for the face
+ * On any error but MM_EHIP (after which the device's work is unknown, and with
+ * it every array of the call) pos and Q hold the values they had before the call
+ * when it returns (a failed step is not written out, or put back), so the caller
+ * can retry from them: after MM_ECAPACITY for the face
  * capacity (mm_last_error names it), with a context created with a larger
  * face_capacity; after MM_ENONFINITE (a start-of-step state that is not
  * finite, or a step that produced one), with a smaller dt_max or repaired
@@ -389,7 +390,9 @@ typedef struct {
   double step_p50, step_p99, step_mean;   /* ms, over simulation steps: the duration of the batch
                                              step each took part in, readback included */
   double turnaround_p50, turnaround_p99;  /* s, over requests: finished - arrival */
-  int32_t max_resident;      /* most simulations resident at once */
+  int32_t max_resident;      /* most simulations resident at once (holding their room; one that has
+                                completed holds it until the requests that arrived during its last
+                                step have been admitted) */
   int32_t reserved;
 } mm_serve_stats;
 
@@ -397,7 +400,8 @@ typedef struct {
  * admitted first come, first served, as soon as they have arrived (wall
  * clock from the call) and fit; every resident simulation advances one step
  * per batch step; a simulation that completes its steps (or fails) is read
- * out to pos_out/Q_out and evicted, and its room goes to the next arrivals.
+ * out to pos_out/Q_out and evicted, and its room goes to the next arrivals
+ * (those that arrived meanwhile and fit beside it are admitted before).
  * res [n_req] and stats (host) receive the outcome.  Returns MM_OK unless
  * the loop itself could not run. */
 mm_status mm_serve(mm_batch *b, const mm_request *req, int32_t n_req, mm_request_result *res,

@@ -106,7 +106,7 @@ def test_mesh_does_not_follow_from_the_one_before(orc, precision, n, n_in):
 def test_clustered_simulation_alone_and_in_a_mix(precision, n, n_in):
     import paper_1707_05333_amd as M
     pos, prim = _cluster(n, n_in, seed=n + 1)
-    big = W.c1_uniform_random_velocity(n_side=18)
+    big = W.c1_uniform_random_velocity(n_side=17)   # 4,913 cells: an odd offset, other cells share a wavefront
     _case("clustered simulation", n=n, precision=precision)
     p = M.make_params(box=BOX, precision=precision)
     pb = M.make_params(box=big.box, precision=precision, **big.params)
